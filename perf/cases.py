@@ -39,17 +39,17 @@ def listed():
         # the smallest: one sensor, 64 chains in double precision (the reference target); one wave, latency only
         _run("reference_f64", "single", "plain", "f64", 1, 64, 64, 500, 500, False),
         # the batch of 256 homogeneous groups x 256 chains, one wave per SIMD
-        _run("homogeneous_65k", "homogeneous", "plain", "f32", 256, 65_536, 128, 1000, 2000, True, sigma=8.0),
+        _run("homogeneous_65k", "homogeneous", "plain", "f32", 256, 65_536, 128, 1000, 40_000, True, sigma=8.0),
         # the benchmark's headline: 1000 ragged cone-source pairs in 100 layers, tuned proposal
-        _run("layered_1m", "layered", "plain", "f32", 1000, 1 << 20, 128, 1000, 1500, True, sigma=8.0),
+        _run("layered_1m", "layered", "plain", "f32", 1000, 1 << 20, 128, 1000, 4000, True, sigma=8.0),
         # gradient-informed sampling on the same geometry, 262,144 chains
-        _run("layered_langevin_262k", "layered", "langevin", "f32", 1000, 262_144, 128, 500, 1500, True),
+        _run("layered_langevin_262k", "layered", "langevin", "f32", 1000, 262_144, 128, 500, 4000, True),
         # the joint Langevin move (a chain count that leaves the last block ragged)
-        _run("layered_joint_50k", "layered", "joint", "f32", 193, 50_001, 128, 200, 1500, True, h=0.02),
+        _run("layered_joint_50k", "layered", "joint", "f32", 193, 50_001, 128, 200, 4000, True, h=0.02),
         # whole-path tree moves on the ragged batch
-        _run("layered_tree_262k", "layered", "tree", "f32", 1000, 262_144, 128, 200, 1000, True, sigma=4.0, h=0.3),
+        _run("layered_tree_262k", "layered", "tree", "f32", 1000, 262_144, 128, 200, 4000, True, sigma=4.0, h=0.3),
         # the two-region test at full scale: long paths, simplified-Liu mixture, von Mises-Fisher source
-        _run("regions_tree_65k", "regions", "tree", "f32", 8, 65_536, 256, 50, 50, False, h=0.3),
+        _run("regions_tree_65k", "regions", "tree", "f32", 8, 65_536, 256, 50, 500, False, h=0.3),
         # the score pass that follows every chunk of the headline batch
         dict(name="score_1m", kind="score", medium="layered", precision="f32", targets=1000, chains=1 << 20, cap=128,
              mean_n=4.0, out="score"),
@@ -87,7 +87,7 @@ def draw(rng):
         steps = 50 if medium == "regions" else rng.randint(100, 500) if sampler in ("plain", "langevin") \
             else rng.randint(50, 200)
         c = _run("", medium, sampler, precision, targets, chains, rng.choice([64, 96, 128]), steps,
-                 50 if medium == "regions" else 1000, medium != "regions" and rng.random() < 0.7,
+                 100 if medium == "regions" else 2000, medium != "regions" and rng.random() < 0.7,
                  sigma=rng.choice([1.0, 2.0, 4.0, 8.0]), h=0.02 if sampler == "joint" else 0.3 if sampler == "tree"
                  else 0.05, n_perturb=rng.choice([2, 3, 3, 4]))
     elif kind == "score":
@@ -217,7 +217,7 @@ def prepare(case, seed):
         w.update(sampler=SAMPLERS[case["sampler"]], mala_h=case["h"], sigma=case["sigma"], n_perturb=case["n_perturb"])
         if case["medium"] == "regions":
             # long paths equilibrate slowly from a straight start: begin at the equilibrium's length
-            s = _snapshot_sampler(w, seed, 28.0, case["precision"], False)
+            s = _snapshot_sampler(w, seed, 45.0, case["precision"], False)
         else:
             s = Sampler(w, device=DEV, precision=case["precision"])
         if case["tilt"]:
