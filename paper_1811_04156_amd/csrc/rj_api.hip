@@ -671,10 +671,11 @@ int rjpath_anchor(rjpath_medium* m, const rjpath_targets* t, double* anchor, voi
     if (r) return r;
     hipStream_t s = (hipStream_t)stream;
     const int T = t->n_targets;
-    r = grow_ws(m, sizeof(double) * T);
+    const int nchunk = anchor_chunks(T);
+    r = grow_ws(m, sizeof(double) * T * (1 + (size_t)nchunk));
     if (r) return r;
     KArgs a = make_args(m, t, nullptr);
-    HIPCHK(launch_anchor(a, m->d_gl, m->d_gl + 120, 120, m->d_ws, s), "anchor kernel launch");
+    HIPCHK(launch_anchor(a, m->d_gl, m->d_gl + 120, m->d_ws, m->d_ws + T, nchunk, s), "anchor kernel launch");
     HIPCHK(hipMemcpyAsync(anchor, m->d_ws, sizeof(double) * T, hipMemcpyDeviceToHost, s), "hipMemcpyAsync");
     HIPCHK(hipStreamSynchronize(s), "hipStreamSynchronize");
     return RJPATH_OK;

@@ -37,9 +37,11 @@ hipError_t launch_dlength(int T, int P, const double* score, const double* score
                           hipStream_t s);
 // *counter += steps on the device (keeps captured graphs advancing)
 hipError_t launch_advance(uint64_t* counter, uint64_t steps, hipStream_t s);
-// I_{n0} per target into anchor[T] (device).  `lay64` is the FP64 layer table.
-hipError_t launch_anchor(const KArgs& a, const double* gl_x, const double* gl_w, int ngl, double* anchor,
-                         hipStream_t s);
+// I_{n0} per target into anchor[T] (device), with `nchunk` blocks per target
+// whose sums go to part[T * nchunk] (nchunk = 1: straight to anchor; part unused)
+int anchor_chunks(int T);
+hipError_t launch_anchor(const KArgs& a, const double* gl_x, const double* gl_w, double* anchor, double* part,
+                         int nchunk, hipStream_t s);
 // per (target, group) sums of the chain statistics into red[T * groups * RD_NW] (zeroed by the kernel's caller)
 hipError_t launch_reduce(const KArgs& a, int groups, double* red, hipStream_t s);
 // flattens each target's sector tilt logw[T * (cap + 1)] from the pilot histogram

@@ -10,6 +10,7 @@
 // that overlap on one GPU share that array and race.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <mutex>
 #include <string>
@@ -138,7 +139,10 @@ hipError_t launch_intensity_noalloc(const KArgs& a, int groups, const double* an
     e = launch_reduce(a, groups, red, s);
     if (e != hipSuccess) return e;
     if (!anchor) {
-        e = launch_anchor(a, gl, gl + 120, 120, anc, s);
+        // the chunk sums take what the array has left (one block per target if that is too little)
+        const size_t left = (SCRATCH_DOUBLES - nred - a.T) / a.T;
+        const int nchunk = (int)std::min<size_t>(left, anchor_chunks(a.T));
+        e = launch_anchor(a, gl, gl + 120, anc, anc + a.T, nchunk, s);
         if (e != hipSuccess) return e;
         anchor = anc;
     }

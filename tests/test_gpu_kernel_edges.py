@@ -1,0 +1,60 @@
+"""Kernel branches at the sizes and shapes where they change over, against
+the FP64 oracle or the kernels' own general forms."""
+import numpy as np
+import pytest
+
+from paper_1811_04156_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def rj():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1811_04156_amd import rjpath
+    rjpath.load()
+    return rjpath
+
+
+def _cone_targets(edges, f_sl, det, sensor_z, copies=1):
+    """Cone sources (20 degrees about x) at z = 5 whose sensor (radius 0.165 m,
+    about 55 degrees off the axis, 8 m away) is centred at height sensor_z."""
+    L = len(edges) - 1
+    rng = np.random.default_rng(L)
+    media = W._layered_medium(rng.uniform(8, 30, L), rng.uniform(30, 90, L), np.full(L, 0.9), 0.0, 1.0)
+    media["edges"] = np.asarray(edges, np.float64)
+    media["f_sl"] = np.full(L, f_sl)
+    src = np.tile([0.0, 0.0, 5.0], (copies, 1))
+    sen = np.array([[4.6, 6.5, sensor_z]] * copies) + np.arange(copies)[:, None] * [0.3, 0.0, 0.0]
+    r, ax, half = np.full(copies, 0.165), np.tile([1.0, 0.0, 0.0], (copies, 1)), np.full(copies, np.deg2rad(20.0))
+    n, init = W._cone_start(src, sen, r, ax, half)
+    tg = W._targets(np.zeros(copies), src, sen, r, np.full(copies, W.EMIT_CONE), ax, half, n, init,
+                    np.full(copies, det), np.tile([0.0, -1.0, 0.0], (copies, 1)))
+    w = dict(name="cone", cap=16, **media, **tg, c_target=np.arange(copies, dtype=np.int32))
+    w.update(W.DEFAULT_RUN)
+    return w
+
+
+@pytest.mark.parametrize("case", ["one layer", "inside", "astride an edge", "over several edges", "mixture", "paper"])
+@pytest.mark.parametrize("copies", [1, 3])
+def test_one_scatter_anchor_branches(rj, case, copies):
+    """I_3 at the device's resolution against the oracle's same rule, for each
+    form of the cap integral: the sensor inside one layer, astride one edge
+    and over several edges (the general form, as for the simplified-Liu
+    mixture and the paper's angular response).  The same nodes summed in FP64:
+    rounding only, held to 1e-9 as for the layered batch's targets."""
+    from oracle import oracle as O
+    edges = {"one layer": [0.0, 100.0], "over several edges": [0.0, 3.0, 6.95, 7.0, 7.05, 12.0]}.get(
+        case, [0.0, 3.0, 7.0, 12.0])
+    z = 7.0 if case in ("astride an edge", "over several edges") else 5.8
+    w = _cone_targets(edges, 0.45 if case == "mixture" else 0.0, 1 if case == "paper" else 0, z, copies)
+    assert np.all(w["t_n0"] == 3)
+    an = rj.Sampler(w, precision="f32").anchor()
+    orc = O.Oracle(w)
+    for t in range(copies):
+        ref = orc.anchor_I3(t, 32, 32, 32, 8, 8)
+        print(case, t, an[t] / ref - 1)
+        assert an[t] == pytest.approx(ref, rel=1e-9), t
