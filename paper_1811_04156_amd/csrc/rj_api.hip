@@ -81,6 +81,7 @@ struct TuneKey {
 struct rjpath_medium {
     int n_media = 0, L_total = 0, n_edges = 0;
     bool layered = false; // some medium has more than one layer
+    bool even = true;     // every medium has more than one layer, evenly spaced
     bool has_sl = false;  // some layer has f_SL > 0
     MedInfo* d_info = nullptr;
     double* d_edge = nullptr;
@@ -174,7 +175,10 @@ int rjpath_init_medium(rjpath_medium** out, const rjpath_medium_desc* d, void* s
     h->n_media = M;
     h->L_total = L;
     h->n_edges = L + M;
-    for (int mi = 0; mi < M; ++mi) h->layered |= info[mi].cnt > 1;
+    for (int mi = 0; mi < M; ++mi) {
+        h->layered |= info[mi].cnt > 1;
+        h->even &= info[mi].cnt > 1 && info[mi].uniform;
+    }
     for (int l = 0; l < L; ++l) h->has_sl |= lay[l * LY_NW + LY_FSL] > 0;
     hipStream_t s = (hipStream_t)stream;
     auto up = [&](void** dst, const void* src, size_t bytes) -> hipError_t {
@@ -285,6 +289,7 @@ KArgs make_args(const rjpath_medium* m, const rjpath_targets* t, const rjpath_ch
     a.L_total = m->L_total;
     a.n_edges = m->n_edges;
     a.layered = m->layered;
+    a.even = m->even;
     a.has_sl = m->has_sl;
     a.tab_bytes = 0;
     if (m->layered && c->precision == RJPATH_F32) {

@@ -116,6 +116,7 @@ template <class R> struct Tgt {
     int n0;       // anchor sector
     // medium
     int mcnt, uniform;
+    bool hom;     // mcnt == 1 (a constant where the launch knows it, so that the lookups' tests fold)
     bool sl;      // false: no layer of the medium mixes in the Rayleigh-like term
     double ax, ay, az, e0, inv_h, usrc;
     // the FP32 layer lookups: the axis rounded, the source's position in layer
@@ -139,7 +140,7 @@ template <class R> __device__ __forceinline__ V3<R> from_eta(const Tgt<R>& T, V3
 }
 
 template <class R> __device__ __forceinline__ LayV<R> lay_at(const Tgt<R>& T, int l) {
-    if (T.mcnt == 1) return T.l0;
+    if (T.hom) return T.l0;
     LayV<R> ly = lay_load(T.lay + l * LY_NW);
     if (!T.sl) ly.fsl = (R)0;
     return ly;
@@ -152,7 +153,7 @@ template <class R> __device__ __forceinline__ double axis_u(const Tgt<R>& T, V3<
 // Layer l with edge_l <= u < edge_{l+1}, outer layers unbounded.
 template <class R> __device__ __forceinline__ int layer_u(const Tgt<R>& T, double u) {
     int cnt = T.mcnt;
-    if (cnt == 1) return 0;
+    if (T.hom) return 0;
     int l;
     if (T.uniform) {
         double q = floor((u - T.e0) * T.inv_h);
@@ -172,7 +173,7 @@ template <class R> __device__ __forceinline__ int layer_u(const Tgt<R>& T, doubl
 }
 
 template <class R> __device__ __forceinline__ int layer_at(const Tgt<R>& T, V3<R> p) {
-    if (T.mcnt == 1) return 0;
+    if (T.hom) return 0;
     return layer_u(T, axis_u(T, p));
 }
 
@@ -191,7 +192,7 @@ template <class R> struct LPt {
 // branching (the same index as layer_u).
 template <class R> __device__ __forceinline__ int layer_idx_s(const Tgt<R>& T, double u, double e0, double inv_h) {
     const int cnt = T.mcnt;
-    if (cnt == 1) return 0;
+    if (T.hom) return 0;
     if (!T.uniform) return layer_u(T, u);
     double q = floor((u - e0) * inv_h);
     q = fmin(fmax(q, 0.0), (double)(cnt - 1));
@@ -230,7 +231,7 @@ constexpr float LAYER_REACH = 64.0f;
 // source, or in a medium with unevenly spaced edges).
 template <class R> __device__ __forceinline__ LPt<R> lpt_fast(const Tgt<R>& T, V3<R> p, bool& near) {
     near = false;
-    if (T.mcnt == 1) return LPt<R>{(R)0, 0};
+    if (T.hom) return LPt<R>{(R)0, 0};
     if constexpr (sizeof(R) == 8) {
         const double u = axis_u(T, p);
         return LPt<R>{u, layer_idx(T, u)};
@@ -249,7 +250,7 @@ template <class R> __device__ __forceinline__ LPt<R> lpt_fast(const Tgt<R>& T, V
 // never negative (no-op in FP64).
 template <class R> __device__ __forceinline__ void lpt_settle(const Tgt<R>& T, V3<R> p, LPt<R>& q) {
     if constexpr (sizeof(R) == 4) {
-        if (T.mcnt == 1) return;
+        if (T.hom) return;
         const MedInfo& m = *T.mi;
         const int l = layer_idx_s(T, axis_u_m(T, p), m.e0, m.inv_h);
         R x = q.u;
@@ -272,7 +273,7 @@ template <class R> __device__ __forceinline__ LPt<R> lpt(const Tgt<R>& T, V3<R> 
 // FP64 so that short crossings of a layer boundary keep their precision.
 template <class R>
 __device__ __forceinline__ void seg_depth(const Tgt<R>& T, V3<R> P, V3<R> Q, R len, R& tc, R& tb) {
-    if (T.mcnt == 1) {
+    if (T.hom) {
         tc = T.l0.c * len;
         tb = T.l0.b * len;
         return;
@@ -304,7 +305,7 @@ __device__ __forceinline__ void seg_depth(const Tgt<R>& T, V3<R> P, V3<R> Q, R l
 // seg_depth with the endpoints' layer points already known.
 template <class R>
 __device__ __forceinline__ void seg_depth_lp(const Tgt<R>& T, LPt<R> P, LPt<R> Q, R len, R& tc, R& tb) {
-    if (T.mcnt == 1) {
+    if (T.hom) {
         tc = T.l0.c * len;
         tb = T.l0.b * len;
         return;
@@ -497,6 +498,7 @@ __device__ __forceinline__ void load_target(const KArgs& a, int t, Tgt<R>& T, co
     T.n0 = a.n0[t];
     const MedInfo mi = a.minfo[a.medium[t]];
     T.mcnt = mi.cnt;
+    T.hom = mi.cnt == 1;
     T.sl = true;
     T.uniform = mi.uniform;
     T.ax = mi.ax;

@@ -272,7 +272,7 @@ __device__ __forceinline__ void seg_depth_grad_lp(const Tgt<R>& T, LPt<R> P, LPt
     R F = s.tc * Mth<R>::rcp(s.len); // mean total coefficient along the segment
     dP = (-F) * s.u;
     dQ = F * s.u;
-    if (T.mcnt > 1 && P.l != Q.l) {
+    if (!T.hom && P.l != Q.l) {
         double cP = (double)T.lay[P.l * LY_NW + LY_C], cQ = (double)T.lay[Q.l * LY_NW + LY_C];
         const double du = (double)Q.u - (double)P.u;
         const double inv = du != 0.0 ? 1.0 / du : 0.0;
@@ -1188,11 +1188,15 @@ __device__ __forceinline__ void one_step(const KArgs& a, const Tgt<R>& T, const 
 // The step kernel.  MK: MK_HOM (every medium of the launch is homogeneous: the
 // layer lookups fold away), MK_LAY (layer tables read from HBM) or MK_LAY_LDS
 // (tables staged in LDS).  SL: some layer mixes in the Rayleigh-like term.
+// EVEN: every medium of the launch has several evenly spaced layers, so that
+// the lookups' tests for one layer and for uneven edges fold: each of the
+// four segments and seven layer reads of a step otherwise carries two
+// branches of its own (about 700 basic blocks in the kernel, which also keep
+// the loads of one segment from being issued with the next one's).
 // ---------------------------------------------------------------------------
 enum { MK_HOM = 0, MK_LAY = 1, MK_LAY_LDS = 2 };
 
-template <class R, int MK, int SAMP, bool SL>
-__global__ void __launch_bounds__(256) run_kernel(KArgs a) {
+template <class R, int MK, int SAMP, bool SL, bool EVEN> __device__ __forceinline__ void run_body(const KArgs& a) {
     constexpr bool TAB = MK == MK_LAY_LDS;
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, bs = blockDim.x;
@@ -1229,7 +1233,14 @@ __global__ void __launch_bounds__(256) run_kernel(KArgs a) {
     Tgt<R> T;
     load_target(a, t, T, tab);
     // compile-time facts of this instantiation (the lookups that test them fold)
-    if (MK == MK_HOM) T.mcnt = 1;
+    if (MK == MK_HOM) {
+        T.mcnt = 1;
+        T.hom = true;
+    }
+    if (EVEN) {
+        T.hom = false;
+        T.uniform = 1;
+    }
     T.sl = SL;
     if (!SL) T.l0.fsl = (R)0;
     PathRef<R, false> ps{lslots, (Vtx<R>*)a.verts + c, a.V, C};
@@ -1311,6 +1322,15 @@ __global__ void __launch_bounds__(256) run_kernel(KArgs a) {
         sp[14] += ln.ma;
         sp[15] += ln.ne;
     }
+}
+
+template <class R, int MK, int SAMP, bool SL> __global__ void __launch_bounds__(256) run_kernel(KArgs a) {
+    run_body<R, MK, SAMP, SL, false>(a);
+}
+
+template <class R, int MK, int SAMP, bool SL>
+__global__ void __launch_bounds__(256, sizeof(R) == 4 ? 2 : 1) run_even_layers_kernel(KArgs a) {
+    run_body<R, MK, SAMP, SL, true>(a);
 }
 
 } // namespace rj

@@ -58,3 +58,40 @@ def test_one_scatter_anchor_branches(rj, case, copies):
         ref = orc.anchor_I3(t, 32, 32, 32, 8, 8)
         print(case, t, an[t] / ref - 1)
         assert an[t] == pytest.approx(ref, rel=1e-9), t
+
+
+def _with_spare_medium(w):
+    """The same workload with one more, homogeneous medium that no target
+    uses: the launch then takes the kernels without the even-layers facts."""
+    w = dict(w)
+    L = len(w["lam_s"])
+    w["m_axis"] = np.concatenate([w["m_axis"], [[0.0, 0.0, 1.0]]])
+    w["m_layer_off"] = np.append(w["m_layer_off"], L).astype(np.int32)
+    w["m_layer_cnt"] = np.append(w["m_layer_cnt"], 1).astype(np.int32)
+    w["edges"] = np.concatenate([w["edges"], [0.0, 1.0]])
+    for k, v in (("lam_s", 20.0), ("lam_a", 80.0), ("g", 0.9), ("f_sl", 0.0)):
+        w[k] = np.append(w[k], v)
+    return w
+
+
+@pytest.mark.parametrize("f_sl", [0.0, 0.45])
+@pytest.mark.parametrize("sampler", [0, 1, 2, 3])
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+def test_even_layer_kernels_take_the_general_kernels_steps(rj, prec, sampler, f_sl):
+    """Evenly layered media run kernels of their own; the general ones do the
+    same arithmetic, so the paths agree bit for bit (257 chains: a ragged last
+    wave; 5 slots per chain, so that paths leave them)."""
+    w = W.layered_pairs(seed=4, pairs=7, chains=257, cap=40, n_layers=9, dz=4.0, dmin=4.0, dmax=25.0)
+    w["f_sl"] = np.where(np.arange(9) % 2 == 0, f_sl, 0.0)
+    w.update(sampler=sampler, mala_h=0.02 if sampler == 1 else 0.2, sigma=2.0, burn_in=0)
+    out = []
+    for ww in (w, _with_spare_medium(w)):
+        s = rj.Sampler(ww, precision=prec)
+        s.run(300, block=64, v_lds=5)
+        torch.cuda.synchronize()
+        n, v = s.get_state()
+        used = np.arange(s.cap)[None, :] < n[:, None]
+        out.append((n, np.where(used[..., None], v, 0.0), s.logp.cpu().numpy(), s.stats.cpu().numpy()))
+    for x, y in zip(*out):
+        assert np.array_equal(x, y)
+    assert out[0][0].max() > 6
