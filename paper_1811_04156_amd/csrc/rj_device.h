@@ -64,15 +64,24 @@ template <class R> __device__ __forceinline__ V3<R> pos(const Vtx<R>& v) { retur
 
 // ---------------------------------------------------------------------------
 // Philox4x32-10 (Salmon et al., SC'11): two 32x32->64 products per round via
-// v_mad_u64_u32, Weyl key schedule.
+// v_mad_u64_u32, Weyl key schedule.  The counters of a step are (chain, step,
+// step >> 32, block): after one round two words are still the same for the
+// whole wave, so the first two rounds use plain xors, which the compiler keeps
+// in scalar registers; from the third on the three-way xor is one v_bitop3_b32
+// (two v_xor_b32 otherwise: 32 of about 650 vector instructions of a step).
 // ---------------------------------------------------------------------------
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+    return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+
 __device__ __forceinline__ void philox4x32_10(uint32_t c[4], uint32_t k0, uint32_t k1) {
 #pragma unroll
     for (int r = 0; r < 10; ++r) {
         uint64_t p0 = (uint64_t)0xD2511F53u * c[0];
         uint64_t p1 = (uint64_t)0xCD9E8D57u * c[2];
-        uint32_t n0 = (uint32_t)(p1 >> 32) ^ c[1] ^ k0;
-        uint32_t n2 = (uint32_t)(p0 >> 32) ^ c[3] ^ k1;
+        const uint32_t h0 = (uint32_t)(p0 >> 32), h1 = (uint32_t)(p1 >> 32);
+        uint32_t n0 = r < 2 ? h1 ^ (c[1] ^ k0) : xor3(h1, c[1], k0);
+        uint32_t n2 = r < 3 ? h0 ^ (c[3] ^ k1) : xor3(h0, c[3], k1);
         c[0] = n0;
         c[1] = (uint32_t)p1;
         c[2] = n2;

@@ -75,6 +75,7 @@ template <class R, bool LO> struct PathRef {
         if (LO || v < V) return ((LdsScalar<R>)(lds + v * WAVE))[3];
         return glb[(size_t)v * C].w;
     }
+    __device__ __forceinline__ R lds_w(int v) const { return ((LdsScalar<R>)(lds + v * WAVE))[3]; }
     __device__ __forceinline__ void stw(int v, R x) const {
         if (LO || v < V) ((LdsScalar<R>)(lds + v * WAVE))[3] = x;
         else glb[(size_t)v * C].w = x;
@@ -512,10 +513,14 @@ __device__ __forceinline__ R vtx_term(const Tgt<R>& T, int kind, const LayV<R>& 
 }
 
 // The eight random words of one step: Philox4x32-10 blocks 0 and 1 of the
-// counter (chain, step).
-__device__ __forceinline__ void draw8(const StepCtx& sc, uint64_t step, uint32_t r[8]) {
-    uint32_t q0[4] = {sc.chain, (uint32_t)step, (uint32_t)(step >> 32), 0u};
-    uint32_t q1[4] = {sc.chain, (uint32_t)step, (uint32_t)(step >> 32), 1u};
+// counter (chain, step).  The products that depend on the chain alone are the
+// same at every step and the compiler keeps them in registers; the whole-path
+// moves need those registers (their walks spill otherwise) and form them again.
+template <int SAMP> __device__ __forceinline__ void draw8(const StepCtx& sc, uint64_t step, uint32_t r[8]) {
+    uint32_t chain = sc.chain;
+    if constexpr (SAMP == SAMP_JOINT || SAMP == SAMP_TREE) asm volatile("" : "+v"(chain));
+    uint32_t q0[4] = {chain, (uint32_t)step, (uint32_t)(step >> 32), 0u};
+    uint32_t q1[4] = {chain, (uint32_t)step, (uint32_t)(step >> 32), 1u};
     philox4x32_10(q0, sc.k0, sc.k1);
     philox4x32_10(q1, sc.k0, sc.k1);
     r[0] = q0[0]; r[1] = q0[1]; r[2] = q0[2]; r[3] = q0[3];
@@ -523,7 +528,8 @@ __device__ __forceinline__ void draw8(const StepCtx& sc, uint64_t step, uint32_t
 }
 
 // ---------------------------------------------------------------------------
-// Per-lane sampler state and statistics.
+// Per-lane sampler state and statistics.  Counts that are the same for every
+// lane (the steps of each class) are formed at the end of the launch.
 // ---------------------------------------------------------------------------
 template <class R> struct Lane {
     int n;
@@ -534,14 +540,40 @@ template <class R> struct Lane {
     double invw; // 1 / w(n) of the sector tilt
     double lwm, lw0, lwp; // log w(n - 1), log w(n), log w(n + 1)
     // statistics of this launch.  The sums that depend on n alone are kept
-    // lazily: `run` counts the counted steps spent at the current n and is
-    // folded in when n changes and at the end of the launch.
-    uint32_t run;
-    uint32_t hrun; // steps of this launch at the current n not yet added to the sector histogram
+    // lazily: the steps since `mark`, the step of the launch from which the
+    // chain has had its current n, are folded in when n changes and at the
+    // end of the launch.
+    int mark;
     double a1, a2, sl, sl2;
     uint64_t sn;
-    uint32_t cnt, c2, ncap, pp, pb, pd, ap, ab, ad, mp, ma;
+    uint32_t cnt, c2, ncap, pb, ap, ab, ad, mp, ma;
     uint32_t ne; // jump proposals rejected without a density evaluation (birth at cap, death at n = 2)
+};
+
+// Depths that a birth's segment scan reads at once (16 cover all but rare
+// long paths of the batched workloads; the FP64 and Langevin variants keep 8
+// so that their registers still allow two resident waves per SIMD where they
+// did).
+template <class R, int SAMP> __device__ constexpr int scan_slots() {
+    return (sizeof(R) == 4 && SAMP == SAMP_PLAIN) ? 16 : 8;
+}
+
+// Perturbation steps among the `count` steps from global index s0 on.
+__device__ __forceinline__ uint32_t count_perturbs(uint64_t s0, uint32_t count, int cycle, int n_perturb) {
+    auto upto = [&](uint64_t x) {
+        const uint64_t q = x / (uint64_t)cycle, f = x % (uint64_t)cycle;
+        return q * (uint64_t)n_perturb + (f < (uint64_t)n_perturb ? f : (uint64_t)n_perturb);
+    };
+    return (uint32_t)(upto(s0 + count) - upto(s0));
+}
+
+// The wave's place in the launch: step s of the launch (global index
+// step0 + s), counted in the statistics from s >= first on.
+struct StepLoop {
+    uint64_t step0;
+    int s, first;
+    bool tilt;
+    __device__ __forceinline__ bool counted() const { return s >= first; }
 };
 
 // 1 / w(n) = e^{-log w(n)} of the sector tilt, a weight of the statistics
@@ -552,29 +584,44 @@ template <class R> __device__ __forceinline__ double inv_tilt(double lw) {
     else return exp(-lw);
 }
 
-template <class R> __device__ __forceinline__ void fold_run(Lane<R>& ln, int n0, int cap, bool tilt) {
-    const uint32_t r = ln.run;
+// Adds the steps spent at the current n to the sums (counted steps) and to
+// the sector histogram (every step of the launch).
+template <class R> __device__ __forceinline__ void fold_run(Lane<R>& ln, int n0, const StepCtx& sc, const StepLoop& lp) {
+    const int from = ln.mark > lp.first ? ln.mark : lp.first;
+    const uint32_t r = lp.s > from ? (uint32_t)(lp.s - from) : 0u;
     const bool at0 = ln.n == n0;
     ln.cnt += r;
     ln.c2 += at0 ? r : 0u;
     ln.sn += (uint64_t)r * (uint64_t)ln.n;
-    ln.ncap += ln.n == cap ? r : 0u;
-    if (tilt) {
+    ln.ncap += ln.n == sc.cap ? r : 0u;
+    if (lp.tilt) {
         const double a = (double)r * ln.invw;
         ln.a1 += a;
         ln.a2 += at0 ? a : 0.0;
     }
-    ln.run = 0;
+    if (sc.hist && lp.s > ln.mark) atomicAdd(sc.hist + ln.n, (uint32_t)(lp.s - ln.mark));
+    ln.mark = lp.s;
 }
 
-// Adds the steps spent at the current n to the sector histogram.
-template <class R> __device__ __forceinline__ void fold_hist(Lane<R>& ln, const StepCtx& sc) {
-    if (sc.hist && ln.hrun) atomicAdd(sc.hist + ln.n, ln.hrun);
-    ln.hrun = 0;
+// The per-step sums of a counted step, after the move.
+template <class R> __device__ __forceinline__ void count_step(Lane<R>& ln) {
+    ln.sl += ln.L;
+    ln.sl2 += ln.L * ln.L;
 }
 
+template <class R>
+__device__ __forceinline__ void put_trace(const KArgs& a, const Lane<R>& ln, int c, int s, int move, int idx, int accepted,
+                                          R logA, R logu) {
+    if (a.trace && ln.live) {
+        double* tr = a.trace + ((size_t)c * a.trace_steps + a.trace_off + s) * RJPATH_TRACE_WORDS;
+        tr[0] = move;
+        tr[1] = accepted;
+        tr[2] = idx;
+        tr[3] = (double)logA;
+        tr[4] = (double)logu;
+    }
+}
 
-// One step of one lane; returns the move kind, writes log A / accepted / index.
 // ---------------------------------------------------------------------------
 // Tree-coordinate move of the whole path (App. "Path space coordinate
 // system"; Sec. "Path proposal distribution").  Interval (k, l), l - k >= 2,
@@ -755,16 +802,15 @@ __device__ __forceinline__ void tree_move(const Tgt<R>& T, const PathRef<R, LO>&
     }
 }
 
+// A perturbation step: moves interior vertex j or the end point (or, by the
+// sampler, every interior vertex, or the whole path in tree coordinates).
+// n does not change.  Returns the move kind, log A, the vertex and whether it
+// was accepted.
 template <class R, bool LO, int SAMP>
-__device__ __forceinline__ void step_body(const Tgt<R>& T, const PathRef<R, LO>& ps, const GlobalPath<R>& work,
-                                          Lane<R>& ln, const StepCtx& sc, uint64_t step, bool perturb, bool tree,
-                                          int& move, int& idx, int& accepted, R& logA, R& logu) {
-    uint32_t r[8];
-    draw8(sc, step, r);
+__device__ __forceinline__ void perturb_move(const Tgt<R>& T, const PathRef<R, LO>& ps, const GlobalPath<R>& work,
+                                             Lane<R>& ln, const StepCtx& sc, uint64_t step, const uint32_t r[8], R logu,
+                                             bool tree, int& move, int& idx, int& accepted, R& logA) {
     const int n = ln.n;
-    // (a chain that is not live rejects every proposal)
-    logu = ln.live ? Mth<R>::log(unif<R>(r[1])) : -Mth<R>::ninf();
-    move = MV_NULL;
     idx = -1;
     accepted = 0;
     logA = Mth<R>::ninf();
@@ -776,211 +822,227 @@ __device__ __forceinline__ void step_body(const Tgt<R>& T, const PathRef<R, LO>&
             return;
         }
     }
-    if (perturb) {
-        const int j = 1 + pick(r[0], (uint32_t)(n - 1));
-        idx = j;
-        const bool is_end = (j == n - 1);
-        constexpr bool MALA = SAMP == SAMP_JOINT;
-        if (MALA && !is_end) {
-            // ---------- joint Langevin move of all interior vertices ----------
-            move = MV_MALA;
-            const R h = (R)sc.mala_h, hh = (R)0.5 * h, sh = Mth<R>::sqrt(h);
-            // One loop walks the current path x and the proposal y together:
-            // the walk over x finishes the gradient of vertex k, which gives
-            // y_k, which the walk over y consumes at once (it finishes the
-            // gradient of y_{k-2}).  y goes to the work buffer only for the
-            // copy-back on acceptance.
-            double half_xi2 = 0.0, rev = 0.0;
-            ScoreWalker<R> wx, wy;
-            const V3<R> x0 = ps.p(0);
-            wx.init(T, x0);
-            wy.init(T, x0);
-            // y_k, y_{k-1}, y_{k-2} of the last vertex k fed to the y walk, kept
-            // as scalars so that the ring stays in registers
-            R y0x = x0.x, y0y = x0.y, y0z = x0.z, y1x = x0.x, y1y = x0.y, y1z = x0.z;
-            R y2x = x0.x, y2y = x0.y, y2z = x0.z;
-            // y_k from the gradient of x at vertex k (interior: Langevin step)
-            auto make_y = [&](int k, V3<R> g) __attribute__((always_inline)) {
-                V3<R> y = ps.p(k);
-                if (k >= 1 && k <= n - 2) {
-                    uint32_t q[4] = {sc.chain, (uint32_t)step, (uint32_t)(step >> 32), 2u + (uint32_t)k};
-                    philox4x32_10(q, sc.k0, sc.k1);
-                    V3<R> xi;
-                    box_muller3<R>(q[0], q[1], q[2], q[3], xi);
-                    half_xi2 += 0.5 * (double)dot(xi, xi);
-                    y = y + hh * g + sh * xi;
-                    work.glb[(size_t)k * work.C] = Vtx<R>{y.x, y.y, y.z, (R)0};
-                }
-                return y;
-            };
-            // the reverse-proposal term of vertex k from the gradient of y there
-            auto rev_term = [&](int k, V3<R> g, V3<R> yk) __attribute__((always_inline)) {
-                if (k >= 1 && k <= n - 2) {
-                    V3<R> d = ps.p(k) - yk - hh * g;
-                    rev += (double)dot(d, d) / (2.0 * (double)h);
-                }
-            };
-            auto feed_y = [&](V3<R> y) __attribute__((always_inline)) {
-                y2x = y1x;
-                y2y = y1y;
-                y2z = y1z;
-                y1x = y0x;
-                y1y = y0y;
-                y1z = y0z;
-                y0x = y.x;
-                y0y = y.y;
-                y0z = y.z;
-                const int ky = wy.k;
-                V3<R> gy;
-                if (wy.step(T, y, gy)) rev_term(ky - 2, gy, V3<R>{y2x, y2y, y2z});
-            };
-            V3<R> g, g2;
-            for (int k = 1; k < n; ++k) {
-                if (wx.step(T, ps.p(k), g) && k >= 3) feed_y(make_y(k - 2, g));
+    const int j = 1 + pick(r[0], (uint32_t)(n - 1));
+    idx = j;
+    const bool is_end = (j == n - 1);
+    if (SAMP == SAMP_JOINT && !is_end) {
+        // ---------- joint Langevin move of all interior vertices ----------
+        move = MV_MALA;
+        const R h = (R)sc.mala_h, hh = (R)0.5 * h, sh = Mth<R>::sqrt(h);
+        // One loop walks the current path x and the proposal y together:
+        // the walk over x finishes the gradient of vertex k, which gives
+        // y_k, which the walk over y consumes at once (it finishes the
+        // gradient of y_{k-2}).  y goes to the work buffer only for the
+        // copy-back on acceptance.
+        double half_xi2 = 0.0, rev = 0.0;
+        ScoreWalker<R> wx, wy;
+        const V3<R> x0 = ps.p(0);
+        wx.init(T, x0);
+        wy.init(T, x0);
+        // y_k, y_{k-1}, y_{k-2} of the last vertex k fed to the y walk, kept
+        // as scalars so that the ring stays in registers
+        R y0x = x0.x, y0y = x0.y, y0z = x0.z, y1x = x0.x, y1y = x0.y, y1z = x0.z;
+        R y2x = x0.x, y2y = x0.y, y2z = x0.z;
+        // y_k from the gradient of x at vertex k (interior: Langevin step)
+        auto make_y = [&](int k, V3<R> g) __attribute__((always_inline)) {
+            V3<R> y = ps.p(k);
+            if (k >= 1 && k <= n - 2) {
+                uint32_t q[4] = {sc.chain, (uint32_t)step, (uint32_t)(step >> 32), 2u + (uint32_t)k};
+                philox4x32_10(q, sc.k0, sc.k1);
+                V3<R> xi;
+                box_muller3<R>(q[0], q[1], q[2], q[3], xi);
+                half_xi2 += 0.5 * (double)dot(xi, xi);
+                y = y + hh * g + sh * xi;
+                work.glb[(size_t)k * work.C] = Vtx<R>{y.x, y.y, y.z, (R)0};
             }
-            // (vertex 0 never moves; its gradient is not needed)
-            const double lpx = wx.finish(T, g, g2);
-            if (n >= 3) feed_y(make_y(n - 2, g));
-            feed_y(make_y(n - 1, g2));
-            const double lpy = wy.finish(T, g, g2);
-            if (n >= 3) rev_term(n - 2, g, V3<R>{y1x, y1y, y1z});
-            double la = lpy - lpx - rev + half_xi2;
-            logA = isfinite(lpy) ? (R)la : Mth<R>::ninf();
-            if (logu < logA) {
-                accepted = 1;
-                for (int k = 1; k <= n - 2; ++k) ps.st(k, work.ld(k));
-                full_logp(T, ps, n, ln.L, &ln.S); // refresh the cached depths, L and S
-            }
-            return;
-        }
-        // ---------- single-vertex perturbation: the five-vertex window ----------
-        const bool hm2 = j >= 2, hp1 = !is_end, hp2 = j <= n - 3;
-        // slots j-2 .. j+2 (absent neighbours are replaced by stand-ins below;
-        // in LDS their slots are readable as they are, elsewhere the indices
-        // are clamped to stay in range)
-        Vtx<R> wm2, vm1, vo, wp1, wp2;
-        ps.ld5(LO || hm2 ? j - 2 : 0, j - 1, j, LO || hp1 ? j + 1 : 0, LO || hp2 ? j + 2 : 0, wm2, vm1, vo, wp1, wp2);
-        const V3<R> gm2 = pos(wm2), fm1 = pos(vm1), fo = pos(vo);
-        const V3<R> gp1 = pos(wp1), gp2 = pos(wp2);
-        const V3<R> fm2 = hm2 ? gm2 : fm1 - ex;
-        const V3<R> fp1 = hp1 ? gp1 : fo + ex;
-        const V3<R> fp2 = hp2 ? gp2 : fp1 + ex;
-        move = is_end ? MV_END : MV_INTERIOR;
-        // layer points of the window vertices, once each; the ones near an
-        // edge are settled together with the proposal's (one branch per
-        // step), except that the Langevin step needs the old window first
-        constexpr bool EARLY = SAMP == SAMP_LOCAL;
-        bool q1, q2, q3, q4;
-        LPt<R> pm1 = lpt_fast(T, fm1, q1), po = lpt_fast(T, fo, q2), pp1 = lpt_fast(T, fp1, q3);
-        if constexpr (EARLY) {
-            if (q1 | q2 | q3) {
-                lpt_settle(T, fm1, pm1);
-                lpt_settle(T, fo, po);
-                lpt_settle(T, fp1, pp1);
-            }
-        }
-        Seg<R> Ao, Bo;
-        LayV<R> lm1, lo, lp1;
-        auto old_window = [&]() __attribute__((always_inline)) {
-            Ao = make_seg_lp(T, fm1, fo, pm1, po);
-            Bo = make_seg_lp(T, fo, fp1, po, pp1);
-            lm1 = lay_at(T, pm1.l);
-            lo = lay_at(T, po.l);
-            lp1 = lay_at(T, pp1.l);
+            return y;
         };
-        if constexpr (EARLY) old_window();
-        const V3<R> um = unit_dir(fm2, fm1), up = unit_dir(fp1, fp2), nu1 = unit_dir_eta(T, fp1);
-        const int km1 = hm2 ? VK_TURN : VK_EMIT;
-        const int kj = is_end ? VK_END : VK_TURN;
-        const int kp1 = !hp1 ? VK_NONE : (hp2 ? VK_TURN : VK_END);
-        // one log and one sin/cos pair serve both proposals: Box-Muller on
-        // words 4..7 for the Gaussian step, and words 4, 5 for the end-point
-        // von Mises-Fisher step (inverse CDF of its cosine, uniform azimuth)
-        const R u4 = unif<R>(r[4]), u5 = unif<R>(r[5]);
-        const R lg = Mth<R>::log(is_end ? u4 + ((R)1 - u4) * (R)sc.e2k : u4);
-        const R c5 = Mth<R>::cos2pi(u5), s5 = Mth<R>::sin2pi(u5);
-        V3<R> fn, nu, nn;
-        R hx = (R)0, half_xi2 = (R)0;
-        {
-            const R rho1 = Mth<R>::sqrt((R)-2 * lg);
-            const R rho2 = Mth<R>::sqrt((R)-2 * Mth<R>::log(unif<R>(r[6])));
-            const V3<R> xi = {rho1 * c5, rho1 * s5, rho2 * Mth<R>::cos2pi(unif<R>(r[7]))};
-            V3<R> fg;
-            if constexpr (SAMP == SAMP_LOCAL) {
-                // single-vertex Langevin step with h = mala_h * (shorter adjacent segment)^2
-                const V3<R> gx = vertex_grad(T, km1, lm1, um, pm1, po, pp1, Ao, Bo, lo, kp1, up, nu1, lp1);
-                const R m = fmin(Ao.len, Bo.len);
-                hx = (R)sc.mala_h * m * m;
-                half_xi2 = (R)0.5 * dot(xi, xi);
-                fg = fo + ((R)0.5 * hx) * gx + Mth<R>::sqrt(hx) * xi;
-            } else {
-                fg = fo + (R)sc.sigma * xi;
+        // the reverse-proposal term of vertex k from the gradient of y there
+        auto rev_term = [&](int k, V3<R> g, V3<R> yk) __attribute__((always_inline)) {
+            if (k >= 1 && k <= n - 2) {
+                V3<R> d = ps.p(k) - yk - hh * g;
+                rev += (double)dot(d, d) / (2.0 * (double)h);
             }
-            V3<R> dd = from_eta(T, fo), e2, e3;
-            nu = Mth<R>::rsqrt(dot(dd, dd)) * dd; // sensor normal at the current end point
-            onb(nu, e2, e3);
-            const R omw = -lg * (R)sc.ikappa; // 1 - cos
-            const R wv = (R)1 - omw;
-            const R sw = Mth<R>::sqrt(fmax(omw * ((R)2 - omw), (R)0));
-            nn = wv * nu + sw * (c5 * e2 + s5 * e3); // sensor normal at the proposed end point
-            fn = is_end ? T.eta + (T.eta_lo + T.rad * nn) : fg;
+        };
+        auto feed_y = [&](V3<R> y) __attribute__((always_inline)) {
+            y2x = y1x;
+            y2y = y1y;
+            y2z = y1z;
+            y1x = y0x;
+            y1y = y0y;
+            y1z = y0z;
+            y0x = y.x;
+            y0y = y.y;
+            y0z = y.z;
+            const int ky = wy.k;
+            V3<R> gy;
+            if (wy.step(T, y, gy)) rev_term(ky - 2, gy, V3<R>{y2x, y2y, y2z});
+        };
+        V3<R> g, g2;
+        for (int k = 1; k < n; ++k) {
+            if (wx.step(T, ps.p(k), g) && k >= 3) feed_y(make_y(k - 2, g));
         }
-        LPt<R> pn = lpt_fast(T, fn, q4);
-        if constexpr (EARLY) {
-            if (q4) lpt_settle(T, fn, pn);
-        } else {
-            if (q1 | q2 | q3 | q4) {
-                lpt_settle(T, fm1, pm1);
-                lpt_settle(T, fo, po);
-                lpt_settle(T, fp1, pp1);
-                lpt_settle(T, fn, pn);
-            }
-            old_window();
-        }
-        const Seg<R> An = make_seg_lp(T, fm1, fn, pm1, pn), Bn = make_seg_lp(T, fn, fp1, pn, pp1);
-        const LayV<R> lnw = lay_at(T, pn.l);
-        R d = seg_term(An) - seg_term(Ao);
-        d += hp1 ? seg_term(Bn) - seg_term(Bo) : (R)0;
-        d += vtx_term<R, false, true, false>(T, km1, lm1, um, An.u, nu1) -
-             vtx_term<R, false, true, false>(T, km1, lm1, um, Ao.u, nu1);
-        d += vtx_term<R, true, false, false>(T, kj, lnw, An.u, Bn.u, nn) -
-             vtx_term<R, true, false, false>(T, kj, lo, Ao.u, Bo.u, nu);
-        d += vtx_term<R, true, false, true>(T, kp1, lp1, Bn.u, up, nu1) -
-             vtx_term<R, true, false, true>(T, kp1, lp1, Bo.u, up, nu1);
-        if constexpr (SAMP == SAMP_LOCAL) {
-            // log q(x | y) - log q(y | x) of the two Gaussian proposals, each
-            // with its own step size (so the normalisations h^{-3/2} enter)
-            const V3<R> gy = vertex_grad(T, km1, lm1, um, pm1, pn, pp1, An, Bn, lnw, kp1, up, nu1, lp1);
-            const R m = fmin(An.len, Bn.len);
-            const R hy = (R)sc.mala_h * m * m;
-            const V3<R> b = (fo - fn) - ((R)0.5 * hy) * gy;
-            const R lq = (R)1.5 * Mth<R>::log(hx * Mth<R>::rcp(hy)) - dot(b, b) * Mth<R>::rcp((R)2 * hy) + half_xi2;
-            d += is_end ? (R)0 : lq;
-            move = is_end ? MV_END : MV_LMALA;
-        }
-        // the angular response changes only when the end point itself moves
-        if (T.dk == RJPATH_DET_PAPER && is_end) d += rho_log(T, nn) - rho_log(T, nu);
-        logA = d;
+        // (vertex 0 never moves; its gradient is not needed)
+        const double lpx = wx.finish(T, g, g2);
+        if (n >= 3) feed_y(make_y(n - 2, g));
+        feed_y(make_y(n - 1, g2));
+        const double lpy = wy.finish(T, g, g2);
+        if (n >= 3) rev_term(n - 2, g, V3<R>{y1x, y1y, y1z});
+        double la = lpy - lpx - rev + half_xi2;
+        logA = isfinite(lpy) ? (R)la : Mth<R>::ninf();
         if (logu < logA) {
             accepted = 1;
-            ps.st(j, Vtx<R>{fn.x, fn.y, fn.z, hp1 ? Bn.tb : (R)0});
-            ps.stw(j - 1, An.tb);
-            ln.L += (double)An.len - (double)Ao.len + (hp1 ? (double)Bn.len - (double)Bo.len : 0.0);
-            ln.S += ((double)An.tb - (double)vm1.w) + (hp1 ? (double)Bn.tb - (double)vo.w : 0.0);
+            for (int k = 1; k <= n - 2; ++k) ps.st(k, work.ld(k));
+            full_logp(T, ps, n, ln.L, &ln.S); // refresh the cached depths, L and S
         }
         return;
     }
-    // ---------- birth / death through the bi-spherical map ----------
+    // ---------- single-vertex perturbation: the five-vertex window ----------
+    const bool hm2 = j >= 2, hp1 = !is_end, hp2 = j <= n - 3;
+    // slots j-2 .. j+2 (absent neighbours are replaced by stand-ins below;
+    // in LDS their slots are readable as they are, elsewhere the indices
+    // are clamped to stay in range)
+    Vtx<R> wm2, vm1, vo, wp1, wp2;
+    ps.ld5(LO || hm2 ? j - 2 : 0, j - 1, j, LO || hp1 ? j + 1 : 0, LO || hp2 ? j + 2 : 0, wm2, vm1, vo, wp1, wp2);
+    const V3<R> gm2 = pos(wm2), fm1 = pos(vm1), fo = pos(vo);
+    const V3<R> gp1 = pos(wp1), gp2 = pos(wp2);
+    const V3<R> fm2 = hm2 ? gm2 : fm1 - ex;
+    const V3<R> fp1 = hp1 ? gp1 : fo + ex;
+    const V3<R> fp2 = hp2 ? gp2 : fp1 + ex;
+    move = is_end ? MV_END : MV_INTERIOR;
+    // layer points of the window vertices, once each; the ones near an
+    // edge are settled together with the proposal's (one branch per
+    // step), except that the Langevin step needs the old window first
+    constexpr bool EARLY = SAMP == SAMP_LOCAL;
+    bool q1, q2, q3, q4;
+    LPt<R> pm1 = lpt_fast(T, fm1, q1), po = lpt_fast(T, fo, q2), pp1 = lpt_fast(T, fp1, q3);
+    if constexpr (EARLY) {
+        if (q1 | q2 | q3) {
+            lpt_settle(T, fm1, pm1);
+            lpt_settle(T, fo, po);
+            lpt_settle(T, fp1, pp1);
+        }
+    }
+    Seg<R> Ao, Bo;
+    LayV<R> lm1, lo, lp1;
+    auto old_window = [&]() __attribute__((always_inline)) {
+        Ao = make_seg_lp(T, fm1, fo, pm1, po);
+        Bo = make_seg_lp(T, fo, fp1, po, pp1);
+        lm1 = lay_at(T, pm1.l);
+        lo = lay_at(T, po.l);
+        lp1 = lay_at(T, pp1.l);
+    };
+    if constexpr (EARLY) old_window();
+    // the direction past f_{j+1}: of the next segment or, where f_{j+1} is the
+    // end point, of the sensor normal there (a turn reads the one, an end
+    // factor the other: one normalisation serves both)
+    const bool fin = hp1 && !hp2;
+    const V3<R> um = unit_dir(fm2, fm1);
+    V3<R> up;
+    {
+        const V3<R> rt = fp2 - fp1, re = from_eta(T, fp1);
+        const V3<R> rr = {fin ? re.x : rt.x, fin ? re.y : rt.y, fin ? re.z : rt.z};
+        up = Mth<R>::rsqrt(dot(rr, rr)) * rr;
+    }
+    const int km1 = hm2 ? VK_TURN : VK_EMIT;
+    const int kj = is_end ? VK_END : VK_TURN;
+    const int kp1 = !hp1 ? VK_NONE : (hp2 ? VK_TURN : VK_END);
+    // one log and one sin/cos pair serve both proposals: Box-Muller on
+    // words 4..7 for the Gaussian step, and words 4, 5 for the end-point
+    // von Mises-Fisher step (inverse CDF of its cosine, uniform azimuth)
+    const R u4 = unif<R>(r[4]), u5 = unif<R>(r[5]);
+    const R lg = Mth<R>::log(is_end ? u4 + ((R)1 - u4) * (R)sc.e2k : u4);
+    const R c5 = Mth<R>::cos2pi(u5), s5 = Mth<R>::sin2pi(u5);
+    V3<R> fn, nu, nn;
+    R hx = (R)0, half_xi2 = (R)0;
+    {
+        const R rho1 = Mth<R>::sqrt((R)-2 * lg);
+        const R rho2 = Mth<R>::sqrt((R)-2 * Mth<R>::log(unif<R>(r[6])));
+        const V3<R> xi = {rho1 * c5, rho1 * s5, rho2 * Mth<R>::cos2pi(unif<R>(r[7]))};
+        V3<R> fg;
+        if constexpr (SAMP == SAMP_LOCAL) {
+            // single-vertex Langevin step with h = mala_h * (shorter adjacent segment)^2
+            const V3<R> gx = vertex_grad(T, km1, lm1, um, pm1, po, pp1, Ao, Bo, lo, kp1, up, up, lp1);
+            const R m = fmin(Ao.len, Bo.len);
+            hx = (R)sc.mala_h * m * m;
+            half_xi2 = (R)0.5 * dot(xi, xi);
+            fg = fo + ((R)0.5 * hx) * gx + Mth<R>::sqrt(hx) * xi;
+        } else {
+            fg = fo + (R)sc.sigma * xi;
+        }
+        V3<R> dd = from_eta(T, fo), e2, e3;
+        nu = Mth<R>::rsqrt(dot(dd, dd)) * dd; // sensor normal at the current end point
+        onb(nu, e2, e3);
+        const R omw = -lg * (R)sc.ikappa; // 1 - cos
+        const R wv = (R)1 - omw;
+        const R sw = Mth<R>::sqrt(fmax(omw * ((R)2 - omw), (R)0));
+        nn = wv * nu + sw * (c5 * e2 + s5 * e3); // sensor normal at the proposed end point
+        fn = is_end ? T.eta + (T.eta_lo + T.rad * nn) : fg;
+    }
+    LPt<R> pn = lpt_fast(T, fn, q4);
+    if constexpr (EARLY) {
+        if (q4) lpt_settle(T, fn, pn);
+    } else {
+        if (q1 | q2 | q3 | q4) {
+            lpt_settle(T, fm1, pm1);
+            lpt_settle(T, fo, po);
+            lpt_settle(T, fp1, pp1);
+            lpt_settle(T, fn, pn);
+        }
+        old_window();
+    }
+    const Seg<R> An = make_seg_lp(T, fm1, fn, pm1, pn), Bn = make_seg_lp(T, fn, fp1, pn, pp1);
+    const LayV<R> lnw = lay_at(T, pn.l);
+    R d = seg_term(An) - seg_term(Ao);
+    d += hp1 ? seg_term(Bn) - seg_term(Bo) : (R)0;
+    d += vtx_term<R, false, true, false>(T, km1, lm1, um, An.u, up) -
+         vtx_term<R, false, true, false>(T, km1, lm1, um, Ao.u, up);
+    d += vtx_term<R, true, false, false>(T, kj, lnw, An.u, Bn.u, nn) -
+         vtx_term<R, true, false, false>(T, kj, lo, Ao.u, Bo.u, nu);
+    d += vtx_term<R, true, false, true>(T, kp1, lp1, Bn.u, up, up) -
+         vtx_term<R, true, false, true>(T, kp1, lp1, Bo.u, up, up);
+    if constexpr (SAMP == SAMP_LOCAL) {
+        // log q(x | y) - log q(y | x) of the two Gaussian proposals, each
+        // with its own step size (so the normalisations h^{-3/2} enter)
+        const V3<R> gy = vertex_grad(T, km1, lm1, um, pm1, pn, pp1, An, Bn, lnw, kp1, up, up, lp1);
+        const R m = fmin(An.len, Bn.len);
+        const R hy = (R)sc.mala_h * m * m;
+        const V3<R> b = (fo - fn) - ((R)0.5 * hy) * gy;
+        const R lq = (R)1.5 * Mth<R>::log(hx * Mth<R>::rcp(hy)) - dot(b, b) * Mth<R>::rcp((R)2 * hy) + half_xi2;
+        d += is_end ? (R)0 : lq;
+        move = is_end ? MV_END : MV_LMALA;
+    }
+    // the angular response changes only when the end point itself moves
+    if (T.dk == RJPATH_DET_PAPER && is_end) d += rho_log(T, nn) - rho_log(T, nu);
+    logA = d;
+    if (logu < logA) {
+        accepted = 1;
+        ps.st(j, Vtx<R>{fn.x, fn.y, fn.z, hp1 ? Bn.tb : (R)0});
+        ps.stw(j - 1, An.tb);
+        ln.L += (double)An.len - (double)Ao.len + (hp1 ? (double)Bn.len - (double)Bo.len : 0.0);
+        ln.S += ((double)An.tb - (double)vm1.w) + (hp1 ? (double)Bn.tb - (double)vo.w : 0.0);
+    }
+}
+
+// A jump step: birth or death of an interior vertex through the bi-spherical
+// map.  Returns the move kind, log A, the segment or vertex (-1: the proposal
+// is invalid) and whether it was accepted.
+template <class R, bool LO, int SAMP>
+__device__ __forceinline__ void jump_move(const Tgt<R>& T, const PathRef<R, LO>& ps, Lane<R>& ln, const StepCtx& sc,
+                                          const StepLoop& lp, const uint32_t r[8], R logu, int& move, int& idx,
+                                          int& accepted, R& logA) {
+    const int n = ln.n;
+    idx = -1;
+    accepted = 0;
+    const V3<R> ex = {(R)1, (R)0, (R)0};
     const bool birth = r[2] < sc.bthresh;
     move = birth ? MV_BIRTH : MV_DEATH;
     // S = sum of the cached segment depths, kept by the lane as a running sum
     // (summed afresh in path order at every launch start and after whole-path
-    // moves).  The segment scan of a birth reads the first WB depths once into
-    // registers (loads issued together) and the rest four at a time.
-    // (16 cover all but rare long paths of the batched workloads; the FP64
-    // and Langevin variants keep 8 so that their registers still allow two
-    // resident waves per SIMD where they did)
-    constexpr int WB = (sizeof(R) == 4 && SAMP == SAMP_PLAIN) ? 16 : 8;
+    // moves).  The segment scan of a birth reads the first depths from their
+    // LDS slots at once (scan_slots: depths past the path's end are stale or
+    // zero, never negative) and the rest four at a time.
+    constexpr int WB = scan_slots<R, SAMP>();
     const double S = ln.S;
     const bool valid = birth ? (n < sc.cap && S > 0.0) : (n > 2);
     int iA = 0, jv = 1;
@@ -992,17 +1054,18 @@ __device__ __forceinline__ void step_body(const Tgt<R>& T, const PathRef<R, LO>&
             const double tgt = (double)unif<double>(r[0]) * S;
             R wv[WB];
 #pragma unroll
-            for (int v = 0; v < WB; ++v) wv[v] = ps.w(v < n - 1 ? v : 0);
+            for (int v = 0; v < WB; ++v) wv[v] = ps.lds_w(v < ps.V ? v : ps.V);
             double cum = 0.0;
             int k = 0;
-            // (past the path the cumulative sum stays at S > U S: no count;
-            // once it exceeds U S no later prefix counts either)
+            // (slots past the path only count once its whole sum does not
+            // exceed U S, by rounding; k is then cut to the last segment)
 #pragma unroll
             for (int v = 0; v < WB; ++v) {
-                cum += v < n - 1 ? (double)wv[v] : 0.0;
+                cum += (double)wv[v];
                 k += cum <= tgt ? 1 : 0;
             }
-            for (int v = WB; v < n - 1 && cum <= tgt; v += 4) {
+            k = k < ps.V ? k : ps.V; // (the padding slot read past V holds no depth)
+            for (int v = WB < ps.V ? WB : ps.V; v < n - 1 && cum <= tgt; v += 4) {
                 R w4[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) w4[i] = ps.w(v + i < n - 1 ? v + i : v);
@@ -1078,15 +1141,22 @@ __device__ __forceinline__ void step_body(const Tgt<R>& T, const PathRef<R, LO>&
     }
     const LPt<R> pv = lpt(T, fv);
     const Seg<R> sA = make_seg_lp(T, A, fv, pA, pv), sB = make_seg_lp(T, fv, B, pv, pB);
-    const V3<R> up = unit_dir(fprev, A), un = unit_dir(B, fnext), nuB = unit_dir_eta(T, B);
+    // the direction past B: of the next segment, or the sensor normal where B is the end point
+    const V3<R> up = unit_dir(fprev, A);
+    V3<R> un;
+    {
+        const V3<R> rt = fnext - B, re = from_eta(T, B);
+        const V3<R> rr = {hnext ? rt.x : re.x, hnext ? rt.y : re.y, hnext ? rt.z : re.z};
+        un = Mth<R>::rsqrt(dot(rr, rr)) * rr;
+    }
     const LayV<R> la = lay_at(T, pA.l), lb = lay_at(T, pB.l), lv = lay_at(T, pv.l);
     const int kA = hprev ? VK_TURN : VK_EMIT, kB = hnext ? VK_TURN : VK_END;
     // (an end point B is the same in x and y: its angular response cancels)
-    const R tx = vtx_term<R, false, true, false>(T, kA, la, up, AB.u, nuB) +
-                 vtx_term<R, true, false, false>(T, kB, lb, AB.u, un, nuB);
-    const R ty = vtx_term<R, false, true, false>(T, kA, la, up, sA.u, nuB) +
-                 vtx_term<R, true, false, false>(T, kB, lb, sB.u, un, nuB) +
-                 vtx_term<R, false, false, false>(T, VK_TURN, lv, sA.u, sB.u, nuB);
+    const R tx = vtx_term<R, false, true, false>(T, kA, la, up, AB.u, un) +
+                 vtx_term<R, true, false, false>(T, kB, lb, AB.u, un, un);
+    const R ty = vtx_term<R, false, true, false>(T, kA, la, up, sA.u, un) +
+                 vtx_term<R, true, false, false>(T, kB, lb, sB.u, un, un) +
+                 vtx_term<R, false, false, false>(T, VK_TURN, lv, sA.u, sB.u, un);
     V3<R> dq = sA.u - sB.u;
     R q = dot(dq, dq);
     // segment factors of y over x times |J| / q(s) q(t) q(phi): the inverse-square
@@ -1106,8 +1176,7 @@ __device__ __forceinline__ void step_body(const Tgt<R>& T, const PathRef<R, LO>&
     logA = valid ? (birth ? logAb : -logAb) : Mth<R>::ninf();
     if (logu < logA) {
         accepted = 1;
-        fold_run(ln, T.n0, sc.cap, sc.logw != nullptr); // the steps spent at the old n
-        fold_hist(ln, sc);
+        fold_run(ln, T.n0, sc, lp); // the steps spent at the old n
         const double dL = (double)sA.len + (double)sB.len - (double)AB.len;
         if (birth) {
             ps.shift_up(iB, n - 1);
@@ -1137,52 +1206,54 @@ __device__ __forceinline__ void step_body(const Tgt<R>& T, const PathRef<R, LO>&
     }
 }
 
-// One sampler step of a lane inside the step loop: the move, then the move
-// counts, the per-step sums, the optional histogram and trace.
+// One perturbation step of a lane inside the step loop (the tree sampler's
+// first step of a cycle is a tree-coordinate move), then the counts.  The
+// class of a step is the wave's, so each class has its own loop below and its
+// counts are touched only there.
 template <class R, bool LO, int SAMP>
-__device__ __forceinline__ void one_step(const KArgs& a, const Tgt<R>& T, const PathRef<R, LO>& ps,
-                                         const GlobalPath<R>& work, Lane<R>& ln, const StepCtx& sc, uint64_t step0,
-                                         int s, int& phase, int c, int t) {
-    const uint64_t step = step0 + (uint64_t)s;
-    const bool perturb = phase < a.n_perturb;
+__device__ __forceinline__ void perturb_step(const KArgs& a, const Tgt<R>& T, const PathRef<R, LO>& ps,
+                                             const GlobalPath<R>& work, Lane<R>& ln, const StepCtx& sc,
+                                             const StepLoop& lp, bool first, int c) {
+    const uint64_t step = lp.step0 + (uint64_t)lp.s;
+    uint32_t r[8];
+    draw8<SAMP>(sc, step, r);
+    // (a chain that is not live rejects every proposal)
+    const R logu = ln.live ? Mth<R>::log(unif<R>(r[1])) : -Mth<R>::ninf();
     int move, idx, accepted;
-    R logA, logu;
-    const bool counted = (int64_t)step >= a.burn_in;
-    // the tree sampler makes the first step of every cycle a tree-coordinate move
-    const bool tree = SAMP == SAMP_TREE && phase == 0 && perturb;
-    step_body<R, LO, SAMP>(T, ps, work, ln, sc, step, perturb, tree, move, idx, accepted, logA, logu);
-    {
-        // move counts, branch-free (per-branch updates get merged by the
-        // compiler into a dynamically indexed stack slot)
-        const uint32_t cu = counted ? 1u : 0u, ca = (uint32_t)accepted;
-        const uint32_t ib = cu & (move == MV_BIRTH ? 1u : 0u), id = cu & (move == MV_DEATH ? 1u : 0u);
-        const uint32_t ip = cu - ib - id, im = cu & ((move == MV_MALA || move == MV_LMALA || move == MV_TREE) ? 1u : 0u);
-        ln.ne += cu & (((move == MV_BIRTH || move == MV_DEATH) && idx < 0) ? 1u : 0u);
-        ln.pb += ib;
-        ln.pd += id;
-        ln.pp += ip;
-        ln.mp += im;
-        ln.ab += ib & ca;
-        ln.ad += id & ca;
-        ln.ap += ip & ca;
-        ln.ma += im & ca;
+    R logA;
+    perturb_move<R, LO, SAMP>(T, ps, work, ln, sc, step, r, logu, SAMP == SAMP_TREE && first, move, idx, accepted, logA);
+    if (lp.counted()) {
+        ln.ap += (uint32_t)accepted;
+        if constexpr (SAMP != SAMP_PLAIN) {
+            const uint32_t im = (move == MV_MALA || move == MV_LMALA || move == MV_TREE) ? 1u : 0u;
+            ln.mp += im;
+            ln.ma += im & (uint32_t)accepted;
+        }
+        count_step(ln);
     }
-    if (counted) {
-        ln.run += 1;
-        ln.sl += ln.L;
-        ln.sl2 += ln.L * ln.L;
-    }
-    ln.hrun += 1;
-    if (a.trace && ln.live) {
-        double* tr = a.trace + ((size_t)c * a.trace_steps + a.trace_off + s) * RJPATH_TRACE_WORDS;
-        tr[0] = move;
-        tr[1] = accepted;
-        tr[2] = idx;
-        tr[3] = (double)logA;
-        tr[4] = (double)logu;
-    }
-    phase = (phase + 1 == a.cycle_len) ? 0 : phase + 1;
+    put_trace(a, ln, c, lp.s, move, idx, accepted, logA, logu);
 }
+
+template <class R, bool LO, int SAMP>
+__device__ __forceinline__ void jump_step(const KArgs& a, const Tgt<R>& T, const PathRef<R, LO>& ps, Lane<R>& ln,
+                                          const StepCtx& sc, const StepLoop& lp, int c) {
+    uint32_t r[8];
+    draw8<SAMP>(sc, lp.step0 + (uint64_t)lp.s, r);
+    const R logu = ln.live ? Mth<R>::log(unif<R>(r[1])) : -Mth<R>::ninf();
+    int move, idx, accepted;
+    R logA;
+    jump_move<R, LO, SAMP>(T, ps, ln, sc, lp, r, logu, move, idx, accepted, logA);
+    if (lp.counted()) {
+        const uint32_t ib = move == MV_BIRTH ? 1u : 0u, ac = (uint32_t)accepted;
+        ln.ne += idx < 0 ? 1u : 0u;
+        ln.pb += ib;
+        ln.ab += ib & ac;
+        ln.ad += ac & ~ib;
+        count_step(ln);
+    }
+    put_trace(a, ln, c, lp.s, move, idx, accepted, logA, logu);
+}
+
 
 // ---------------------------------------------------------------------------
 // The step kernel.  MK: MK_HOM (every medium of the launch is homogeneous: the
@@ -1249,6 +1320,9 @@ template <class R, int MK, int SAMP, bool SL, bool EVEN> __device__ __forceinlin
     // stage the LDS part of the path
     const int nl0 = ln.n < a.V ? ln.n : a.V;
     for (int v = 0; v < nl0; ++v) lds_st<R>(ps.lds + v * WAVE, ps.glb[(size_t)v * C]);
+    // the depths a birth's scan reads past the path (slot V is padding): none
+    for (int v = nl0; v <= a.V && v < scan_slots<R, SAMP>(); ++v) pl.stw(v, (R)0);
+    if (a.V < scan_slots<R, SAMP>()) pl.stw(a.V, (R)0);
 
     ln.lp = full_logp(T, ps, ln.n, ln.L, &ln.S);
     const bool healthy = isfinite(ln.lp);
@@ -1277,24 +1351,54 @@ template <class R, int MK, int SAMP, bool SL, bool EVEN> __device__ __forceinlin
         ln.lwp = sc.logw[ln.n < cap ? ln.n + 1 : cap];
         ln.invw = inv_tilt<R>(ln.lw0);
     }
-    const uint64_t step0 = a.step_dev ? *a.step_dev + a.step0 : a.step0; // step0 is the offset then
-    int phase = (int)(step0 % (uint64_t)a.cycle_len);
+    StepLoop lp{};
+    lp.step0 = a.step_dev ? *a.step_dev + a.step0 : a.step0; // step0 is the offset then
+    lp.tilt = sc.logw != nullptr;
+    {
+        const int64_t d = a.burn_in - (int64_t)lp.step0;
+        lp.first = d < 0 ? 0 : (d < (int64_t)a.steps ? (int)d : a.steps);
+    }
+    int phase = (int)(lp.step0 % (uint64_t)a.cycle_len);
 
     ln.live = healthy;
     // Every lane runs every step (a lane that is not live only rejects), so
-    // that the step loop is uniform across the wave.  The wave stays in the
-    // LDS-only loop while all its paths fit their slots and falls to the
-    // general loop (slots beyond V in HBM) while some do not.
-    int s = 0;
-    while (s < a.steps) {
-        for (; s < a.steps && __all(ln.n < a.V); ++s)
-            one_step<R, true, SAMP>(a, T, pl, work, ln, sc, step0, s, phase, c, t);
-        for (; s < a.steps && !__all(ln.n < a.V); ++s)
-            one_step<R, false, SAMP>(a, T, ps, work, ln, sc, step0, s, phase, c, t);
+    // that the step loop is uniform across the wave.  The steps of one class
+    // follow each other in a loop of their own.  A wave takes the LDS-only
+    // form of a step while all its paths fit their slots (n changes in jump
+    // steps alone: one vote per run of perturbation steps) and the general
+    // form (slots beyond V in HBM) while some do not.
+    while (lp.s < a.steps) {
+        const int left = a.steps - lp.s;
+        if (phase < a.n_perturb) {
+            const int m = a.n_perturb - phase < left ? a.n_perturb - phase : left, end = lp.s + m;
+            bool first = phase == 0;
+            if (__all(ln.n < a.V)) {
+                for (; lp.s < end; ++lp.s, first = false)
+                    perturb_step<R, true, SAMP>(a, T, pl, work, ln, sc, lp, first, c);
+            } else {
+                for (; lp.s < end; ++lp.s, first = false)
+                    perturb_step<R, false, SAMP>(a, T, ps, work, ln, sc, lp, first, c);
+            }
+            phase += m;
+        } else {
+            const int m = a.cycle_len - phase < left ? a.cycle_len - phase : left, end = lp.s + m;
+            for (; lp.s < end; ++lp.s) {
+                if (__all(ln.n < a.V))
+                    jump_step<R, true, SAMP>(a, T, pl, ln, sc, lp, c);
+                else
+                    jump_step<R, false, SAMP>(a, T, ps, ln, sc, lp, c);
+            }
+            phase += m;
+        }
+        if (phase == a.cycle_len) phase = 0;
     }
+    // counted steps of each class (the same for every lane)
+    const uint32_t counted = (uint32_t)(a.steps - lp.first);
+    const uint32_t perturbs = count_perturbs(lp.step0 + (uint64_t)lp.first, counted, a.cycle_len, a.n_perturb);
+    const uint32_t jumps = counted - perturbs;
 
-    fold_run(ln, T.n0, cap, sc.logw != nullptr);
-    if (healthy) fold_hist(ln, sc);
+    if (!healthy) ln.mark = lp.s; // (nothing of it enters the histogram)
+    fold_run(ln, T.n0, sc, lp);
     // log p of the final path (refreshed once rather than tracked per step)
     if (healthy) ln.lp = full_logp(T, ps, ln.n, ln.L);
     // write back the LDS part, the vertex count, log p and the statistics
@@ -1311,9 +1415,9 @@ template <class R, int MK, int SAMP, bool SL, bool EVEN> __device__ __forceinlin
         sp[3] += ln.sl;
         sp[4] += ln.sl2;
         sp[5] += (double)ln.sn;
-        sp[6] += ln.pp;
+        sp[6] += perturbs;
         sp[7] += ln.pb;
-        sp[8] += ln.pd;
+        sp[8] += jumps - ln.pb;
         sp[9] += ln.ap;
         sp[10] += ln.ab;
         sp[11] += ln.ad;
@@ -1324,7 +1428,11 @@ template <class R, int MK, int SAMP, bool SL, bool EVEN> __device__ __forceinlin
     }
 }
 
-template <class R, int MK, int SAMP, bool SL> __global__ void __launch_bounds__(256) run_kernel(KArgs a) {
+// (FP32: two waves per SIMD, which the joint Langevin variant with the mixture
+// and tables in HBM would miss by three registers, and the leaner ones reach
+// by themselves; below, some even-layer variants spill a few values for it)
+template <class R, int MK, int SAMP, bool SL>
+__global__ void __launch_bounds__(256, sizeof(R) == 4 && SAMP == SAMP_JOINT ? 2 : 1) run_kernel(KArgs a) {
     run_body<R, MK, SAMP, SL, false>(a);
 }
 

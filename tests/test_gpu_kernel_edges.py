@@ -95,3 +95,25 @@ def test_even_layer_kernels_take_the_general_kernels_steps(rj, prec, sampler, f_
     for x, y in zip(*out):
         assert np.array_equal(x, y)
     assert out[0][0].max() > 6
+
+
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+@pytest.mark.parametrize("slots", [1, 7, 8, 9, 15, 16, 17])
+def test_slot_count_around_the_scan_leaves_the_paths_alone(rj, prec, slots):
+    """A birth's segment scan reads a fixed number of LDS slots and continues
+    in HBM; path lengths on both sides of the slot count and of the scan give
+    the same paths bit for bit, whatever the slots (sampling also starts in
+    the middle of the launch, so that the statistics fold a partial run)."""
+    w = W.single_target(1.5, 0.165, 0.3, 50.0, 0.9, chains=130, cap=64, burn_in=150, seed=53)
+    out = []
+    for v in (40, slots):
+        s = rj.Sampler(w, precision=prec)
+        for k in range(3):
+            s.run(200, block=64, v_lds=v)
+        torch.cuda.synchronize()
+        n, x = s.get_state()
+        used = np.arange(s.cap)[None, :] < n[:, None]
+        out.append((n, np.where(used[..., None], x, 0.0), s.logp.cpu().numpy(), s.stats.cpu().numpy()))
+    for x, y in zip(*out):
+        assert np.array_equal(x, y)
+    assert out[0][0].max() > 17 and out[0][3][:, 0].min() == 450
