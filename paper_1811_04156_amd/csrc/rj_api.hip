@@ -322,16 +322,29 @@ int device_cus() {
 // instruction per two issue slots of its SIMD, and a second resident wave
 // nearly doubles the SIMD's throughput (measured on gfx950).  So:
 //  - fewer chains than two waves per SIMD: one 64-chain wave per block with
-//    32 slots per lane (16 in FP64), the fastest configuration measured for
-//    one wave per SIMD;
+//    up to 32 slots per lane (16 in FP64), the fastest configuration measured
+//    for one wave per SIMD; fewer where the blocks (up to four per CU, one wave
+//    per SIMD) would otherwise not all be resident: every block stages the
+//    media tables, and with those of 100 layers beside 32 slots only three fit,
+//    so that 49,153 to 65,536 chains ran in two rounds (60,000 chains of the
+//    single-vertex Langevin sampler, 500 steps: 3.23 ms with 32 slots, 1.82 ms
+//    with the 30 that let the fourth in);
 //  - otherwise (FP32): 256-chain blocks with as many slots as let two blocks
 //    (eight waves) share a CU's LDS, so that two waves are resident per SIMD
 //    (the step kernel's register use allows two).
 void default_launch(const rjpath_chains* c, size_t tab_bytes, int& block, int& V) {
     const int cap = c->cap;
+    const int cus = device_cus();
     block = 64;
     V = std::min(cap, c->precision == RJPATH_F64 ? 16 : 32);
-    const long long two_waves = 2LL * 4 * device_cus() * 64;
+    const long long blocks = ((long long)c->n_chains + 63) / 64;
+    const size_t per_cu = (size_t)std::min<long long>(4, (blocks + cus - 1) / cus);
+    const size_t share = LDS_MAX / per_cu;
+    if (share > tab_bytes) {
+        const long long fit = (long long)((share - tab_bytes) / (64 * vtx_bytes(c->precision))) - 2;
+        if (fit >= 8) V = (int)std::min<long long>(V, fit);
+    }
+    const long long two_waves = 2LL * 4 * cus * 64;
     if (c->precision == RJPATH_F32 && (long long)c->n_chains >= two_waves) {
         const size_t per_block = LDS_MAX / 2;
         if (per_block > tab_bytes) {

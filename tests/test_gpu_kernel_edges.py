@@ -117,3 +117,20 @@ def test_slot_count_around_the_scan_leaves_the_paths_alone(rj, prec, slots):
     for x, y in zip(*out):
         assert np.array_equal(x, y)
     assert out[0][0].max() > 17 and out[0][3][:, 0].min() == 450
+
+
+@pytest.mark.parametrize("chains", [49_152, 51_201])
+def test_default_launch_with_staged_tables(rj, chains):
+    """The default launch gives up slots so that four blocks with 100-layer
+    tables share a CU (from 49,153 chains on 256 CUs): the same paths as with
+    an explicit launch."""
+    w = W.layered_pairs(seed=6, pairs=50, chains=chains, cap=48)
+    w["burn_in"] = 0
+    out = []
+    for kw in (dict(), dict(block=128, v_lds=11)):
+        s = rj.Sampler(w, precision="f32")
+        s.run(60, **kw)
+        torch.cuda.synchronize()
+        out.append((s.n.clone(), s.logp.clone(), s.stats.clone()))
+    for x, y in zip(*out):
+        assert torch.equal(x, y)
