@@ -318,6 +318,16 @@ int device_cus() {
     return cus;
 }
 
+// Chains per wave of the tree sampler: 64 from two waves per SIMD on; below
+// that fewer, down to 8, so that the shared whole-path moves of the same chains
+// use more of the chip.
+int tree_cpw(int n_chains) {
+    const long long two_waves = 2LL * 4 * device_cus();
+    int cpw = 64;
+    while (cpw > 8 && (long long)n_chains < two_waves * cpw) cpw /= 2;
+    return cpw;
+}
+
 // Default launch configuration.  One wave per SIMD issues at most about one
 // instruction per two issue slots of its SIMD, and a second resident wave
 // nearly doubles the SIMD's throughput (measured on gfx950).  So:
@@ -332,23 +342,27 @@ int device_cus() {
 //  - otherwise (FP32): 256-chain blocks with as many slots as let two blocks
 //    (eight waves) share a CU's LDS, so that two waves are resident per SIMD
 //    (the step kernel's register use allows two).
-void default_launch(const rjpath_chains* c, size_t tab_bytes, int& block, int& V) {
+//  - the tree sampler: the same with its waves counted (tree_cpw chains each);
+//    in 256-thread blocks of 64-chain waves half of the slots hold proposals.
+void default_launch(const rjpath_chains* c, size_t tab_bytes, int sampler, int& block, int& V) {
     const int cap = c->cap;
     const int cus = device_cus();
+    const bool tree = sampler == RJPATH_TREE;
+    const int cpw = tree ? tree_cpw(c->n_chains) : 64;
     block = 64;
     V = std::min(cap, c->precision == RJPATH_F64 ? 16 : 32);
-    const long long blocks = ((long long)c->n_chains + 63) / 64;
+    const long long blocks = ((long long)c->n_chains + cpw - 1) / cpw;
     const size_t per_cu = (size_t)std::min<long long>(4, (blocks + cus - 1) / cus);
     const size_t share = LDS_MAX / per_cu;
     if (share > tab_bytes) {
         const long long fit = (long long)((share - tab_bytes) / (64 * vtx_bytes(c->precision))) - 2;
         if (fit >= 8) V = (int)std::min<long long>(V, fit);
     }
-    const long long two_waves = 2LL * 4 * cus * 64;
-    if (c->precision == RJPATH_F32 && (long long)c->n_chains >= two_waves) {
+    if (c->precision == RJPATH_F32 && (tree ? blocks > 4LL * cus : (long long)c->n_chains >= 2LL * 4 * cus * 64)) {
         const size_t per_block = LDS_MAX / 2;
         if (per_block > tab_bytes) {
-            const long long slots = (long long)((per_block - tab_bytes) / (256 * vtx_bytes(RJPATH_F32))) - 2;
+            long long slots = (long long)((per_block - tab_bytes) / (256 * vtx_bytes(RJPATH_F32))) - 2;
+            if (tree && cpw == 64) slots /= 2;
             if (slots >= 8) {
                 block = 256;
                 V = (int)std::min<long long>(std::min(cap, 32), slots);
@@ -374,6 +388,15 @@ int run_impl(rjpath_medium* m, const rjpath_targets* t, const rjpath_chains* c, 
     a.trace_steps = p->steps;
     a.hist = p->hist;
     a.step_dev = p->step_counter;
+    if (p->sampler == RJPATH_TREE) {
+        a.cpw = tree_cpw(c->n_chains);
+        if (a.cpw == 64) {
+            // LDS slots for the proposals: what the blocks that fit a CU leave
+            const size_t per = (size_t)block * vtx_bytes(c->precision), x = a.tab_bytes + (size_t)(V + 2) * per;
+            const size_t share = LDS_MAX / std::max<size_t>(1, std::min<size_t>(LDS_MAX / x, 512 / (size_t)block));
+            a.Vy = (int)std::min<size_t>(V, (share - x) / per);
+        }
+    }
     int chunk = p->chunk > 0 ? p->chunk : p->steps;
     for (int done = 0; done < p->steps; done += chunk) {
         // with a device counter, step0 carries the offset inside this call
@@ -424,7 +447,7 @@ int rjpath_run_chains(rjpath_medium* m, const rjpath_targets* t, const rjpath_ch
     if (r) return r;
     if (p->steps == 0) return RJPATH_OK;
     int block, V;
-    default_launch(c, make_args(m, t, c).tab_bytes, block, V);
+    default_launch(c, make_args(m, t, c).tab_bytes, p->sampler, block, V);
     auto it = m->tuned.find(TuneKey{c->cap, c->precision, p->sampler});
     if (it != m->tuned.end()) {
         block = it->second.first;
@@ -453,7 +476,7 @@ int rjpath_autotune(rjpath_medium* m, const rjpath_targets* t, const rjpath_chai
     {
         // the default launch is always a candidate
         int db, dv;
-        default_launch(c, make_args(m, t, c).tab_bytes, db, dv);
+        default_launch(c, make_args(m, t, c).tab_bytes, p->sampler, db, dv);
         if ((size_t)(dv + 2) * db * vtx_bytes(c->precision) <= budget) cand.push_back({db, dv});
     }
     for (int b : {64, 256})

@@ -622,206 +622,25 @@ __device__ __forceinline__ void put_trace(const KArgs& a, const Lane<R>& ln, int
     }
 }
 
-// ---------------------------------------------------------------------------
-// Tree-coordinate move of the whole path (App. "Path space coordinate
-// system"; Sec. "Path proposal distribution").  Interval (k, l), l - k >= 2,
-// places vertex m = (k + l) / 2 by bi-spherical coordinates (zeta, t, phi)
-// about the foci f_k, f_l (cos s = tanh zeta), then splits into (k, m) and
-// (m, l); the root is (0, n - 1).  The azimuth is measured in a frame handed
-// down the tree: the root's is the orthonormal completion of its axis, a
-// child's has e3 = the unit normal of the plane of its parent's foci and
-// vertex (the parent's frame turned about the parent's axis to the parent
-// vertex's azimuth, then rotated onto the child's axis) and e2 = e3 x e1.
-// The move draws a von Mises-Fisher step of the end point on the sensor
-// (words 4, 5, as the end-point perturbation) and Gaussian steps of variance
-// mala_h / n for every (zeta, t, phi) (vertex m: one Philox block with
-// counter word 3 = 2 + m), builds the proposal node by node in pre-order (each
-// vertex's foci and frame come from vertices placed before it) into the work
-// buffer, and accepts with
-//   log A = log p(y) - log p(x) + sum_m [log J_m(y) - log J_m(x)],
-//   J_m = gamma^3 sech^2(zeta) / (cosh t - tanh zeta)^3.
-// The coordinates are formed from unit vectors: with uA, uB the unit vectors
-// from f_m to its foci, 1 + cos s = |uA + uB|^2 / 2, 1 - cos s = |uA - uB|^2 / 2
-// and sin s = |uA + uB| |uA - uB| / 2, which keep their precision for nearly
-// straight (s ~ pi) and nearly folded paths.
-// ---------------------------------------------------------------------------
-template <class R> struct TreePath {
-    // the proposal: vertex 0 from the path, interior vertices from the work
-    // buffer, the end point held apart
-    GlobalPath<R> work;
-    V3<R> y0, yend;
-    int n;
-    __device__ __forceinline__ V3<R> p(int v) const {
-        // (selected per component: a choice between whole vectors would go
-        // through the stack)
-        const V3<R> g = work.p(v);
-        const bool s0 = v == 0, se = v == n - 1;
-        return {s0 ? y0.x : (se ? yend.x : g.x), s0 ? y0.y : (se ? yend.y : g.y), s0 ? y0.z : (se ? yend.z : g.z)};
-    }
-    // the y walk's segment depths are kept in the work buffer (slot v: the
-    // segment leaving vertex v) for the copy-back on acceptance
-    __device__ __forceinline__ void stw(int v, R x) const { work.glb[(size_t)v * work.C].w = x; }
-};
+} // namespace rj
 
-// frame (e2, e3) of interval (k, l) of a path: root -> onb of the axis;
-// otherwise from the parent interval (kp, lp) and its vertex fp.  Both are
-// formed and one is selected by value (a choice between output references
-// would become a dynamically indexed stack slot).
-template <class R> struct Frame2 {
-    V3<R> e2, e3;
-};
+#include "rj_tree.h"
 
-template <class R>
-__device__ __forceinline__ Frame2<R> tree_frame(bool root, V3<R> e1, V3<R> fkp, V3<R> flp, V3<R> fp) {
-    V3<R> r2, r3;
-    onb(e1, r2, r3);
-    const V3<R> ep = unit_dir(fkp, flp);
-    const V3<R> g = fp - fkp;
-    const V3<R> c = {ep.y * g.z - ep.z * g.y, ep.z * g.x - ep.x * g.z, ep.x * g.y - ep.y * g.x};
-    const V3<R> c3 = Mth<R>::rsqrt(dot(c, c)) * c;
-    const V3<R> c2 = {c3.y * e1.z - c3.z * e1.y, c3.z * e1.x - c3.x * e1.z, c3.x * e1.y - c3.y * e1.x};
-    Frame2<R> f;
-    f.e2 = {root ? r2.x : c2.x, root ? r2.y : c2.y, root ? r2.z : c2.z};
-    f.e3 = {root ? r3.x : c3.x, root ? r3.y : c3.y, root ? r3.z : c3.z};
-    return f;
-}
-
-template <class R, bool LO>
-__device__ __forceinline__ void tree_move(const Tgt<R>& T, const PathRef<R, LO>& ps, const GlobalPath<R>& work,
-                                          Lane<R>& ln, const StepCtx& sc, uint64_t step, const uint32_t r[8],
-                                          R logu, int& accepted, R& logA) {
-    const int n = ln.n;
-    const V3<R> x0 = ps.p(0), xe = ps.p(n - 1);
-    // end point: von Mises-Fisher step about the current sensor normal
-    V3<R> yend;
-    {
-        const R u4 = unif<R>(r[4]), u5 = unif<R>(r[5]);
-        const R lg = Mth<R>::log(u4 + ((R)1 - u4) * (R)sc.e2k);
-        const V3<R> dd = from_eta(T, xe);
-        const V3<R> nu = Mth<R>::rsqrt(dot(dd, dd)) * dd;
-        V3<R> e2, e3;
-        onb(nu, e2, e3);
-        const R omw = -lg * (R)sc.ikappa;
-        const R sw = Mth<R>::sqrt(fmax(omw * ((R)2 - omw), (R)0));
-        const V3<R> nn = ((R)1 - omw) * nu + sw * (Mth<R>::cos2pi(u5) * e2 + Mth<R>::sin2pi(u5) * e3);
-        yend = T.eta + (T.eta_lo + T.rad * nn);
-    }
-    auto xat = [&](int v) __attribute__((always_inline)) { return ps.p(v); };
-    const TreePath<R> yp{work, x0, yend, n};
-    auto yat = [&](int v) __attribute__((always_inline)) { return yp.p(v); };
-    const R sig = Mth<R>::sqrt((R)sc.mala_h / (R)n);
-    double lj = 0.0; // sum of log J(y) - log J(x)
-    bool ok = true;
-    // Nodes in pre-order (a node before its subtrees, so every vertex's foci
-    // and frame are placed before it): node i is found by descending from the
-    // root, skipping whole left subtrees by their vertex count.  A lane visits
-    // its n - 2 nodes only.
-    for (int i = 0; i < n - 2; ++i) {
-        {
-            int k = 0, l = n - 1, kp = 0, lp = n - 1, left = i;
-            bool root = true;
-            for (;;) {
-                const int mid = (k + l) >> 1;
-                if (left == 0) break;
-                left -= 1; // the node itself
-                kp = k;
-                lp = l;
-                root = false;
-                if (left < mid - k - 1) {
-                    l = mid;
-                } else {
-                    left -= mid - k - 1;
-                    k = mid;
-                }
-            }
-            const int m = (k + l) >> 1, pm = (kp + lp) >> 1;
-            // current coordinates of x_m
-            const V3<R> xk = xat(k), xl = xat(l), xm = xat(m);
-            const V3<R> rx = xl - xk;
-            const R gx = (R)0.5 * Mth<R>::sqrt(dot(rx, rx));
-            const V3<R> e1x = ((R)0.5 * Mth<R>::rcp(gx)) * rx;
-            const Frame2<R> fx = tree_frame(root, e1x, xat(kp), xat(lp), xat(pm));
-            const V3<R> e2x = fx.e2, e3x = fx.e3;
-            const V3<R> va = xk - xm, vb = xl - xm;
-            const R dA = Mth<R>::sqrt(dot(va, va)), dB = Mth<R>::sqrt(dot(vb, vb));
-            const V3<R> ua = Mth<R>::rcp(dA) * va, ub = Mth<R>::rcp(dB) * vb;
-            const V3<R> sp = ua + ub, sm = ua - ub;
-            const R np2 = dot(sp, sp), nm2 = dot(sm, sm);
-            const R zeta = (R)0.5 * Mth<R>::log(np2 * Mth<R>::rcp(nm2));
-            const R tt = Mth<R>::log(dA * Mth<R>::rcp(dB));
-            const V3<R> q = xm - (R)0.5 * (xk + xl);
-            const R phi = atan2(dot(q, e3x), dot(q, e2x));
-            // log J(x): sech zeta = sin s, cosh t - tanh zeta = (dA - dB)^2 / (2 dA dB) + (1 - cos s)
-            const R dd = dA - dB;
-            const R denx = dd * dd * Mth<R>::rcp((R)2 * dA * dB) + (R)0.5 * nm2;
-            lj -= (double)((R)3 * Mth<R>::log(gx) + Mth<R>::log((R)0.25 * np2 * nm2) - (R)3 * Mth<R>::log(denx));
-            // proposed coordinates
-            uint32_t qd[4] = {sc.chain, (uint32_t)step, (uint32_t)(step >> 32), 2u + (uint32_t)m};
-            philox4x32_10(qd, sc.k0, sc.k1);
-            V3<R> xi;
-            box_muller3<R>(qd[0], qd[1], qd[2], qd[3], xi);
-            const R z2 = zeta + sig * xi.x, t2 = tt + sig * xi.y, p2 = phi + sig * xi.z;
-            // y_m from its (already placed) foci and frame
-            const V3<R> yk = yat(k), yl = yat(l);
-            const V3<R> ry = yl - yk;
-            const R gy = (R)0.5 * Mth<R>::sqrt(dot(ry, ry));
-            const V3<R> e1y = ((R)0.5 * Mth<R>::rcp(gy)) * ry;
-            const Frame2<R> fy = tree_frame(root, e1y, yat(kp), yat(lp), yat(pm));
-            const V3<R> e2y = fy.e2, e3y = fy.e3;
-            // tanh and sech of zeta and cosh t - tanh zeta without cancellation
-            const R az = fabs(z2);
-            const R ez = Mth<R>::exp((R)-2 * az);
-            const R th = copysign(((R)1 - ez) * Mth<R>::rcp((R)1 + ez), z2);
-            const R sh = (R)2 * Mth<R>::sqrt(ez) * Mth<R>::rcp((R)1 + ez);
-            const R et = Mth<R>::exp(t2), iet = Mth<R>::rcp(et);
-            const R sht = (R)0.5 * (et - iet);
-            const R s2h = sht * sht * Mth<R>::rcp((R)0.5 * (et + iet) + (R)1); // cosh t - 1 = sinh^2 t / (cosh t + 1)
-            const R omt = z2 > (R)0 ? (R)2 * ez * Mth<R>::rcp((R)1 + ez) : (R)1 - th; // 1 - tanh zeta
-            const R deny = s2h + omt;
-            const V3<R> dir = sht * e1y + sh * (Mth<R>::cos2pi(p2 * (R)0.15915494309189534) * e2y +
-                                                Mth<R>::sin2pi(p2 * (R)0.15915494309189534) * e3y);
-            const V3<R> ym = (R)0.5 * (yk + yl) + (gy * Mth<R>::rcp(deny)) * dir;
-            lj += (double)((R)3 * Mth<R>::log(gy) + (R)2 * Mth<R>::log(sh) - (R)3 * Mth<R>::log(deny));
-            ok = ok && isfinite(ym.x) && isfinite(ym.y) && isfinite(ym.z);
-            work.glb[(size_t)m * work.C] = Vtx<R>{ym.x, ym.y, ym.z, (R)0};
-        }
-    }
-    double Lx, Ly = 0.0, Sy = 0.0;
-    const double lpx = full_logp(T, ps, n, Lx);
-    const double lpy = ok ? full_logp(T, yp, n, Ly, &Sy) : -__builtin_inf();
-    const double la = lpy - lpx + lj;
-    logA = isfinite(lpy) && isfinite(la) ? (R)la : Mth<R>::ninf();
-    if (logu < logA) {
-        accepted = 1;
-        // the proposal with the depths its walk left in the work buffer
-        for (int k = 1; k <= n - 2; ++k) ps.st(k, work.ld(k));
-        ps.stw(0, work.ld(0).w);
-        ps.st(n - 1, Vtx<R>{yend.x, yend.y, yend.z, (R)0});
-        ln.L = Ly;
-        ln.S = Sy;
-    }
-}
+namespace rj {
 
 // A perturbation step: moves interior vertex j or the end point (or, by the
-// sampler, every interior vertex, or the whole path in tree coordinates).
+// joint Langevin sampler, every interior vertex).
 // n does not change.  Returns the move kind, log A, the vertex and whether it
 // was accepted.
 template <class R, bool LO, int SAMP>
 __device__ __forceinline__ void perturb_move(const Tgt<R>& T, const PathRef<R, LO>& ps, const GlobalPath<R>& work,
                                              Lane<R>& ln, const StepCtx& sc, uint64_t step, const uint32_t r[8], R logu,
-                                             bool tree, int& move, int& idx, int& accepted, R& logA) {
+                                             int& move, int& idx, int& accepted, R& logA) {
     const int n = ln.n;
     idx = -1;
     accepted = 0;
     logA = Mth<R>::ninf();
     const V3<R> ex = {(R)1, (R)0, (R)0};
-    if constexpr (SAMP == SAMP_TREE) {
-        if (tree) {
-            move = MV_TREE;
-            tree_move<R, LO>(T, ps, work, ln, sc, step, r, logu, accepted, logA);
-            return;
-        }
-    }
     const int j = 1 + pick(r[0], (uint32_t)(n - 1));
     idx = j;
     const bool is_end = (j == n - 1);
@@ -1206,14 +1025,13 @@ __device__ __forceinline__ void jump_move(const Tgt<R>& T, const PathRef<R, LO>&
     }
 }
 
-// One perturbation step of a lane inside the step loop (the tree sampler's
-// first step of a cycle is a tree-coordinate move), then the counts.  The
+// One perturbation step of a lane inside the step loop, then the counts.  The
 // class of a step is the wave's, so each class has its own loop below and its
 // counts are touched only there.
 template <class R, bool LO, int SAMP>
 __device__ __forceinline__ void perturb_step(const KArgs& a, const Tgt<R>& T, const PathRef<R, LO>& ps,
                                              const GlobalPath<R>& work, Lane<R>& ln, const StepCtx& sc,
-                                             const StepLoop& lp, bool first, int c) {
+                                             const StepLoop& lp, int c) {
     const uint64_t step = lp.step0 + (uint64_t)lp.s;
     uint32_t r[8];
     draw8<SAMP>(sc, step, r);
@@ -1221,17 +1039,39 @@ __device__ __forceinline__ void perturb_step(const KArgs& a, const Tgt<R>& T, co
     const R logu = ln.live ? Mth<R>::log(unif<R>(r[1])) : -Mth<R>::ninf();
     int move, idx, accepted;
     R logA;
-    perturb_move<R, LO, SAMP>(T, ps, work, ln, sc, step, r, logu, SAMP == SAMP_TREE && first, move, idx, accepted, logA);
+    perturb_move<R, LO, SAMP>(T, ps, work, ln, sc, step, r, logu, move, idx, accepted, logA);
     if (lp.counted()) {
         ln.ap += (uint32_t)accepted;
-        if constexpr (SAMP != SAMP_PLAIN) {
-            const uint32_t im = (move == MV_MALA || move == MV_LMALA || move == MV_TREE) ? 1u : 0u;
+        if constexpr (SAMP == SAMP_JOINT || SAMP == SAMP_LOCAL) {
+            const uint32_t im = (move == MV_MALA || move == MV_LMALA) ? 1u : 0u;
             ln.mp += im;
             ln.ma += im & (uint32_t)accepted;
         }
         count_step(ln);
     }
     put_trace(a, ln, c, lp.s, move, idx, accepted, logA, logu);
+}
+
+// The tree sampler's first step of every cycle: a tree-coordinate move of
+// every chain of the wave.
+template <class R>
+__device__ __forceinline__ void tree_step(const KArgs& a, const Tgt<R>& T, const PathRef<R, false>& ps,
+                                          const WavePaths<R>& W, Lane<R>& ln, const StepCtx& sc, const StepLoop& lp,
+                                          bool one_target, int c) {
+    const uint64_t step = lp.step0 + (uint64_t)lp.s;
+    uint32_t r[8];
+    draw8<SAMP_TREE>(sc, step, r);
+    const R logu = ln.live ? Mth<R>::log(unif<R>(r[1])) : -Mth<R>::ninf();
+    int accepted;
+    R logA;
+    tree_move<R>(T, ps, W, ln, sc, step, r, logu, one_target, accepted, logA);
+    if (lp.counted()) {
+        ln.ap += (uint32_t)accepted;
+        ln.mp += 1u;
+        ln.ma += (uint32_t)accepted;
+        count_step(ln);
+    }
+    put_trace(a, ln, c, lp.s, MV_TREE, -1, accepted, logA, logu);
 }
 
 template <class R, bool LO, int SAMP>
@@ -1286,19 +1126,38 @@ template <class R, int MK, int SAMP, bool SL, bool EVEN> __device__ __forceinlin
         tab = MedTab<R>{lay, edge, pre};
         tab_bytes = a.tab_bytes;
     }
-    const int c = blockIdx.x * bs + tid;
-    if (c >= a.C) return;
     const size_t C = (size_t)a.C;
+    const int lane = tid % WAVE, cap = a.cap;
+    // the wave's first chain; a wave of the tree sampler owns a.cpw chains
+    // (its first lanes') and shares their whole-path moves over all 64 lanes
+    constexpr bool SHARED = SAMP == SAMP_TREE;
+    const int c0 = (int)blockIdx.x * (bs / WAVE) * (SHARED ? a.cpw : WAVE) + (tid / WAVE) * (SHARED ? a.cpw : WAVE);
+    int c = c0 + lane;
+    const bool own = c < a.C && (!SHARED || lane < a.cpw);
+    if (!SHARED && !own) return;
     // this wave's tile, past its leading padding slot
-    LdsPtr<R> lslots = (LdsPtr<R>)((L4<R>*)(smem + tab_bytes) + (size_t)(tid / WAVE) * (a.V + SLOT_PAD) * WAVE +
-                                   WAVE + tid % WAVE);
-    const int t = a.target[c];
+    const LdsPtr<R> tiles = (LdsPtr<R>)((L4<R>*)(smem + tab_bytes));
+    const LdsPtr<R> tile = tiles + (size_t)(tid / WAVE) * (a.V + SLOT_PAD) * WAVE + WAVE;
+    const LdsPtr<R> lslots = tile + lane;
+    int t = own ? a.target[c] : -1;
     Lane<R> ln{};
-    ln.n = a.n[c];
-    const int cap = a.cap;
+    ln.n = own ? a.n[c] : 0;
     // malformed chains are flagged and never touched
-    if (t < 0 || t >= a.T || ln.n < 2 || ln.n > cap || a.medium[t] < 0 || a.medium[t] >= a.n_media) {
-        a.status[c] = 1;
+    const bool good = own && t >= 0 && t < a.T && ln.n >= 2 && ln.n <= cap && a.medium[t] >= 0 && a.medium[t] < a.n_media;
+    if (own && !good) a.status[c] = 1;
+    if (SHARED) {
+        // lanes without a chain stay for the shared moves, as a dead chain of
+        // two equal vertices on the first good lane's target
+        const uint64_t m = __ballot(good);
+        if (m == 0) return;
+        const int from = __ffsll((unsigned long long)m) - 1;
+        const int t1 = __shfl(t, from, WAVE);
+        if (!good) {
+            t = t1;
+            c = c0 + from;
+            ln.n = 2;
+        }
+    } else if (!good) {
         return;
     }
     Tgt<R> T;
@@ -1319,14 +1178,38 @@ template <class R, int MK, int SAMP, bool SL, bool EVEN> __device__ __forceinlin
     GlobalPath<R> work{a.work ? (Vtx<R>*)a.work + c : nullptr, C};
     // stage the LDS part of the path
     const int nl0 = ln.n < a.V ? ln.n : a.V;
-    for (int v = 0; v < nl0; ++v) lds_st<R>(ps.lds + v * WAVE, ps.glb[(size_t)v * C]);
+    if (!SHARED || good) {
+        for (int v = 0; v < nl0; ++v) lds_st<R>(ps.lds + v * WAVE, ps.glb[(size_t)v * C]);
+    } else {
+        for (int v = 0; v < nl0; ++v) lds_st<R>(ps.lds + v * WAVE, Vtx<R>{(R)0, (R)0, (R)0, (R)0});
+    }
     // the depths a birth's scan reads past the path (slot V is padding): none
     for (int v = nl0; v <= a.V && v < scan_slots<R, SAMP>(); ++v) pl.stw(v, (R)0);
     if (a.V < scan_slots<R, SAMP>()) pl.stw(a.V, (R)0);
 
     ln.lp = full_logp(T, ps, ln.n, ln.L, &ln.S);
-    const bool healthy = isfinite(ln.lp);
-    a.status[c] = healthy ? 0 : 1;
+    const bool healthy = good && isfinite(ln.lp);
+    if (good) a.status[c] = healthy ? 0 : 1;
+    WavePaths<R> W{};
+    bool one_target = false;
+    if constexpr (SHARED) {
+        // proposals: the tile's columns from 32 on where the wave owns at most
+        // 32 chains, else a.Vy slots' room behind the block's tiles
+        const bool half = a.cpw < WAVE;
+        W.x = tile;
+        W.V = a.V;
+        W.y = half ? tile + WAVE / 2
+                   : tiles + (size_t)(bs / WAVE) * (a.V + SLOT_PAD) * WAVE + (size_t)(tid / WAVE) * a.Vy * WAVE;
+        W.My = half ? a.V * (WAVE / 2) : a.Vy * WAVE;
+        W.ymask = half ? ~(WAVE / 2 - 1) : 0;
+        W.gx = (Vtx<R>*)a.verts + c0;
+        W.part = (Vtx<R>*)a.work + (size_t)c0 * cap;
+        W.room = (a.C - c0 < a.cpw ? a.C - c0 : a.cpw) * cap;
+        W.C = C;
+        W.chain0 = (uint32_t)c0;
+        W.lane = lane;
+        one_target = __all(t == __builtin_amdgcn_readfirstlane(t));
+    }
 
     StepCtx sc;
     sc.chain = (uint32_t)c;
@@ -1371,13 +1254,16 @@ template <class R, int MK, int SAMP, bool SL, bool EVEN> __device__ __forceinlin
         const int left = a.steps - lp.s;
         if (phase < a.n_perturb) {
             const int m = a.n_perturb - phase < left ? a.n_perturb - phase : left, end = lp.s + m;
-            bool first = phase == 0;
+            if constexpr (SHARED) {
+                if (phase == 0) {
+                    tree_step<R>(a, T, ps, W, ln, sc, lp, one_target, c);
+                    ++lp.s;
+                }
+            }
             if (__all(ln.n < a.V)) {
-                for (; lp.s < end; ++lp.s, first = false)
-                    perturb_step<R, true, SAMP>(a, T, pl, work, ln, sc, lp, first, c);
+                for (; lp.s < end; ++lp.s) perturb_step<R, true, SAMP>(a, T, pl, work, ln, sc, lp, c);
             } else {
-                for (; lp.s < end; ++lp.s, first = false)
-                    perturb_step<R, false, SAMP>(a, T, ps, work, ln, sc, lp, first, c);
+                for (; lp.s < end; ++lp.s) perturb_step<R, false, SAMP>(a, T, ps, work, ln, sc, lp, c);
             }
             phase += m;
         } else {
@@ -1401,6 +1287,7 @@ template <class R, int MK, int SAMP, bool SL, bool EVEN> __device__ __forceinlin
     fold_run(ln, T.n0, sc, lp);
     // log p of the final path (refreshed once rather than tracked per step)
     if (healthy) ln.lp = full_logp(T, ps, ln.n, ln.L);
+    if (SHARED && !good) return;
     // write back the LDS part, the vertex count, log p and the statistics
     const int nw = ln.n < a.V ? ln.n : a.V;
     for (int v = 0; v < nw; ++v) ps.glb[(size_t)v * C] = lds_ld<R>(ps.lds + v * WAVE);
