@@ -1206,6 +1206,7 @@ template <class R, int MK, int SAMP, bool SL, bool EVEN> __device__ __forceinlin
         W.part = (Vtx<R>*)a.work + (size_t)c0 * cap;
         W.room = (a.C - c0 < a.cpw ? a.C - c0 : a.cpw) * cap;
         W.C = C;
+        W.cpw = a.cpw;
         W.chain0 = (uint32_t)c0;
         W.lane = lane;
         one_target = __all(t == __builtin_amdgcn_readfirstlane(t));

@@ -32,8 +32,9 @@ namespace rj {
 // 266 us per tree step that way.  Here the wave shares the work of its chains
 // instead: at level d of the trees the items are (chain, node), 2^d per chain
 // that reaches the level, 64 at a time; then the items are (chain, segment)
-// over both walks of log p.  The terms of log A are summed per chain in FP64 in
-// the tile's leading padding slot, which nothing else keeps.  The walks use the
+// over both walks of log p, and over the accepted proposals' copy-back.  The
+// terms of log A are summed per chain in FP64 in the tile's leading padding
+// slot, which nothing else keeps.  The walks use the
 // lane's own target, so a wave with several targets walks its chains lane by
 // lane.  With fewer chains than two waves per SIMD a wave owns fewer than 64
 // chains (cpw), so that more waves share the work.
@@ -52,6 +53,7 @@ template <class R> struct WavePaths {
     Vtx<R>* gx;        // vertex 0 of the wave's first chain
     Vtx<R>* part;      // the wave's part of the work buffer (cap vertices per chain)
     int V, My, ymask;  // LDS vertex i of the proposals is y[i + (i & ymask)]
+    int cpw;           // chains of the wave (a power of two; the last wave may have fewer)
     int room;          // vertices of the wave's part
     size_t C;
     uint32_t chain0;   // the wave's first chain
@@ -69,10 +71,10 @@ template <class R> struct WavePaths {
         if (i < My) ((LdsScalar<R>)(y + (i + (i & ymask))))[3] = w;
         else part[i].w = w;
     }
-    // the chain's FP64 sum of the terms of log A (padding slot -1)
+    // the chain's FP64 sums (padding slot -1 holds two)
     __device__ __forceinline__ LdsScalar<double> sum(int q) const { return (LdsScalar<double>)(x - WAVE + q); }
-    __device__ __forceinline__ void add(int q, double v) const {
-        __hip_atomic_fetch_add(sum(q), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __device__ __forceinline__ void add(int q, double v, int k = 0) const {
+        __hip_atomic_fetch_add(sum(q) + k, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
 };
 
@@ -83,10 +85,55 @@ template <class R> struct WaveChain {
     int q, at, copy;
     __device__ __forceinline__ V3<R> x(int v) const {
         if (v < W.V) return pos(lds_ld<R>(W.x + v * WAVE + q));
-        if (copy) return pos(W.part[copy + at + v]);
-        return pos(W.gx[(size_t)v * W.C + q]);
+        return far_x(v);
+    }
+    __device__ __forceinline__ V3<R> far_x(int v) const {
+        const Vtx<R>* const p = copy ? W.part + (copy + at + v) : W.gx + ((size_t)v * W.C + q);
+        const L4<R> g = *(const L4<R>*)p;
+        return {g.x, g.y, g.z};
     }
     __device__ __forceinline__ V3<R> y(int v) const { return pos(W.ldy(at + v)); }
+    // Several vertices at once: LDS reads for all (the ones that lie elsewhere
+    // read some slot), then one branch that fetches those together.
+    template <int K> __device__ __forceinline__ void xs(const int (&v)[K], V3<R> (&o)[K]) const {
+        int hi = v[0];
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+            o[i] = pos(lds_ld<R>(W.x + (v[i] < W.V ? v[i] : W.V) * WAVE + q));
+            hi = max(hi, v[i]);
+        }
+        if (hi >= W.V) {
+            V3<R> g[K];
+#pragma unroll
+            for (int i = 0; i < K; ++i) g[i] = far_x(v[i]);
+#pragma unroll
+            for (int i = 0; i < K; ++i)
+                if (v[i] >= W.V) o[i] = g[i];
+        }
+    }
+    template <int K> __device__ __forceinline__ void ys(const int (&v)[K], V3<R> (&o)[K]) const {
+        int hi = v[0];
+#pragma unroll
+        for (int i = 0; i < K; ++i) hi = max(hi, v[i]);
+        if (W.My > 0) { // (uniform)
+#pragma unroll
+            for (int i = 0; i < K; ++i) {
+                const int j = min(at + v[i], W.My - 1);
+                o[i] = pos(lds_ld<R>(W.y + (j + (j & W.ymask))));
+            }
+        }
+        if (at + hi >= W.My) {
+            V3<R> g[K];
+#pragma unroll
+            for (int i = 0; i < K; ++i) {
+                const L4<R> p = *(const L4<R>*)(W.part + (at + v[i]));
+                g[i] = {p.x, p.y, p.z};
+            }
+#pragma unroll
+            for (int i = 0; i < K; ++i)
+                if (at + v[i] >= W.My) o[i] = g[i];
+        }
+    }
 };
 
 // One chain's path or proposal as the log p walk of a single lane reads it.
@@ -95,6 +142,57 @@ template <class R, bool Y> struct LanePath {
     __device__ __forceinline__ V3<R> p(int v) const { return Y ? c.y(v) : c.x(v); }
     __device__ __forceinline__ void stw(int v, R t) const {
         if (Y) c.W.styw(c.at + v, t);
+    }
+};
+
+// Inclusive prefix sum over the 64 lanes by data-parallel moves (no LDS).
+__device__ __forceinline__ int wave_prefix(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true); // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true); // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true); // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true); // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false); // row_bcast:15 into rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false); // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
+// Items of the wave's chains in chain order, 64 at a time: `first` is the
+// chain's first item and `cnt` its count (0: none) in its own lane.  next()
+// gives each lane its item's chain and the item's place in it; the starts in
+// the window are one bit mask, whose bits below a lane count the chains.
+struct WaveItems {
+    int lane, first, base, total, seen, nth;
+    bool has;
+    __device__ __forceinline__ void init(int lane_, int cnt) {
+        lane = lane_;
+        has = cnt > 0;
+        const int end = wave_prefix(cnt);
+        total = __builtin_amdgcn_readlane(end, WAVE - 1);
+        first = end - cnt;
+        const uint64_t m = __ballot(has);
+        const int n = __popcll(m);
+        const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        nth = __builtin_amdgcn_ds_permute(4 * (has ? rank : n + lane - rank), lane); // lane r: the r-th chain's lane
+        base = 0;
+        seen = 0;
+    }
+    __device__ __forceinline__ bool more() const { return base < total; }
+    // the window's items: true if this lane has one; q: its chain's lane, k: its place
+    __device__ __forceinline__ bool next(int& q, int& k) {
+        const int s = first - base;
+        const bool in = has && s >= 0 && s < WAVE;
+        const uint64_t bit = in ? 1ull << s : 0ull;
+        // the starts are distinct, so their sum is their union
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane(wave_prefix((int)(uint32_t)bit), WAVE - 1);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane(wave_prefix((int)(uint32_t)(bit >> 32)), WAVE - 1);
+        const int upto = (int)__builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u)) +
+                         (int)(((lane < 32 ? lo : hi) >> (lane & 31)) & 1u);
+        q = __shfl(nth, (seen + upto - 1) & (WAVE - 1), WAVE);
+        k = base + lane - __shfl(first, q, WAVE);
+        const bool mine = base + lane < total;
+        seen += __popc(lo) + __popc(hi);
+        base += WAVE;
+        return mine;
     }
 };
 
@@ -128,9 +226,14 @@ template <class R>
 __device__ __forceinline__ void tree_node(const WaveChain<R>& c, const StepCtx& sc, uint64_t step, R sig, bool root,
                                           bool right, int kp, int lp, int m) {
     const int pm = (kp + lp) >> 1;
-    const V3<R> xkp = c.x(kp), xlp = c.x(lp), xpm = c.x(pm);
-    const V3<R> ykp = c.y(kp), ylp = c.y(lp), ypm = c.y(pm);
-    const V3<R> xm = root ? xpm : c.x(m);
+    V3<R> xv[4], yv[3];
+    {
+        const int vx[4] = {kp, lp, pm, m}, vy[3] = {kp, lp, pm};
+        c.xs(vx, xv);
+        c.ys(vy, yv);
+    }
+    const V3<R> xkp = xv[0], xlp = xv[1], xpm = xv[2], xm = xv[3];
+    const V3<R> ykp = yv[0], ylp = yv[1], ypm = yv[2]; // (the root's own vertex, not placed yet, is not used)
     // the foci: the parent's vertex and one of its foci
     auto pick3 = [](bool s, V3<R> a, V3<R> b) __attribute__((always_inline)) {
         return V3<R>{s ? a.x : b.x, s ? a.y : b.y, s ? a.z : b.z};
@@ -220,17 +323,22 @@ __device__ __forceinline__ void tree_move(const Tgt<R>& T, const PathRef<R, fals
     const V3<R> x0 = ps.p(0), xe = ps.p(n - 1);
     // the chains' places among the wave's vertices, and the paths' copy
     const int mine = act ? n : 0;
-    int at = mine;
-#pragma unroll
-    for (int o = 1; o < WAVE; o <<= 1) {
-        const int up = __shfl_up(at, o, WAVE);
-        at += lane >= o ? up : 0;
-    }
-    const int all = __shfl(at, WAVE - 1, WAVE);
-    at -= mine;
+    const int upto = wave_prefix(mine), at = upto - mine;
+    const int all = __builtin_amdgcn_readlane(upto, WAVE - 1);
     const int copy = 2 * all <= W.room && __any(mine > W.V) ? all : 0;
     if (copy) {
-        for (int v = W.V; v < mine; ++v) W.part[copy + at + v] = ps.glb[(size_t)v * W.C];
+        // row by row, lanes over the wave's chains (whole cache lines), four rows in flight
+        const int q = lane & (W.cpw - 1), rows = WAVE / W.cpw;
+        const int nq = __shfl(mine, q, WAVE), to = copy + __shfl(at, q, WAVE);
+        for (int v = W.V + lane / W.cpw; __any(v < nq); v += 4 * rows) {
+            L4<R> g[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (v + i * rows < nq) g[i] = *(const L4<R>*)(W.gx + ((size_t)(v + i * rows) * W.C + q));
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (v + i * rows < nq) *(L4<R>*)(W.part + (to + v + i * rows)) = g[i];
+        }
     }
     // end point: von Mises-Fisher step about the current sensor normal
     V3<R> yend;
@@ -287,24 +395,22 @@ __device__ __forceinline__ void tree_move(const Tgt<R>& T, const PathRef<R, fals
     }
     // log p(y) - log p(x)
     if (one_target) {
-        // items: the segments of all chains in order; chain q's are those from
-        // at(q) - q' on, q' chains with segments lying before it
-        const uint64_t have = __ballot(N > 0);
-        const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(have >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)have, 0u));
-        const int first = at - before, end = first + N, total = all - __popcll(have);
-        for (int base = 0; base < total; base += WAVE) {
-            const int i = base + lane;
-            int q = 0; // the first lane with end > i
-#pragma unroll
-            for (int o = WAVE / 2; o > 0; o >>= 1) q += __shfl(end, q + o - 1, WAVE) <= i ? o : 0;
-            q &= WAVE - 1;
+        // items: the segments of all chains in order
+        WaveItems it;
+        it.init(lane, N);
+        while (it.more()) {
+            int q, k;
+            const bool has = it.next(q, k);
             const WaveChain<R> cq{W, q, __shfl(at, q, WAVE), copy};
-            const int nq = __shfl(n, q, WAVE), k = i - __shfl(first, q, WAVE);
-            if (i < total) {
-                const int k2 = k + 2 < nq ? k + 2 : k + 1;
+            const int nq = __shfl(n, q, WAVE);
+            if (has) {
+                const int v[3] = {k, k + 1, k + 2 < nq ? k + 2 : k + 1};
+                V3<R> x[3], y[3];
+                cq.xs(v, x);
+                cq.ys(v, y);
                 R tx, ty;
-                const double a = walk_term(T, nq, k, cq.x(k), cq.x(k + 1), cq.x(k2), tx);
-                const double b = walk_term(T, nq, k, cq.y(k), cq.y(k + 1), cq.y(k2), ty);
+                const double a = walk_term(T, nq, k, x[0], x[1], x[2], tx);
+                const double b = walk_term(T, nq, k, y[0], y[1], y[2], ty);
                 W.styw(cq.at + k, ty);
                 W.add(q, b - a);
             }
@@ -320,26 +426,37 @@ __device__ __forceinline__ void tree_move(const Tgt<R>& T, const PathRef<R, fals
     if (act) {
         const double la = *W.sum(lane);
         logA = isfinite(la) ? (R)la : Mth<R>::ninf();
-        if (logu < logA) {
-            accepted = 1;
-            // the proposal with the depths its walk left, its length and depth
-            // sum in path order as full_logp forms them
-            double L = 0.0, S = 0.0;
-            Vtx<R> f = W.ldy(at);
-            ps.stw(0, f.w);
-            for (int k = 1; k < n; ++k) {
-                const Vtx<R> g = W.ldy(at + k);
-                const V3<R> d = pos(g) - pos(f);
+        accepted = logu < logA ? 1 : 0;
+        // (the sums of the accepted proposal's length and depths next)
+        W.sum(lane)[0] = 0.0;
+        W.sum(lane)[1] = 0.0;
+    }
+    // the accepted proposals, with the depths their walk left
+    WaveItems it;
+    it.init(lane, accepted ? n : 0);
+    while (it.more()) {
+        int q, k;
+        const bool has = it.next(q, k);
+        const int aq = __shfl(at, q, WAVE), nq = __shfl(n, q, WAVE);
+        if (has) {
+            Vtx<R> f = W.ldy(aq + k);
+            if (k < nq - 1) {
+                const V3<R> d = pos(W.ldy(aq + k + 1)) - pos(f);
                 const R l2 = dot(d, d);
                 const R len = l2 * Mth<R>::rsqrt(l2);
-                L += (double)len;
-                S += (double)f.w;
-                ps.st(k, k < n - 1 ? g : Vtx<R>{g.x, g.y, g.z, (R)0});
-                f = g;
+                W.add(q, (double)len, 0);
+                W.add(q, (double)f.w, 1);
+            } else {
+                f.w = (R)0;
             }
-            ln.L = L;
-            ln.S = S;
+            if (k < W.V) lds_st<R>(W.x + k * WAVE + q, f);
+            else W.gx[(size_t)k * W.C + q] = f;
         }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    if (accepted) {
+        ln.L = W.sum(lane)[0];
+        ln.S = W.sum(lane)[1];
     }
 }
 
