@@ -537,4 +537,24 @@ template <class R> __device__ __forceinline__ MedTab<R> hbm_tab(const KArgs& a) 
     return MedTab<R>{(const R*)a.lay, a.edge, a.pre};
 }
 
+// Bytes of the media tables in LDS: the layer table, then the edges, then the
+// prefix integrals, each 16-byte aligned.
+template <class R> __host__ __device__ inline size_t table_bytes(const KArgs& a) {
+    const size_t lay = ((size_t)a.L_total * LY_NW * sizeof(R) + 15) & ~(size_t)15;
+    return lay + 8 * (((size_t)a.n_edges + 1) & ~(size_t)1) + 16 * (size_t)a.n_edges;
+}
+
+// Copies them to `smem` (all threads of the block; the caller synchronises).
+template <class R> __device__ __forceinline__ MedTab<R> stage_tables(const KArgs& a, unsigned char* smem) {
+    const size_t nl = (size_t)a.L_total * LY_NW, ne = (size_t)a.n_edges;
+    R* lay = (R*)smem;
+    double* edge = (double*)(smem + ((nl * sizeof(R) + 15) & ~(size_t)15));
+    double* pre = edge + ((ne + 1) & ~(size_t)1);
+    const size_t tid = threadIdx.x, bs = blockDim.x;
+    for (size_t i = tid; i < nl; i += bs) lay[i] = ((const R*)a.lay)[i];
+    for (size_t i = tid; i < ne; i += bs) edge[i] = a.edge[i];
+    for (size_t i = tid; i < 2 * ne; i += bs) pre[i] = a.pre[i];
+    return MedTab<R>{lay, edge, pre};
+}
+
 } // namespace rj

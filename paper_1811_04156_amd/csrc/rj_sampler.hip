@@ -3,6 +3,8 @@
 // the step-kernel variants (rj_step.h, rj_run.h).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "rj_step.h"
 #include "rj_wave.h"
 
@@ -10,19 +12,193 @@ namespace rj {
 
 // ---------------------------------------------------------------------------
 // Score kernel: log p, d log p / d vertices and the per-layer parameter score.
-// The score sums of a block whose chains belong to at most two targets are
-// accumulated in an LDS table (1 + 3 L_total doubles per target) and flushed
-// with one global atomic per non-zero entry; other blocks add per lane.
+//
+// Work split.  A wave takes 64 chains.  Their vertices are read row by row
+// (whole cache lines) into an LDS strip, chain after chain without gaps, and
+// the (chain, segment) items go over all lanes: one lane per chain waits for the
+// wave's longest path (mean n 6, longest 25 to 40 on the ragged batches), which
+// is where the 443 us of 2^20 chains went (19 us at the rate of a large copy),
+// with FP64 layer lookups and two to four FP64 atomics of every lane per
+// vertex; now 205 us (tables read from HBM and two waves per SIMD: 315).
+//
+// The score sums of a block whose chains belong to at most two targets go to
+// an LDS table, per target the sum of the weights and per layer the weighted
+// path length, scatterings and d log sigma / dg, which become the derivatives
+// when the block adds them to the caller's sums; other blocks add per item.
 // ---------------------------------------------------------------------------
+// Facts of the launch's media that fold the lookups' tests (as in the step
+// kernel): every medium homogeneous, every medium of several evenly spaced
+// layers (both without the simplified-Liu term), or neither.
+enum { GK_ANY = 0, GK_EVEN = 1, GK_HOM = 2 };
+
+// Where a chain's score contributions go: the block's LDS table (layer sums)
+// or the caller's array (derivatives).
+struct ScoreDst {
+    double* row; // the target's row: weight, then three per layer
+    bool table;
+    // path length len (weighted) in a layer with coefficients av, bv
+    __device__ __forceinline__ void length(int l, double len, double av, double bv) const {
+        double* const p = row + 1 + 3 * l;
+        if (table) {
+            atomicAdd(p, len);
+        } else {
+            // d/d lambda_s = -b^2 d/db, d/d lambda_a = -a^2 d/da, with d log p/da = -L_l and
+            // d log p/db = N_l / b - L_l (L_l: path length in layer l, N_l: scatterings in l)
+            atomicAdd(p, bv * bv * len);
+            atomicAdd(p + 1, av * av * len);
+        }
+    }
+    __device__ __forceinline__ void scatter(int l, double w, double dg, double bv) const {
+        double* const p = row + 1 + 3 * l;
+        if (table) atomicAdd(p + 1, w);
+        else atomicAdd(p, -bv * w); // log b at a scattering vertex
+        atomicAdd(p + 2, w * dg);
+    }
+};
+
+// d log sigma / dg at a turn, q = |ua - ub|^2
+__device__ __forceinline__ double dturn_dg(double g, double fsl, double q) {
+    double mu = 1.0 - 0.5 * q;
+    double den = (1 - g) * (1 - g) + g * q;
+    double dhg = -2 * g / (1 - g * g) - 3 * (g - mu) / den;
+    if (fsl == 0.0) return dhg;
+    const double PI = 3.14159265358979323846;
+    double lhg = log((1 - g * g) / (4 * PI)) - 1.5 * log(den);
+    double lsl = log((1 + g) / (1 - g) / (4 * PI)) + 2 * g / (1 - g) * log(0.5 * (1 + mu));
+    double dsl = 2.0 / ((1 + g) * (1 - g)) + 2.0 / ((1 - g) * (1 - g)) * log(0.5 * (1 + mu));
+    double m = lhg > lsl ? lhg : lsl;
+    double es = fsl * exp(lsl - m), eh = (1 - fsl) * exp(lhg - m);
+    return (es * dsl + eh * dhg) / (es + eh);
+}
+
+// The score contributions of the segment P -> Q of weight w: its length per
+// layer and, where `turn`, the scattering at P, which the unit vector um leads
+// to.
 template <class R>
-__global__ void __launch_bounds__(256) grad_kernel(KArgs a, double* logp_out, Vtx<R>* dv, double* score,
-                                                   int L_total, int lds_rows, int lweight) {
+__device__ __forceinline__ void segment_score(const Tgt<R>& T, int off, const ScoreDst& D, double w, V3<R> P, V3<R> Q,
+                                              bool turn, V3<R> um) {
+    const V3<R> r = Q - P;
+    const R l2 = dot(r, r), il = Mth<R>::rsqrt(l2);
+    const V3<R> u = il * r;
+    const double len = (double)(l2 * il);
+    const double uP = axis_u(T, P), uQ = axis_u(T, Q);
+    const int lP = layer_u(T, uP), lQ = layer_u(T, uQ);
+    if (lP == lQ) {
+        const LayV<R> ly = lay_at(T, lP);
+        D.length(off + lP, w * len, (double)ly.a, (double)ly.b);
+    } else {
+        const double lo = uP < uQ ? uP : uQ, hi = uP < uQ ? uQ : uP;
+        const int llo = lP < lQ ? lP : lQ, lhi = lP < lQ ? lQ : lP;
+        const double scl = len / (hi - lo);
+        for (int l = llo; l <= lhi; ++l) {
+            const double in = ((l == lhi ? hi : T.edge[l + 1]) - (l == llo ? lo : T.edge[l])) * scl;
+            const LayV<R> ly = lay_at(T, l);
+            D.length(off + l, w * in, (double)ly.a, (double)ly.b);
+        }
+    }
+    if (turn) {
+        const LayV<R> ly = lay_at(T, lP);
+        const V3<R> dd = um - u;
+        D.scatter(off + lP, w, dturn_dg((double)ly.g, (double)ly.fsl, (double)dot(dd, dd)), (double)ly.b);
+    }
+}
+
+// The wave's vertices: vertex i of its chains in order, the first `M` in LDS.
+template <class R> struct WaveStrip {
+    LdsPtr<R> lds;
+    const Vtx<R>* g; // vertex 0 of the wave's first chain
+    size_t C;
+    int M;
+    // vertex v of chain q, whose vertex 0 is vertex `at` of the wave
+    __device__ __forceinline__ V3<R> p(int at, int v, int q) const {
+        const int i = at + v;
+        if (i < M) return pos(lds_ld<R>(lds + i));
+        return pos(g[(size_t)v * C + q]);
+    }
+};
+
+// log p's factors of segment k of a path of n vertices and the gradient of its
+// vertex j = k + 1, with the terms in the order in which score_stream adds
+// them; p(v) reads vertex v.
+template <class R, class P>
+__device__ __forceinline__ double segment_grad(const Tgt<R>& T, int n, int k, P p, V3<R>& grad) {
+    const int j = k + 1;
+    const V3<R> f0 = p(k), f1 = p(j);
+    const LPt<R> p0 = lpt(T, f0), p1 = lpt(T, f1);
+    const Seg<R> A = make_seg_lp(T, f0, f1, p0, p1);
+    double t = (double)seg_term(A);
+    V3<R> dP, dQ;
+    seg_depth_grad_lp(T, p0, p1, A, dP, dQ);
+    const R ilA = (R)2 * Mth<R>::rcp(A.len);
+    const V3<R> z = {(R)0, (R)0, (R)0};
+    V3<R> g = z - dQ - ilA * A.u;
+    if (k == 0) {
+        t += (double)emit_term(T, A.u);
+        if (T.ek == RJPATH_EMIT_VMF) g = g + T.kappa * dunit(A.u, A.len, T.ed);
+    } else {
+        const V3<R> um = unit_dir(p(k - 1), f0), dd = um - A.u;
+        const R h = dturn_dmu(lay_at(T, p0.l), dot(dd, dd));
+        g = g + h * dunit(A.u, A.len, um);
+    }
+    if (j < n - 1) {
+        const V3<R> f2 = p(j + 1);
+        const LPt<R> p2 = lpt(T, f2);
+        const Seg<R> B = make_seg_lp(T, f1, f2, p1, p2);
+        seg_depth_grad_lp(T, p1, p2, B, dP, dQ);
+        const R ilB = (R)2 * Mth<R>::rcp(B.len);
+        g = g - dP + ilB * B.u;
+        const LayV<R> ly = lay_at(T, p1.l);
+        t += (double)(ly.logb + turn_term(ly, A.u, B.u));
+        {
+            const V3<R> dd = A.u - B.u;
+            const R h = dturn_dmu(ly, dot(dd, dd));
+            g = g + h * dunit(A.u, A.len, B.u) - h * dunit(B.u, B.len, A.u);
+        }
+        if (j < n - 2) {
+            const V3<R> uc = unit_dir(f2, p(j + 2)), dd = B.u - uc;
+            const R h = dturn_dmu(lay_at(T, p2.l), dot(dd, dd));
+            g = g - h * dunit(B.u, B.len, uc);
+        } else {
+            const V3<R> nu = unit_dir_eta(T, f2);
+            const R ic = Mth<R>::rcp(-dot(B.u, nu));
+            g = g - ic * ((R)-1 * dunit(B.u, B.len, nu));
+        }
+    } else {
+        t += (double)end_term(T, A.u, f1);
+        const V3<R> d = from_eta(T, f1);
+        const R dn2 = dot(d, d), idn = Mth<R>::rsqrt(dn2);
+        const V3<R> nu = idn * d;
+        const R ic = Mth<R>::rcp(-dot(A.u, nu));
+        const V3<R> dcr = (R)-1 * dunit(A.u, A.len, nu), dcd = (R)-1 * dunit(nu, dn2 * idn, A.u);
+        g = g + ic * dcr + ic * dcd;
+        if (T.dk == RJPATH_DET_PAPER) {
+            const R cr = dot(nu, T.dd);
+            const R th = tanh((R)2 * cr + (R)0.7);
+            g = g + ((R)3 - (R)2 * th) * dunit(nu, dn2 * idn, T.dd);
+        }
+    }
+    grad = g;
+    return A.len > (R)0 ? t : -__builtin_inf();
+}
+
+// LDS of a block: the media tables (tab_bytes, 0: read from HBM), the waves'
+// strips (`strip` vertices each), per wave and chain log p and (lweight) the
+// path length, the score table (lds_rows rows).
+// DV: the vertex gradients are wanted too.
+template <class R, bool DV, int KIND>
+__global__ void __launch_bounds__(256, sizeof(R) == 4 ? 3 : 1) grad_kernel(KArgs a, double* logp_out, Vtx<R>* dv,
+                                                                          double* score, int L_total, int lds_rows,
+                                                                          int lweight, int strip, int tab_bytes) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int tmin_s[4], tmax_s[4];
-    double* tab = (double*)smem;
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
     const size_t C = (size_t)a.C;
     const size_t row = 1 + 3 * (size_t)L_total;
+    const int lane = threadIdx.x % WAVE, wave = threadIdx.x / WAVE;
+    unsigned char* const behind = smem + tab_bytes + (size_t)4 * strip * sizeof(Vtx<R>);
+    double* const slp = (double*)behind + wave * WAVE;
+    double* const sL = (double*)behind + (4 + wave) * WAVE;
+    double* const tab = (double*)behind + (lweight ? 8 : 4) * WAVE;
+    const int c = blockIdx.x * blockDim.x + threadIdx.x, c0 = c - lane;
     int t = -1, n = 0;
     if (c < a.C) {
         t = a.target[c];
@@ -30,8 +206,11 @@ __global__ void __launch_bounds__(256) grad_kernel(KArgs a, double* logp_out, Vt
         if (t < 0 || t >= a.T || n < 2 || n > a.cap || a.medium[t] < 0 || a.medium[t] >= a.n_media) {
             if (logp_out) logp_out[c] = __builtin_nan("");
             t = -1;
+            n = 0;
         }
     }
+    MedTab<R> mt = hbm_tab<R>(a);
+    if (KIND != GK_HOM && tab_bytes) mt = stage_tables<R>(a, smem);
     // block-uniform choice of the score destination
     bool local = false;
     int tmin = 0;
@@ -39,86 +218,129 @@ __global__ void __launch_bounds__(256) grad_kernel(KArgs a, double* logp_out, Vt
         tmin = block_min_i32(t < 0 ? 0x7fffffff : t, tmin_s);
         const int tmax = block_max_i32(t, tmax_s);
         local = tmax >= 0 && tmax - tmin < lds_rows;
-        if (local) {
+        if (local)
             for (size_t i = threadIdx.x; i < (size_t)lds_rows * row; i += blockDim.x) tab[i] = 0.0;
-            __syncthreads();
-        }
     }
-    if (t >= 0) {
-        GlobalPath<R> ps{(Vtx<R>*)a.verts + c, C};
+    __syncthreads();
+    const uint64_t some = __ballot(t >= 0);
+    if (some) {
+        // the strip
+        const int upto = wave_prefix(n), at = upto - n;
+        const WaveStrip<R> S{(LdsPtr<R>)((L4<R>*)(smem + tab_bytes) + (size_t)wave * strip), (const Vtx<R>*)a.verts + c0, C,
+                             strip};
+        for (int v = 0; __any(v < n); v += 4) {
+            L4<R> x[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (v + i < n && at + v + i < strip) x[i] = *(const L4<R>*)(S.g + ((size_t)(v + i) * C + lane));
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (v + i < n && at + v + i < strip) S.lds[at + v + i] = x[i];
+        }
+        slp[lane] = 0.0;
+        if (lweight) sL[lane] = 0.0;
+        if (DV && t >= 0) dv[c] = Vtx<R>{(R)0, (R)0, (R)0, (R)0}; // (vertex 0 never moves)
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        // the lane's target at the moment: its item's, loaded when it changes
+        // (the chains of a target are neighbours, so mostly once)
         Tgt<R> T;
-        load_target(a, t, T, hbm_tab<R>(a));
-        double lp = score_stream(T, ps, n, [&](int k, V3<R> g) {
-            if (dv) dv[(size_t)k * C + c] = Vtx<R>{k > 0 ? g.x : (R)0, k > 0 ? g.y : (R)0, k > 0 ? g.z : (R)0, (R)0};
-        });
-        if (logp_out) logp_out[c] = lp;
-        if (score && isfinite(lp) && a.status[c] == 0) {
-            const int off = a.minfo[a.medium[t]].off;
-            const double* logw = a.logw ? a.logw + (size_t)t * (a.cap + 1) : nullptr;
-            double iw = logw ? exp(-logw[n]) : 1.0;
-            if (lweight) {
-                // weight by the path length (FP64 sum of the segment lengths)
-                double Lp = 0.0;
-                for (int k = 1; k < n; ++k) {
-                    const V3<R> d = ps.p(k) - ps.p(k - 1);
-                    Lp += sqrt((double)dot(d, d));
-                }
-                iw *= Lp;
+        int tc = __builtin_amdgcn_readlane(t, __ffsll((unsigned long long)some) - 1);
+        auto load = [&](int tt) __attribute__((always_inline)) {
+            load_target(a, tt, T, mt);
+            if (KIND == GK_HOM) {
+                T.mcnt = 1;
+                T.hom = true;
             }
-            double* sc = local ? tab + (size_t)(t - tmin) * row : score + (size_t)t * row;
-            atomicAdd(sc, iw);
-            // d/d lambda_s = -b^2 d/db, d/d lambda_a = -a^2 d/da, with d log p/da = -L_l and
-            // d log p/db = N_l / b - L_l (L_l: path length in layer l, N_l: scatterings in l)
-            V3<R> fprev = ps.p(0);
-            Seg<R> sprev;
-            for (int k = 1; k < n; ++k) {
-                V3<R> fc = ps.p(k);
-                Seg<R> s = make_seg(T, fprev, fc);
-                double uP = axis_u(T, fprev), uQ = axis_u(T, fc);
-                int lP = layer_u(T, uP), lQ = layer_u(T, uQ);
-                double lo = uP < uQ ? uP : uQ, hi = uP < uQ ? uQ : uP;
-                int llo = lP < lQ ? lP : lQ, lhi = lP < lQ ? lQ : lP;
-                double scl = lP == lQ ? 0.0 : (double)s.len / (hi - lo);
-                for (int l = llo; l <= lhi; ++l) {
-                    double Lin = lP == lQ ? (double)s.len
-                                          : ((l == lhi ? hi : T.edge[l + 1]) - (l == llo ? lo : T.edge[l])) * scl;
-                    const LayV<R> ly = lay_at(T, l);
-                    double av = (double)ly.a, bv = (double)ly.b;
-                    atomicAdd(sc + 1 + 3 * (off + l) + 0, iw * (bv * bv * Lin));
-                    atomicAdd(sc + 1 + 3 * (off + l) + 1, iw * (av * av * Lin));
+            if (KIND == GK_EVEN) {
+                T.hom = false;
+                T.uniform = 1;
+            }
+            T.sl = KIND == GK_ANY;
+            if (KIND != GK_ANY) T.l0.fsl = (R)0;
+        };
+        load(tc);
+        WaveItems it;
+        it.init(lane, n > 0 ? n - 1 : 0);
+        while (it.more()) {
+            int q, k;
+            const bool has = it.next(q, k);
+            const int aq = __shfl(at, q, WAVE), nq = __shfl(n, q, WAVE), tq = __shfl(t, q, WAVE);
+            if (__any(has && tq != tc)) {
+                tc = has ? tq : tc;
+                load(tc);
+            }
+            if (has) {
+                auto p = [&](int v) __attribute__((always_inline)) { return S.p(aq, v, q); };
+                double f;
+                if constexpr (DV) {
+                    V3<R> g;
+                    f = segment_grad(T, nq, k, p, g);
+                    dv[(size_t)(k + 1) * C + c0 + q] = Vtx<R>{g.x, g.y, g.z, (R)0};
+                } else {
+                    R tb;
+                    f = walk_term(T, nq, k, p(k), p(k + 1), p(k + 2 < nq ? k + 2 : k + 1), tb);
                 }
-                if (k >= 2) {
-                    int l = layer_at(T, fprev);
-                    const LayV<R> ly = lay_at(T, l);
-                    double bv = (double)ly.b, g = (double)ly.g, fsl = (double)ly.fsl;
-                    V3<R> dd = sprev.u - s.u;
-                    double q = (double)dot(dd, dd);
-                    double mu = 1.0 - 0.5 * q;
-                    double den = (1 - g) * (1 - g) + g * q;
-                    double dhg = -2 * g / (1 - g * g) - 3 * (g - mu) / den;
-                    double dg = dhg;
-                    if (fsl != 0.0) {
-                        const double PI = 3.14159265358979323846;
-                        double lhg = log((1 - g * g) / (4 * PI)) - 1.5 * log(den);
-                        double lsl = log((1 + g) / (1 - g) / (4 * PI)) + 2 * g / (1 - g) * log(0.5 * (1 + mu));
-                        double dsl = 2.0 / ((1 + g) * (1 - g)) + 2.0 / ((1 - g) * (1 - g)) * log(0.5 * (1 + mu));
-                        double m = lhg > lsl ? lhg : lsl;
-                        double es = fsl * exp(lsl - m), eh = (1 - fsl) * exp(lhg - m);
-                        dg = (es * dsl + eh * dhg) / (es + eh);
-                    }
-                    atomicAdd(sc + 1 + 3 * (off + l) + 0, iw * (-bv)); // log b at a scattering vertex
-                    atomicAdd(sc + 1 + 3 * (off + l) + 2, iw * dg);
+                atomicAdd(slp + q, f);
+                if (lweight) {
+                    // weight by the path length (FP64 sum of the segment lengths)
+                    const V3<R> d = p(k + 1) - p(k);
+                    atomicAdd(sL + q, sqrt((double)dot(d, d)));
                 }
-                sprev = s;
-                fprev = fc;
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        const double lp = slp[lane];
+        if (t >= 0 && logp_out) logp_out[c] = lp;
+        if (score) {
+            // the weight of a chain in the score (0: it does not count)
+            double w = 0.0;
+            if (t >= 0 && isfinite(lp) && a.status[c] == 0) {
+                const double* lw = a.logw ? a.logw + (size_t)t * (a.cap + 1) : nullptr;
+                w = lw ? exp(-lw[n]) : 1.0;
+                if (lweight) w *= sL[lane];
+            }
+            auto dst = [&](int tt) __attribute__((always_inline)) {
+                return ScoreDst{local ? tab + (size_t)(tt - tmin) * row : score + (size_t)tt * row, local};
+            };
+            if (w != 0.0) atomicAdd(dst(t).row, w);
+            it.init(lane, w != 0.0 ? n - 1 : 0);
+            while (it.more()) {
+                int q, k;
+                const bool has = it.next(q, k);
+                const int aq = __shfl(at, q, WAVE), tq = __shfl(t, q, WAVE);
+                const double wq = __shfl(w, q, WAVE);
+                if (__any(has && tq != tc)) {
+                    tc = has ? tq : tc;
+                    load(tc);
+                }
+                if (has) {
+                    const V3<R> f0 = S.p(aq, k, q), f1 = S.p(aq, k + 1, q);
+                    const V3<R> um = unit_dir(S.p(aq, k > 0 ? k - 1 : 0, q), f0);
+                    segment_score(T, a.minfo[a.medium[tc]].off, dst(tc), wq, f0, f1, k > 0, um);
+                }
             }
         }
     }
     if (local) {
+        // layer sums to derivatives
         __syncthreads();
-        for (size_t i = threadIdx.x; i < (size_t)lds_rows * row; i += blockDim.x) {
-            const size_t tt = tmin + i / row;
-            if (tab[i] != 0.0 && tt < (size_t)a.T) atomicAdd(score + (size_t)tmin * row + i, tab[i]);
+        for (size_t i = threadIdx.x; i < (size_t)lds_rows * (1 + (size_t)L_total); i += blockDim.x) {
+            const size_t r = i / (1 + (size_t)L_total), l = i % (1 + (size_t)L_total), tt = tmin + r;
+            if (tt >= (size_t)a.T) continue;
+            if (l == 0) {
+                const double w = tab[r * row];
+                if (w != 0.0) atomicAdd(score + tt * row, w);
+                continue;
+            }
+            const double* s = tab + r * row + 1 + 3 * (l - 1);
+            if (s[0] == 0.0 && s[1] == 0.0 && s[2] == 0.0) continue;
+            const R* ly = (const R*)a.lay + (l - 1) * LY_NW;
+            const double av = (double)ly[LY_A], bv = (double)ly[LY_B];
+            double* o = score + tt * row + 1 + 3 * (l - 1);
+            const double d0 = bv * bv * s[0] - bv * s[1];
+            if (d0 != 0.0) atomicAdd(o, d0);
+            if (s[0] != 0.0) atomicAdd(o + 1, av * av * s[0]);
+            if (s[2] != 0.0) atomicAdd(o + 2, s[2]);
         }
     }
 }
@@ -139,6 +361,17 @@ hipError_t launch_run(const KArgs& a, int block, hipStream_t s) {
     return launch_run_v<float, 0>(a, block, s);
 }
 
+template <class R> static hipError_t set_grad_lds_limit() {
+    const void* fns[] = {(const void*)grad_kernel<R, false, GK_ANY>,  (const void*)grad_kernel<R, true, GK_ANY>,
+                         (const void*)grad_kernel<R, false, GK_EVEN>, (const void*)grad_kernel<R, true, GK_EVEN>,
+                         (const void*)grad_kernel<R, false, GK_HOM>,  (const void*)grad_kernel<R, true, GK_HOM>};
+    for (const void* f : fns) {
+        hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 144 * 1024);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 hipError_t set_run_lds_limit() {
     hipError_t e = set_lds_limit_v<float, 0>();
     if (e == hipSuccess) e = set_lds_limit_v<float, 1>();
@@ -148,6 +381,8 @@ hipError_t set_run_lds_limit() {
     if (e == hipSuccess) e = set_lds_limit_v<double, 1>();
     if (e == hipSuccess) e = set_lds_limit_v<double, 2>();
     if (e == hipSuccess) e = set_lds_limit_v<double, 3>();
+    if (e == hipSuccess) e = set_grad_lds_limit<float>();
+    if (e == hipSuccess) e = set_grad_lds_limit<double>();
     return e;
 }
 __global__ void advance_kernel(uint64_t* counter, uint64_t steps) {
@@ -159,20 +394,41 @@ hipError_t launch_advance(uint64_t* counter, uint64_t steps, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_grad(const KArgs& a, double* logp_out, void* dv, double* score, int L_total, int lweight,
-                       hipStream_t s) {
-    int block = 256, grid = (a.C + block - 1) / block;
-    // LDS table for two targets per block when it fits in 64 KiB
+template <class R, int KIND>
+static hipError_t launch_grad_t(const KArgs& a, double* logp_out, void* dv, double* score, int L_total, int lweight,
+                                hipStream_t s) {
+    const int block = 256, grid = (a.C + block - 1) / block;
+    // LDS: the media tables (FP32 and FP64 alike, up to 16 KiB), a score table
+    // for two targets per block when it fits in 64 KiB, and the waves' strips: 7
+    // vertices per chain in FP32, which lets three blocks share a CU
     const size_t row_bytes = sizeof(double) * (1 + 3 * (size_t)L_total);
     const int rows = (score && 2 * row_bytes <= 64 * 1024) ? 2 : 0;
-    const size_t lds = rows * row_bytes;
-    if (a.prec == RJPATH_F64)
-        hipLaunchKernelGGL(grad_kernel<double>, dim3(grid), dim3(block), lds, s, a, logp_out, (Vtx<double>*)dv, score,
-                           L_total, rows, lweight);
+    size_t media = KIND == GK_HOM ? 0 : table_bytes<R>(a);
+    if (media > 16 * 1024) media = 0;
+    const int strip = (sizeof(R) == 4 ? 7 : 6) * WAVE;
+    size_t strips = 4 * (size_t)strip * sizeof(Vtx<R>);
+    const size_t lds = media + strips + (lweight ? 8 : 4) * WAVE * sizeof(double) + rows * row_bytes;
+    if (dv)
+        hipLaunchKernelGGL((grad_kernel<R, true, KIND>), dim3(grid), dim3(block), lds, s, a, logp_out, (Vtx<R>*)dv, score,
+                           L_total, rows, lweight, strip, (int)media);
     else
-        hipLaunchKernelGGL(grad_kernel<float>, dim3(grid), dim3(block), lds, s, a, logp_out, (Vtx<float>*)dv, score,
-                           L_total, rows, lweight);
+        hipLaunchKernelGGL((grad_kernel<R, false, KIND>), dim3(grid), dim3(block), lds, s, a, logp_out, (Vtx<R>*)nullptr,
+                           score, L_total, rows, lweight, strip, (int)media);
     return hipGetLastError();
+}
+
+template <class R>
+static hipError_t launch_grad_k(const KArgs& a, double* logp_out, void* dv, double* score, int L_total, int lweight,
+                                hipStream_t s) {
+    if (!a.has_sl && !a.layered) return launch_grad_t<R, GK_HOM>(a, logp_out, dv, score, L_total, lweight, s);
+    if (!a.has_sl && a.even) return launch_grad_t<R, GK_EVEN>(a, logp_out, dv, score, L_total, lweight, s);
+    return launch_grad_t<R, GK_ANY>(a, logp_out, dv, score, L_total, lweight, s);
+}
+
+hipError_t launch_grad(const KArgs& a, double* logp_out, void* dv, double* score, int L_total, int lweight,
+                       hipStream_t s) {
+    if (a.prec == RJPATH_F64) return launch_grad_k<double>(a, logp_out, dv, score, L_total, lweight, s);
+    return launch_grad_k<float>(a, logp_out, dv, score, L_total, lweight, s);
 }
 
 } // namespace rj

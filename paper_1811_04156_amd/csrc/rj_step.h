@@ -214,6 +214,25 @@ __device__ __forceinline__ double full_logp(const Tgt<R>& T, const P& ps, int n,
     return lp;
 }
 
+// The factors of log p that belong to segment k of a path of n vertices (the
+// segment, the emission at k = 0, the turn or the end at vertex k + 1), as
+// full_logp forms them; -inf for a segment without length.
+template <class R>
+__device__ __forceinline__ double walk_term(const Tgt<R>& T, int n, int k, V3<R> f0, V3<R> f1, V3<R> f2, R& tb) {
+    const LPt<R> l0 = lpt(T, f0), l1 = lpt(T, f1);
+    const Seg<R> s = make_seg_lp(T, f0, f1, l0, l1);
+    tb = s.tb;
+    double t = (double)seg_term(s);
+    if (k == 0) t += (double)emit_term(T, s.u);
+    if (k <= n - 3) {
+        const LayV<R> ly = lay_at(T, l1.l);
+        t += (double)(ly.logb + turn_term(ly, s.u, unit_dir(f1, f2)));
+    } else {
+        t += (double)end_term(T, s.u, f1);
+    }
+    return s.len > (R)0 ? t : -__builtin_inf();
+}
+
 // q(s) of the bi-spherical proposal with concentration beta, in the two
 // forms the jump needs: E = e^{-2 beta}, the normaliser
 // log((1 - E) / beta) = log(2 sinh(beta) / beta) - beta, and the inverse CDF
@@ -1114,16 +1133,8 @@ template <class R, int MK, int SAMP, bool SL, bool EVEN> __device__ __forceinlin
     MedTab<R> tab = hbm_tab<R>(a);
     size_t tab_bytes = 0;
     if (TAB) {
-        // layer table, then edges, then prefix integrals, each 16-byte aligned
-        const size_t nl = (size_t)a.L_total * LY_NW, ne = (size_t)a.n_edges;
-        R* lay = (R*)smem;
-        double* edge = (double*)(smem + ((nl * sizeof(R) + 15) & ~(size_t)15));
-        double* pre = edge + ((ne + 1) & ~(size_t)1);
-        for (size_t i = tid; i < nl; i += bs) lay[i] = ((const R*)a.lay)[i];
-        for (size_t i = tid; i < ne; i += bs) edge[i] = a.edge[i];
-        for (size_t i = tid; i < 2 * ne; i += bs) pre[i] = a.pre[i];
+        tab = stage_tables<R>(a, smem);
         __syncthreads();
-        tab = MedTab<R>{lay, edge, pre};
         tab_bytes = a.tab_bytes;
     }
     const size_t C = (size_t)a.C;

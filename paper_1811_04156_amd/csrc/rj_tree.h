@@ -2,6 +2,8 @@
 // rj_step.h, whose path storage and density factors it uses).
 #pragma once
 
+#include "rj_wave.h"
+
 namespace rj {
 
 // ---------------------------------------------------------------------------
@@ -145,57 +147,6 @@ template <class R, bool Y> struct LanePath {
     }
 };
 
-// Inclusive prefix sum over the 64 lanes by data-parallel moves (no LDS).
-__device__ __forceinline__ int wave_prefix(int v) {
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true); // row_shr:1
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true); // row_shr:2
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true); // row_shr:4
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true); // row_shr:8
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false); // row_bcast:15 into rows 1 and 3
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false); // row_bcast:31 into rows 2 and 3
-    return v;
-}
-
-// Items of the wave's chains in chain order, 64 at a time: `first` is the
-// chain's first item and `cnt` its count (0: none) in its own lane.  next()
-// gives each lane its item's chain and the item's place in it; the starts in
-// the window are one bit mask, whose bits below a lane count the chains.
-struct WaveItems {
-    int lane, first, base, total, seen, nth;
-    bool has;
-    __device__ __forceinline__ void init(int lane_, int cnt) {
-        lane = lane_;
-        has = cnt > 0;
-        const int end = wave_prefix(cnt);
-        total = __builtin_amdgcn_readlane(end, WAVE - 1);
-        first = end - cnt;
-        const uint64_t m = __ballot(has);
-        const int n = __popcll(m);
-        const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-        nth = __builtin_amdgcn_ds_permute(4 * (has ? rank : n + lane - rank), lane); // lane r: the r-th chain's lane
-        base = 0;
-        seen = 0;
-    }
-    __device__ __forceinline__ bool more() const { return base < total; }
-    // the window's items: true if this lane has one; q: its chain's lane, k: its place
-    __device__ __forceinline__ bool next(int& q, int& k) {
-        const int s = first - base;
-        const bool in = has && s >= 0 && s < WAVE;
-        const uint64_t bit = in ? 1ull << s : 0ull;
-        // the starts are distinct, so their sum is their union
-        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane(wave_prefix((int)(uint32_t)bit), WAVE - 1);
-        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane(wave_prefix((int)(uint32_t)(bit >> 32)), WAVE - 1);
-        const int upto = (int)__builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u)) +
-                         (int)(((lane < 32 ? lo : hi) >> (lane & 31)) & 1u);
-        q = __shfl(nth, (seen + upto - 1) & (WAVE - 1), WAVE);
-        k = base + lane - __shfl(first, q, WAVE);
-        const bool mine = base + lane < total;
-        seen += __popc(lo) + __popc(hi);
-        base += WAVE;
-        return mine;
-    }
-};
-
 // frame (e2, e3) of interval (k, l) of a path: root -> onb of the axis;
 // otherwise from the parent interval (kp, lp) and its vertex fp.  Both are
 // formed and one is selected by value (a choice between output references
@@ -288,25 +239,6 @@ __device__ __forceinline__ void tree_node(const WaveChain<R>& c, const StepCtx& 
     lj += (double)((R)3 * Mth<R>::log(gy) + (R)2 * Mth<R>::log(sh) - (R)3 * Mth<R>::log(deny));
     c.W.sty(c.at + m, Vtx<R>{ym.x, ym.y, ym.z, (R)0});
     c.W.add(c.q, lj);
-}
-
-// The factors of log p that belong to segment k of a path of n vertices (the
-// segment, the emission at k = 0, the turn or the end at vertex k + 1), as
-// full_logp forms them; -inf for a segment without length.
-template <class R>
-__device__ __forceinline__ double walk_term(const Tgt<R>& T, int n, int k, V3<R> f0, V3<R> f1, V3<R> f2, R& tb) {
-    const LPt<R> l0 = lpt(T, f0), l1 = lpt(T, f1);
-    const Seg<R> s = make_seg_lp(T, f0, f1, l0, l1);
-    tb = s.tb;
-    double t = (double)seg_term(s);
-    if (k == 0) t += (double)emit_term(T, s.u);
-    if (k <= n - 3) {
-        const LayV<R> ly = lay_at(T, l1.l);
-        t += (double)(ly.logb + turn_term(ly, s.u, unit_dir(f1, f2)));
-    } else {
-        t += (double)end_term(T, s.u, f1);
-    }
-    return s.len > (R)0 ? t : -__builtin_inf();
 }
 
 // The move of every chain of the wave (all 64 lanes call it together).
