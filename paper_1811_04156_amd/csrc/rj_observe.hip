@@ -141,28 +141,6 @@ template <class R> __device__ __forceinline__ D3 vload(const Vtx<R>* base, size_
     return {(double)x.x, (double)x.y, (double)x.z};
 }
 
-// The chain's path seen through T (dir 0) or T^-1 (dir 1), vertex by vertex.
-template <class R> struct MappedPath {
-    const Vtx<R>* glb;
-    size_t C;
-    int n, dir;
-    const YMap* M;
-    __device__ __forceinline__ V3<R> p(int v) const {
-        const D3 f = vload(glb, C, v);
-        D3 g;
-        double rad;
-        bool in;
-        if (v == 0)
-            g = f;
-        else if (v == n - 1)
-            g = dir == 0 ? yend_fwd(*M, f) : yend_inv(*M, f);
-        else
-            g = dir == 0 ? yfwd(*M, f, rad, in) : yinv(*M, f, rad);
-        return {(R)g.x, (R)g.y, (R)g.z};
-    }
-    __device__ __forceinline__ void stw(int, R) const {}
-};
-
 // Block-level accumulation of (key, group, slot) sums: an LDS table when the
 // block's keys span at most two values, else one atomic per lane.
 struct BlockSums {
@@ -199,71 +177,156 @@ __device__ __forceinline__ void block_sums_end(const BlockSums& b, double* out, 
 // log r = log p_t1(T x) + log|dT/dx| - log p_t0(x) (-inf outside T's domain);
 // a chain of t1 (path y) takes log r = log p_t0(T^-1 y) - log p_t1(y) - log|dT/dx|
 // at x = T^-1 y.  acc[((k * 2 + side) * groups + g) * 2 + {0, 1}] += {sqrt(r), 1} / w(n).
+//
+// Work split.  A wave owns `cpw` chains (64, or fewer where the chains would
+// leave SIMDs without a wave) and shares their vertices over its lanes: a lane
+// maps one vertex and takes the next two, of the path and of its image, from
+// the lanes beside it (windows of 62), so that the map's FP64 sine, cosine or
+// arc tangent is formed once per vertex and no lane waits for the longest
+// path.  One lane per chain, mapping every vertex twice, took 545 us for the
+// two-region test's 65,536 chains of 32 vertices; now about 150 us.
 // ---------------------------------------------------------------------------
+template <class R> __device__ __forceinline__ V3<R> lane_v3(V3<R> p, int from) {
+    return {__shfl(p.x, from, WAVE), __shfl(p.y, from, WAVE), __shfl(p.z, from, WAVE)};
+}
+
 template <class R>
-__global__ void __launch_bounds__(BLK) yield_kernel(KArgs a, int n_pairs, const int32_t* pairs, const int32_t* role,
-                                                    int groups, double* acc, double* logr) {
+__global__ void __launch_bounds__(BLK, sizeof(R) == 4 ? 2 : 1) yield_kernel(KArgs a, int n_pairs, const int32_t* pairs, const int32_t* role,
+                                                    int groups, double* acc, double* logr, int cpw, int strip) {
+    extern __shared__ __align__(16) unsigned char smem[];
     __shared__ double tab[2 * 64 * 2];
+    __shared__ double own[BLK], img[BLK];
+    __shared__ int outside[BLK];
+    __shared__ YMap map[BLK / WAVE];
+    __shared__ Tgt<R> tgt[BLK / WAVE][2];
     __shared__ int smin[BLK / 64], smax[BLK / 64];
-    const int c = blockIdx.x * BLK + threadIdx.x;
-    int key = -1, tc = -1, to = -1, side = 0, n = 0;
-    if (c < a.C) {
+    const int lane = threadIdx.x % WAVE, wave = threadIdx.x / WAVE;
+    const int c0 = ((int)blockIdx.x * (BLK / WAVE) + wave) * cpw, c = c0 + lane;
+    const bool mine = lane < cpw && c < a.C;
+    int key = -1, tc = -1, to = -1, n = 0;
+    if (mine) {
         tc = a.target[c];
         n = a.n[c];
         if (tc >= 0 && tc < a.T && a.status[c] == 0 && n >= 2 && n <= a.cap) {
             const int r = role[tc];
             const int k = r >> 1;
             if (r >= 0 && k < n_pairs && pairs[r] == tc) {
-                side = r & 1;
-                to = pairs[2 * k + (side ^ 1)];
+                to = pairs[2 * k + ((r & 1) ^ 1)];
                 if (to >= 0 && to < a.T && to != tc && a.medium[to] == a.medium[tc] &&
                     a.medium[tc] >= 0 && a.medium[tc] < a.n_media && a.src[3 * to] == a.src[3 * tc] &&
                     a.src[3 * to + 1] == a.src[3 * tc + 1] && a.src[3 * to + 2] == a.src[3 * tc + 2])
                     key = r;
             }
         }
-        if (logr) logr[c] = __builtin_nan("");
     }
+    // log p of the path; log p of its image +- log |dT/dx|; left T's domain
+    double* const sown = own + wave * WAVE;
+    double* const simg = img + wave * WAVE;
+    int* const sout = outside + wave * WAVE;
+    sown[lane] = 0.0;
+    simg[lane] = 0.0;
+    sout[lane] = 0;
+    const int items = key >= 0 ? n : 0;
+    const int upto = wave_prefix(items), at = upto - items, total = __builtin_amdgcn_readlane(upto, WAVE - 1);
+    if (total > 0) {
+        // the vertices, read row by row into the wave's strip
+        const LdsPtr<R> lds = (LdsPtr<R>)((L4<R>*)smem + (size_t)wave * strip);
+        const Vtx<R>* const g = (const Vtx<R>*)a.verts + c0;
+        const size_t C = (size_t)a.C;
+        {
+            const int q = lane & (cpw - 1), rows = WAVE / cpw;
+            const int nq = __shfl(items, q, WAVE), aq = __shfl(at, q, WAVE);
+            for (int v = lane / cpw; __any(v < nq); v += 4 * rows) {
+                L4<R> x[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (v + i * rows < nq && aq + v + i * rows < strip)
+                        x[i] = *(const L4<R>*)(g + ((size_t)(v + i * rows) * C + q));
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (v + i * rows < nq && aq + v + i * rows < strip) lds[aq + v + i * rows] = x[i];
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        // target by target (one or two per wave where the chains of a target are
+        // neighbours); the map and the two targets are kept in LDS (together
+        // they would take 170 registers) and read where they are used
+        const YMap& M = map[wave];
+        uint64_t rest = __ballot(items > 0);
+        while (rest) {
+            const int from = __ffsll((unsigned long long)rest) - 1;
+            const int tq = __builtin_amdgcn_readlane(tc, from), oq = __builtin_amdgcn_readlane(to, from);
+            const int side = __builtin_amdgcn_readlane(key, from) & 1;
+            const bool in_target = items > 0 && tc == tq;
+            rest &= ~__ballot(in_target);
+#pragma unroll 1
+            for (int w = 0; w < 2; ++w) {
+                Tgt<R> T;
+                load_target(a, w == 0 ? tq : oq, T, hbm_tab<R>(a));
+                if (lane == 0) tgt[wave][w] = T;
+            }
+            {
+                const YMap m = ymap(a, side == 0 ? tq : oq, side == 0 ? oq : tq);
+                if (lane == 0) map[wave] = m;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+            WaveItems it;
+            it.init(lane, in_target ? n : 0);
+            while (it.more()) {
+                asm volatile("" ::: "memory"); // (what LDS holds is read again, not kept)
+                int q, k;
+                const bool has = it.next(q, k);
+                it.base -= 2; // (the last two lanes only lend their vertices)
+                it.seen -= it.starts_at_end(2);
+                const int aq = __shfl(at, q, WAVE), nq = __shfl(n, q, WAVE);
+                V3<R> f = {(R)0, (R)0, (R)0}, h = f;
+                double lj = 0.0;
+                bool in = true;
+                if (has) {
+                    f = aq + k < strip ? pos(lds_ld<R>(lds + aq + k)) : pos(g[(size_t)k * C + q]);
+                    const D3 x = {(double)f.x, (double)f.y, (double)f.z};
+                    D3 y = x;
+                    if (k == nq - 1) {
+                        y = side == 0 ? yend_fwd(M, x) : yend_inv(M, x);
+                    } else if (k > 0) {
+                        double rad;
+                        if (side == 0) y = yfwd(M, x, rad, in);
+                        else y = yinv(M, x, rad);
+                        lj = log(rad);
+                    }
+                    if (k == 0) lj = M.le + (nq - 2) * M.lc;
+                    h = {(R)y.x, (R)y.y, (R)y.z};
+                }
+                // the image's walk, then the path's
+                double term = side == 0 ? lj : -lj;
+                V3<R> e = h;
+#pragma unroll 1
+                for (int w = 1; w >= 0; --w) {
+                    const V3<R> e1 = lane_v3(e, lane + 1), e2 = lane_v3(e, lane + 2);
+                    if (has && lane < WAVE - 2) {
+                        if (k < nq - 1) {
+                            const Tgt<R> T = tgt[wave][w];
+                            R tb;
+                            term += walk_term(T, nq, k, e, e1, e2, tb);
+                        }
+                        if (w == 0 && !M.ok) term = __builtin_nan("");
+                        atomicAdd((w == 0 ? sown : simg) + q, term);
+                        if (!in) sout[q] = 1;
+                    }
+                    term = 0.0;
+                    e = f;
+                }
+            }
+        }
+    }
+    __syncthreads();
     double lr = __builtin_nan("");
     if (key >= 0) {
-        const int t0 = side == 0 ? tc : to, t1 = side == 0 ? to : tc;
-        const YMap M = ymap(a, t0, t1);
-        if (M.ok) {
-            const Vtx<R>* base = (const Vtx<R>*)a.verts + c;
-            const size_t C = (size_t)a.C;
-            // log |dT/dx| and the domain of T (side 0)
-            double lj = M.le + (n - 2) * M.lc;
-            bool in = true;
-            for (int v = 1; v + 1 < n; ++v) {
-                double rad;
-                bool inv = true;
-                if (side == 0)
-                    yfwd(M, vload(base, C, v), rad, inv);
-                else
-                    yinv(M, vload(base, C, v), rad);
-                in = in && inv;
-                lj += log(rad);
-            }
-            Tgt<R> T0, T1;
-            load_target(a, t0, T0, hbm_tab<R>(a));
-            load_target(a, t1, T1, hbm_tab<R>(a));
-            double L;
-            const GlobalPath<R> own{(Vtx<R>*)base, C};
-            const MappedPath<R> img{base, C, n, side, &M};
-            if (side == 0) {
-                const double lp0 = full_logp(T0, own, n, L);
-                lr = in ? full_logp(T1, img, n, L) + lj - lp0 : -__builtin_inf();
-            } else {
-                const double lp1 = full_logp(T1, own, n, L);
-                lr = full_logp(T0, img, n, L) - lp1 - lj;
-            }
-            if (lr != lr || lr == __builtin_inf()) key = -1; // a non-finite own density: not a sample
-        } else {
-            key = -1;
-        }
-        if (logr && c < a.C) logr[c] = lr;
+        lr = sout[lane] && sown[lane] == sown[lane] ? -__builtin_inf() : simg[lane] - sown[lane];
+        if (lr != lr || lr == __builtin_inf()) key = -1; // a non-finite own density, or no map: not a sample
     }
-    const int g = (int)(group_hash((uint32_t)c) % (uint32_t)groups);
+    if (mine && logr) logr[c] = lr;
+    const int gr = (int)(group_hash((uint32_t)c) % (uint32_t)groups);
     const int nent = groups * 2;
     BlockSums b = block_sums_begin(key, tab, nent, smin, smax);
     if (key >= 0) {
@@ -271,8 +334,8 @@ __global__ void __launch_bounds__(BLK) yield_kernel(KArgs a, int n_pairs, const 
         const double iw = lw ? exp(-lw[n]) : 1.0;
         const double s = lr == -__builtin_inf() ? 0.0 : exp(0.5 * lr);
         double* dst = b.local ? tab + (size_t)(key - b.kmin) * nent : acc + (size_t)key * nent;
-        atomicAdd(dst + 2 * g, iw * s);
-        atomicAdd(dst + 2 * g + 1, iw);
+        atomicAdd(dst + 2 * gr, iw * s);
+        atomicAdd(dst + 2 * gr + 1, iw);
     }
     block_sums_end(b, acc, nent, 2 * n_pairs);
 }
@@ -296,13 +359,21 @@ __global__ void __launch_bounds__(BLK) lhist_kernel(KArgs a, int bins, double l0
     }
     double L = 0;
     if (t >= 0) {
+        // four rows in flight (one at a time, each step waited for its row)
         const Vtx<R>* base = (const Vtx<R>*)a.verts + c;
         D3 p = vload(base, (size_t)a.C, 0);
-        for (int v = 1; v < n; ++v) {
-            const D3 q = vload(base, (size_t)a.C, v);
-            const D3 d = q - p;
-            L += sqrt(dot(d, d));
-            p = q;
+        for (int v = 1; v < n; v += 4) {
+            D3 q[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (v + i < n) q[i] = vload(base, (size_t)a.C, v + i);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (v + i < n) {
+                    const D3 d = q[i] - p;
+                    L += sqrt(dot(d, d));
+                    p = q[i];
+                }
         }
     }
     const int nent = bins + 1;
@@ -320,16 +391,32 @@ __global__ void __launch_bounds__(BLK) lhist_kernel(KArgs a, int bins, double l0
 
 } // namespace
 
+// Compute units of the current device.
+static int compute_units() {
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 256;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return 256;
+    return cus;
+}
+
+template <class R>
+static hipError_t launch_yield_t(const KArgs& a, int n_pairs, const int32_t* pairs, const int32_t* role, int groups,
+                                 double* acc, double* logr, hipStream_t s) {
+    // chains per wave: 64 from two waves per SIMD on, fewer below, down to 8;
+    // a strip of 8 KiB per wave, so that two waves per SIMD fit
+    int cpw = WAVE;
+    while (cpw > 8 && (long long)a.C < 8LL * compute_units() * cpw) cpw /= 2;
+    const int strip = 8 * 1024 / (int)sizeof(Vtx<R>);
+    const int chains = BLK / WAVE * cpw, grid = (a.C + chains - 1) / chains;
+    hipLaunchKernelGGL(yield_kernel<R>, dim3(grid), dim3(BLK), (size_t)(BLK / WAVE) * 8 * 1024, s, a, n_pairs, pairs, role,
+                       groups, acc, logr, cpw, strip);
+    return hipGetLastError();
+}
+
 hipError_t launch_yield(const KArgs& a, int n_pairs, const int32_t* pairs, const int32_t* role, int groups,
                         double* acc, double* logr, hipStream_t s) {
-    const int grid = (a.C + BLK - 1) / BLK;
-    if (a.prec == RJPATH_F64)
-        hipLaunchKernelGGL(yield_kernel<double>, dim3(grid), dim3(BLK), 0, s, a, n_pairs, pairs, role, groups, acc,
-                           logr);
-    else
-        hipLaunchKernelGGL(yield_kernel<float>, dim3(grid), dim3(BLK), 0, s, a, n_pairs, pairs, role, groups, acc,
-                           logr);
-    return hipGetLastError();
+    if (a.prec == RJPATH_F64) return launch_yield_t<double>(a, n_pairs, pairs, role, groups, acc, logr, s);
+    return launch_yield_t<float>(a, n_pairs, pairs, role, groups, acc, logr, s);
 }
 
 hipError_t launch_lhist(const KArgs& a, int bins, double l0, double width, double* hist, hipStream_t s) {

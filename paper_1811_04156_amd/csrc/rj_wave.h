@@ -55,6 +55,7 @@ __device__ __forceinline__ int wave_prefix(int v) {
 // the window are one bit mask, whose bits below a lane count the chains.
 struct WaveItems {
     int lane, first, base, total, seen, nth;
+    uint64_t mask; // the window's starts
     bool has;
     __device__ __forceinline__ void init(int lane_, int cnt) {
         lane = lane_;
@@ -70,6 +71,9 @@ struct WaveItems {
         seen = 0;
     }
     __device__ __forceinline__ bool more() const { return base < total; }
+    // Starts among the last `m` lanes of the window just given: next() after
+    // base -= m gives those lanes' items again.
+    __device__ __forceinline__ int starts_at_end(int m) const { return __popcll(mask >> (64 - m)); }
     // the window's items: true if this lane has one; q: its chain's lane, k: its place
     __device__ __forceinline__ bool next(int& q, int& k) {
         const int s = first - base;
@@ -83,7 +87,8 @@ struct WaveItems {
         q = __shfl(nth, (seen + upto - 1) & (63), 64);
         k = base + lane - __shfl(first, q, 64);
         const bool mine = base + lane < total;
-        seen += __popc(lo) + __popc(hi);
+        mask = (uint64_t)hi << 32 | lo;
+        seen += __popcll(mask);
         base += 64;
         return mine;
     }

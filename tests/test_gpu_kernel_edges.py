@@ -205,3 +205,40 @@ def test_tree_moves_shared_by_any_number_of_chains(rj):
     assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
     assert np.allclose(a[2], b[2], rtol=1e-12)
     assert a[2][:, 14].sum() > 1000  # tree moves were accepted
+
+
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+def test_bridge_whatever_the_order_and_number_of_chains(rj, prec):
+    """The bridge's waves share the vertices of 8 chains in a small launch and
+    of 64 in a large one, target by target: the same paths grouped by target,
+    dealt out over the targets, and repeated to 131,200 chains give the same
+    log r per chain (sums of about 60 FP64 terms of magnitude up to 1e2 in
+    another order: 1e-11)."""
+    from paper_1811_04156_amd.table1 import replicate
+    w = replicate(W.two_region(b1=0.3, scale=0.1, chains_per_sensor=1, cap=64), 3, 55)
+    w.update(burn_in=0, sampler=3, mala_h=0.3)
+    s = rj.Sampler(w, precision=prec)
+    s.run(400)
+    torch.cuda.synchronize()
+    n, v = s.get_state()
+    C = len(n)
+    out = []
+    orders = [np.arange(C), np.argsort(np.arange(C) % 41, kind="stable")]
+    if prec == "f32":
+        orders.append(np.tile(np.arange(C), 131_200 // C + 1))
+    for order in orders:
+        wp = dict(w)
+        wp["c_target"] = w["c_target"][order]
+        p = rj.Sampler(wp, precision=prec)
+        p.set_state(n[order], v[order][:, : n.max()])
+        acc, lr = p.yield_accumulate(p.yield_pairs([(0, 1), (2, 3), (4, 5)]), groups=4, logr=True)
+        lr = lr.cpu().numpy()
+        assert acc[..., 1].sum().item() == np.sum(np.isfinite(lr) | np.isneginf(lr))
+        first = np.zeros(C)
+        first[order[:C]] = lr[:C]
+        out.append(first)
+        if len(order) > C:
+            assert np.allclose(lr, first[order], rtol=1e-11, atol=1e-11, equal_nan=True)
+    for x in out[1:]:
+        assert np.allclose(out[0], x, rtol=1e-11, atol=1e-11, equal_nan=True)
+    assert np.isfinite(out[0]).sum() > C // 2
