@@ -318,13 +318,21 @@ int device_cus() {
     return cus;
 }
 
-// Chains per wave of the tree sampler: 64 from two waves per SIMD on; below
-// that fewer, down to 8, so that the shared whole-path moves of the same chains
-// use more of the chip.
-int tree_cpw(int n_chains) {
-    const long long two_waves = 2LL * 4 * device_cus();
-    int cpw = 64;
-    while (cpw > 8 && (long long)n_chains < two_waves * cpw) cpw /= 2;
+// Chains per wave of the samplers whose waves share whole-path moves: as few
+// (from 64 down to 8) as keep the launch within so many waves per SIMD, so that
+// the shared moves use more of the chip.  Two are resident.  Tree moves: two
+// (the jumps and perturbations cost by the wave: the 65,536-chain two-region
+// test, 500 steps, takes 132 us per step with 32 chains per wave and 142 with
+// 16).  Joint Langevin moves: four, since most of the run is shared items and
+// a few waves of far targets outlast the rest (50,001 chains of the ragged
+// batch: 26.4 us per step within two, 21.7 within four, 26.2 within eight;
+// 100,000 chains 45.5, 32.7 and 33.6; 20,000 chains 14.8 in each).
+bool shares_moves(int sampler) { return sampler == RJPATH_TREE || sampler == RJPATH_MALA; }
+
+int shared_cpw(int sampler, int n_chains) {
+    const long long waves = (sampler == RJPATH_MALA ? 4LL : 2LL) * 4 * device_cus();
+    int cpw = 8;
+    while (cpw < 64 && (long long)n_chains > waves * cpw) cpw *= 2;
     return cpw;
 }
 
@@ -342,15 +350,15 @@ int tree_cpw(int n_chains) {
 //  - otherwise (FP32): 256-chain blocks with as many slots as let two blocks
 //    (eight waves) share a CU's LDS, so that two waves are resident per SIMD
 //    (the step kernel's register use allows two).
-//  - the tree sampler: the same with its waves counted (tree_cpw chains each).
-//    (Halving the slots so that the proposals of 64-chain waves fit LDS too
+//  - the whole-path samplers: the same with their waves counted (shared_cpw
+//    chains each).  (Halving the slots so that the proposals of 64-chain waves fit LDS too
 //    made the tree step itself no faster, 122 against 113 us for 262,144 chains
 //    of the ragged batch, and the jumps slower.)
 void default_launch(const rjpath_chains* c, size_t tab_bytes, int sampler, int& block, int& V) {
     const int cap = c->cap;
     const int cus = device_cus();
-    const bool tree = sampler == RJPATH_TREE;
-    const int cpw = tree ? tree_cpw(c->n_chains) : 64;
+    const bool shared = shares_moves(sampler);
+    const int cpw = shared ? shared_cpw(sampler, c->n_chains) : 64;
     block = 64;
     V = std::min(cap, c->precision == RJPATH_F64 ? 16 : 32);
     const long long blocks = ((long long)c->n_chains + cpw - 1) / cpw;
@@ -360,7 +368,7 @@ void default_launch(const rjpath_chains* c, size_t tab_bytes, int sampler, int& 
         const long long fit = (long long)((share - tab_bytes) / (64 * vtx_bytes(c->precision))) - 2;
         if (fit >= 8) V = (int)std::min<long long>(V, fit);
     }
-    if (c->precision == RJPATH_F32 && (tree ? blocks > 4LL * cus : (long long)c->n_chains >= 2LL * 4 * cus * 64)) {
+    if (c->precision == RJPATH_F32 && (shared ? blocks > 4LL * cus : (long long)c->n_chains >= 2LL * 4 * cus * 64)) {
         const size_t per_block = LDS_MAX / 2;
         if (per_block > tab_bytes) {
             const long long slots = (long long)((per_block - tab_bytes) / (256 * vtx_bytes(RJPATH_F32))) - 2;
@@ -389,8 +397,8 @@ int run_impl(rjpath_medium* m, const rjpath_targets* t, const rjpath_chains* c, 
     a.trace_steps = p->steps;
     a.hist = p->hist;
     a.step_dev = p->step_counter;
-    if (p->sampler == RJPATH_TREE) {
-        a.cpw = tree_cpw(c->n_chains);
+    if (shares_moves(p->sampler)) {
+        a.cpw = shared_cpw(p->sampler, c->n_chains);
         if (a.cpw == 64) {
             // LDS slots for the proposals: what the blocks that fit a CU leave
             const size_t per = (size_t)block * vtx_bytes(c->precision), x = a.tab_bytes + (size_t)(V + 2) * per;

@@ -9,11 +9,12 @@ namespace rj {
 
 template <class R, int MK, int SAMP, bool SL, bool EVEN>
 static hipError_t launch_run_t(const KArgs& a, int block, hipStream_t s) {
-    const int chains = SAMP == SAMP_TREE ? block / WAVE * a.cpw : block;
+    constexpr bool SHARED = SAMP == SAMP_TREE || SAMP == SAMP_JOINT;
+    const int chains = SHARED ? block / WAVE * a.cpw : block;
     int grid = (a.C + chains - 1) / chains;
-    // media tables, then one tile of V + SLOT_PAD slots per wave, then the tree sampler's proposals
+    // media tables, then one tile of V + SLOT_PAD slots per wave, then the whole-path samplers' proposals
     size_t lds = (MK == MK_LAY_LDS ? a.tab_bytes : 0) + (size_t)(a.V + SLOT_PAD) * block * sizeof(Vtx<R>);
-    if (SAMP == SAMP_TREE && a.cpw == WAVE) lds += (size_t)a.Vy * block * sizeof(Vtx<R>);
+    if (SHARED && a.cpw == WAVE) lds += (size_t)a.Vy * block * sizeof(Vtx<R>);
     if constexpr (EVEN)
         hipLaunchKernelGGL((run_even_layers_kernel<R, MK, SAMP, SL>), dim3(grid), dim3(block), lds, s, a);
     else

@@ -117,70 +117,6 @@ template <class R> struct WaveStrip {
     }
 };
 
-// log p's factors of segment k of a path of n vertices and the gradient of its
-// vertex j = k + 1, with the terms in the order in which score_stream adds
-// them; p(v) reads vertex v.
-template <class R, class P>
-__device__ __forceinline__ double segment_grad(const Tgt<R>& T, int n, int k, P p, V3<R>& grad) {
-    const int j = k + 1;
-    const V3<R> f0 = p(k), f1 = p(j);
-    const LPt<R> p0 = lpt(T, f0), p1 = lpt(T, f1);
-    const Seg<R> A = make_seg_lp(T, f0, f1, p0, p1);
-    double t = (double)seg_term(A);
-    V3<R> dP, dQ;
-    seg_depth_grad_lp(T, p0, p1, A, dP, dQ);
-    const R ilA = (R)2 * Mth<R>::rcp(A.len);
-    const V3<R> z = {(R)0, (R)0, (R)0};
-    V3<R> g = z - dQ - ilA * A.u;
-    if (k == 0) {
-        t += (double)emit_term(T, A.u);
-        if (T.ek == RJPATH_EMIT_VMF) g = g + T.kappa * dunit(A.u, A.len, T.ed);
-    } else {
-        const V3<R> um = unit_dir(p(k - 1), f0), dd = um - A.u;
-        const R h = dturn_dmu(lay_at(T, p0.l), dot(dd, dd));
-        g = g + h * dunit(A.u, A.len, um);
-    }
-    if (j < n - 1) {
-        const V3<R> f2 = p(j + 1);
-        const LPt<R> p2 = lpt(T, f2);
-        const Seg<R> B = make_seg_lp(T, f1, f2, p1, p2);
-        seg_depth_grad_lp(T, p1, p2, B, dP, dQ);
-        const R ilB = (R)2 * Mth<R>::rcp(B.len);
-        g = g - dP + ilB * B.u;
-        const LayV<R> ly = lay_at(T, p1.l);
-        t += (double)(ly.logb + turn_term(ly, A.u, B.u));
-        {
-            const V3<R> dd = A.u - B.u;
-            const R h = dturn_dmu(ly, dot(dd, dd));
-            g = g + h * dunit(A.u, A.len, B.u) - h * dunit(B.u, B.len, A.u);
-        }
-        if (j < n - 2) {
-            const V3<R> uc = unit_dir(f2, p(j + 2)), dd = B.u - uc;
-            const R h = dturn_dmu(lay_at(T, p2.l), dot(dd, dd));
-            g = g - h * dunit(B.u, B.len, uc);
-        } else {
-            const V3<R> nu = unit_dir_eta(T, f2);
-            const R ic = Mth<R>::rcp(-dot(B.u, nu));
-            g = g - ic * ((R)-1 * dunit(B.u, B.len, nu));
-        }
-    } else {
-        t += (double)end_term(T, A.u, f1);
-        const V3<R> d = from_eta(T, f1);
-        const R dn2 = dot(d, d), idn = Mth<R>::rsqrt(dn2);
-        const V3<R> nu = idn * d;
-        const R ic = Mth<R>::rcp(-dot(A.u, nu));
-        const V3<R> dcr = (R)-1 * dunit(A.u, A.len, nu), dcd = (R)-1 * dunit(nu, dn2 * idn, A.u);
-        g = g + ic * dcr + ic * dcd;
-        if (T.dk == RJPATH_DET_PAPER) {
-            const R cr = dot(nu, T.dd);
-            const R th = tanh((R)2 * cr + (R)0.7);
-            g = g + ((R)3 - (R)2 * th) * dunit(nu, dn2 * idn, T.dd);
-        }
-    }
-    grad = g;
-    return A.len > (R)0 ? t : -__builtin_inf();
-}
-
 // LDS of a block: the media tables (tab_bytes, 0: read from HBM), the waves'
 // strips (`strip` vertices each), per wave and chain log p and (lweight) the
 // path length, the score table (lds_rows rows).
@@ -274,7 +210,10 @@ __global__ void __launch_bounds__(256, sizeof(R) == 4 ? 3 : 1) grad_kernel(KArgs
                 double f;
                 if constexpr (DV) {
                     V3<R> g;
-                    f = segment_grad(T, nq, k, p, g);
+                    const V3<R> f5[5] = {p(k > 0 ? k - 1 : 0), p(k), p(k + 1), p(k + 2 < nq ? k + 2 : k + 1),
+                                         p(k + 3 < nq ? k + 3 : k + 1)};
+                    Seg<R> A;
+                    f = segment_grad(T, nq, k, f5, g, A);
                     dv[(size_t)(k + 1) * C + c0 + q] = Vtx<R>{g.x, g.y, g.z, (R)0};
                 } else {
                     R tb;

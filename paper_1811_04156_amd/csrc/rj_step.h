@@ -278,11 +278,6 @@ __device__ __forceinline__ void box_muller3(uint32_t a, uint32_t b, uint32_t c, 
     xi = {rho1 * Mth<R>::cos2pi(u1), rho1 * Mth<R>::sin2pi(u1), rho2 * Mth<R>::cos2pi(u3)};
 }
 
-// ---------------------------------------------------------------------------
-// Score of the path: log p and d log p / d vertex, streamed along the path
-// with a three-vertex register window.  emit(k, g) receives the finished
-// gradient of vertex k (k = 0 .. n-1, in increasing order).
-// ---------------------------------------------------------------------------
 // d tau_c / d P and d tau_c / d Q of a segment with the endpoints' layer
 // points known: the mean coefficient along the segment, plus the change of
 // the layers' shares where it crosses edges.
@@ -364,111 +359,69 @@ __device__ __forceinline__ V3<R> vertex_grad(const Tgt<R>& T, int km1, const Lay
     return g;
 }
 
-// The streaming score as a walker fed one vertex at a time, so that two
-// walks (the current path and a proposal generated from the first walk's
-// gradients) can advance in one loop.  step(f_k) consumes vertex k >= 1 and
-// returns true with the finished gradient of vertex k-2 when k >= 2;
-// finish() adds the end term and returns log p, with the gradients of
-// vertices n-2 and n-1.
-template <class R> struct ScoreWalker {
-    V3<R> gA, gB; // gradients of vertices k-2, k-1 in progress
-    V3<R> fprev;
-    V3<R> uprev; // direction and length of the previous segment
-    R lprev;
-    double lp;
-    bool zero;
-    int k; // next vertex to consume
-
-    __device__ __forceinline__ void init(const Tgt<R>& T, V3<R> f0) {
-        const V3<R> z = {(R)0, (R)0, (R)0};
-        gA = z;
-        gB = z;
-        fprev = f0;
-        uprev = z;
-        lprev = (R)0;
-        lp = 0.0;
-        zero = false;
-        k = 1;
+// log p's factors of segment k of a path of n vertices and the gradient of its
+// vertex j = k + 1, with the terms in path order
+// f: vertices k - 1 .. k + 3 (any value where the path has none), A: the
+// segment.
+template <class R>
+__device__ __forceinline__ double segment_grad(const Tgt<R>& T, int n, int k, const V3<R> (&f)[5], V3<R>& grad, Seg<R>& A) {
+    const int j = k + 1;
+    const V3<R> f0 = f[1], f1 = f[2];
+    const LPt<R> p0 = lpt(T, f0), p1 = lpt(T, f1);
+    A = make_seg_lp(T, f0, f1, p0, p1);
+    double t = (double)seg_term(A);
+    V3<R> dP, dQ;
+    seg_depth_grad_lp(T, p0, p1, A, dP, dQ);
+    const R ilA = (R)2 * Mth<R>::rcp(A.len);
+    const V3<R> z = {(R)0, (R)0, (R)0};
+    V3<R> g = z - dQ - ilA * A.u;
+    if (k == 0) {
+        t += (double)emit_term(T, A.u);
+        if (T.ek == RJPATH_EMIT_VMF) g = g + T.kappa * dunit(A.u, A.len, T.ed);
+    } else {
+        const V3<R> um = unit_dir(f[0], f0), dd = um - A.u;
+        const R h = dturn_dmu(lay_at(T, p0.l), dot(dd, dd));
+        g = g + h * dunit(A.u, A.len, um);
     }
-
-    __device__ __forceinline__ bool step(const Tgt<R>& T, V3<R> fcur, V3<R>& gout) {
-        // (the layer point of fprev is looked up again rather than kept: two
-        // walks advance together and their registers are scarce)
-        const LPt<R> pprev = lpt(T, fprev), pcur = lpt(T, fcur);
-        Seg<R> s = make_seg_lp(T, fprev, fcur, pprev, pcur);
-        zero |= !(s.len > (R)0);
-        lp += (double)seg_term(s);
-        V3<R> dP, dQ;
-        seg_depth_grad_lp(T, pprev, pcur, s, dP, dQ);
-        R il2 = (R)2 * Mth<R>::rcp(s.len);
-        gB = gB - dP + il2 * s.u;
-        const V3<R> z = {(R)0, (R)0, (R)0};
-        V3<R> gC = z - dQ - il2 * s.u; // vertex k
-        if (k == 1) {
-            lp += (double)emit_term(T, s.u);
-            if (T.ek == RJPATH_EMIT_VMF) {
-                V3<R> d = T.kappa * dunit(s.u, s.len, T.ed);
-                gC = gC + d;
-                gB = gB - d;
-            }
+    if (j < n - 1) {
+        const V3<R> f2 = f[3];
+        const LPt<R> p2 = lpt(T, f2);
+        const Seg<R> B = make_seg_lp(T, f1, f2, p1, p2);
+        seg_depth_grad_lp(T, p1, p2, B, dP, dQ);
+        const R ilB = (R)2 * Mth<R>::rcp(B.len);
+        g = g - dP + ilB * B.u;
+        const LayV<R> ly = lay_at(T, p1.l);
+        t += (double)(ly.logb + turn_term(ly, A.u, B.u));
+        {
+            const V3<R> dd = A.u - B.u;
+            const R h = dturn_dmu(ly, dot(dd, dd));
+            g = g + h * dunit(A.u, A.len, B.u) - h * dunit(B.u, B.len, A.u);
+        }
+        if (j < n - 2) {
+            const V3<R> uc = unit_dir(f2, f[4]), dd = B.u - uc;
+            const R h = dturn_dmu(lay_at(T, p2.l), dot(dd, dd));
+            g = g - h * dunit(B.u, B.len, uc);
         } else {
-            // turn (and scattering density) at vertex k-1 between sprev and s
-            const LayV<R> ly = lay_at(T, pprev.l);
-            V3<R> dd = uprev - s.u;
-            lp += (double)(ly.logb + turn_term(ly, uprev, s.u));
-            R h = dturn_dmu(ly, dot(dd, dd));
-            V3<R> da = dunit(uprev, lprev, s.u);
-            V3<R> db = dunit(s.u, s.len, uprev);
-            gA = gA - h * da;
-            gB = gB + h * da - h * db;
-            gC = gC + h * db;
+            const V3<R> nu = unit_dir_eta(T, f2);
+            const R ic = Mth<R>::rcp(-dot(B.u, nu));
+            g = g - ic * ((R)-1 * dunit(B.u, B.len, nu));
         }
-        const bool done = k >= 2;
-        gout = gA;
-        gA = gB;
-        gB = gC;
-        uprev = s.u;
-        lprev = s.len;
-        fprev = fcur;
-        ++k;
-        return done;
-    }
-
-    __device__ __forceinline__ double finish(const Tgt<R>& T, V3<R>& g_nm2, V3<R>& g_nm1) {
-        // end term on segment n-2 and the end point (gA = vertex n-2, gB = vertex n-1)
-        lp += (double)end_term(T, uprev, fprev);
-        V3<R> d = from_eta(T, fprev);
-        R dn2 = dot(d, d);
-        R idn = Mth<R>::rsqrt(dn2);
-        V3<R> nu = idn * d;
-        R c = -dot(uprev, nu);
-        R ic = Mth<R>::rcp(c);
-        V3<R> dcr = (R)-1 * dunit(uprev, lprev, nu);
-        V3<R> dcd = (R)-1 * dunit(nu, dn2 * idn, uprev);
-        gA = gA - ic * dcr;
-        gB = gB + ic * dcr + ic * dcd;
+    } else {
+        t += (double)end_term(T, A.u, f1);
+        const V3<R> d = from_eta(T, f1);
+        const R dn2 = dot(d, d), idn = Mth<R>::rsqrt(dn2);
+        const V3<R> nu = idn * d;
+        const R ic = Mth<R>::rcp(-dot(A.u, nu));
+        const V3<R> dcr = (R)-1 * dunit(A.u, A.len, nu), dcd = (R)-1 * dunit(nu, dn2 * idn, A.u);
+        g = g + ic * dcr + ic * dcd;
         if (T.dk == RJPATH_DET_PAPER) {
-            R cr = dot(nu, T.dd);
-            R th = tanh((R)2 * cr + (R)0.7);
-            gB = gB + ((R)3 - (R)2 * th) * dunit(nu, dn2 * idn, T.dd);
+            const R cr = dot(nu, T.dd);
+            const R th = tanh((R)2 * cr + (R)0.7);
+            g = g + ((R)3 - (R)2 * th) * dunit(nu, dn2 * idn, T.dd);
         }
-        g_nm2 = gA;
-        g_nm1 = gB;
-        return zero ? -__builtin_inf() : lp;
     }
-};
-
-template <class R, class P, class Emit>
-__device__ __forceinline__ double score_stream(const Tgt<R>& T, const P& ps, int n, Emit emit) {
-    ScoreWalker<R> w;
-    w.init(T, ps.p(0));
-    V3<R> g, g2;
-    for (int k = 1; k < n; ++k)
-        if (w.step(T, ps.p(k), g)) emit(k - 2, g);
-    const double lp = w.finish(T, g, g2);
-    if (n >= 3) emit(n - 2, g);
-    emit(n - 1, g2);
-    return lp;
+    grad = g;
+    return A.len > (R)0 ? t : -__builtin_inf();
 }
 
 // Per-lane constants of the step kernel.
@@ -643,12 +596,13 @@ __device__ __forceinline__ void put_trace(const KArgs& a, const Lane<R>& ln, int
 
 } // namespace rj
 
+#include "rj_joint.h"
 #include "rj_tree.h"
 
 namespace rj {
 
-// A perturbation step: moves interior vertex j or the end point (or, by the
-// joint Langevin sampler, every interior vertex).
+// A perturbation step: moves interior vertex j or the end point (the joint
+// Langevin sampler comes here with lanes that picked the end point).
 // n does not change.  Returns the move kind, log A, the vertex and whether it
 // was accepted.
 template <class R, bool LO, int SAMP>
@@ -662,79 +616,7 @@ __device__ __forceinline__ void perturb_move(const Tgt<R>& T, const PathRef<R, L
     const V3<R> ex = {(R)1, (R)0, (R)0};
     const int j = 1 + pick(r[0], (uint32_t)(n - 1));
     idx = j;
-    const bool is_end = (j == n - 1);
-    if (SAMP == SAMP_JOINT && !is_end) {
-        // ---------- joint Langevin move of all interior vertices ----------
-        move = MV_MALA;
-        const R h = (R)sc.mala_h, hh = (R)0.5 * h, sh = Mth<R>::sqrt(h);
-        // One loop walks the current path x and the proposal y together:
-        // the walk over x finishes the gradient of vertex k, which gives
-        // y_k, which the walk over y consumes at once (it finishes the
-        // gradient of y_{k-2}).  y goes to the work buffer only for the
-        // copy-back on acceptance.
-        double half_xi2 = 0.0, rev = 0.0;
-        ScoreWalker<R> wx, wy;
-        const V3<R> x0 = ps.p(0);
-        wx.init(T, x0);
-        wy.init(T, x0);
-        // y_k, y_{k-1}, y_{k-2} of the last vertex k fed to the y walk, kept
-        // as scalars so that the ring stays in registers
-        R y0x = x0.x, y0y = x0.y, y0z = x0.z, y1x = x0.x, y1y = x0.y, y1z = x0.z;
-        R y2x = x0.x, y2y = x0.y, y2z = x0.z;
-        // y_k from the gradient of x at vertex k (interior: Langevin step)
-        auto make_y = [&](int k, V3<R> g) __attribute__((always_inline)) {
-            V3<R> y = ps.p(k);
-            if (k >= 1 && k <= n - 2) {
-                uint32_t q[4] = {sc.chain, (uint32_t)step, (uint32_t)(step >> 32), 2u + (uint32_t)k};
-                philox4x32_10(q, sc.k0, sc.k1);
-                V3<R> xi;
-                box_muller3<R>(q[0], q[1], q[2], q[3], xi);
-                half_xi2 += 0.5 * (double)dot(xi, xi);
-                y = y + hh * g + sh * xi;
-                work.glb[(size_t)k * work.C] = Vtx<R>{y.x, y.y, y.z, (R)0};
-            }
-            return y;
-        };
-        // the reverse-proposal term of vertex k from the gradient of y there
-        auto rev_term = [&](int k, V3<R> g, V3<R> yk) __attribute__((always_inline)) {
-            if (k >= 1 && k <= n - 2) {
-                V3<R> d = ps.p(k) - yk - hh * g;
-                rev += (double)dot(d, d) / (2.0 * (double)h);
-            }
-        };
-        auto feed_y = [&](V3<R> y) __attribute__((always_inline)) {
-            y2x = y1x;
-            y2y = y1y;
-            y2z = y1z;
-            y1x = y0x;
-            y1y = y0y;
-            y1z = y0z;
-            y0x = y.x;
-            y0y = y.y;
-            y0z = y.z;
-            const int ky = wy.k;
-            V3<R> gy;
-            if (wy.step(T, y, gy)) rev_term(ky - 2, gy, V3<R>{y2x, y2y, y2z});
-        };
-        V3<R> g, g2;
-        for (int k = 1; k < n; ++k) {
-            if (wx.step(T, ps.p(k), g) && k >= 3) feed_y(make_y(k - 2, g));
-        }
-        // (vertex 0 never moves; its gradient is not needed)
-        const double lpx = wx.finish(T, g, g2);
-        if (n >= 3) feed_y(make_y(n - 2, g));
-        feed_y(make_y(n - 1, g2));
-        const double lpy = wy.finish(T, g, g2);
-        if (n >= 3) rev_term(n - 2, g, V3<R>{y1x, y1y, y1z});
-        double la = lpy - lpx - rev + half_xi2;
-        logA = isfinite(lpy) ? (R)la : Mth<R>::ninf();
-        if (logu < logA) {
-            accepted = 1;
-            for (int k = 1; k <= n - 2; ++k) ps.st(k, work.ld(k));
-            full_logp(T, ps, n, ln.L, &ln.S); // refresh the cached depths, L and S
-        }
-        return;
-    }
+    const bool is_end = SAMP == SAMP_JOINT || (j == n - 1);
     // ---------- single-vertex perturbation: the five-vertex window ----------
     const bool hm2 = j >= 2, hp1 = !is_end, hp2 = j <= n - 3;
     // slots j-2 .. j+2 (absent neighbours are replaced by stand-ins below;
@@ -1061,11 +943,36 @@ __device__ __forceinline__ void perturb_step(const KArgs& a, const Tgt<R>& T, co
     perturb_move<R, LO, SAMP>(T, ps, work, ln, sc, step, r, logu, move, idx, accepted, logA);
     if (lp.counted()) {
         ln.ap += (uint32_t)accepted;
-        if constexpr (SAMP == SAMP_JOINT || SAMP == SAMP_LOCAL) {
-            const uint32_t im = (move == MV_MALA || move == MV_LMALA) ? 1u : 0u;
+        if constexpr (SAMP == SAMP_LOCAL) {
+            const uint32_t im = move == MV_LMALA ? 1u : 0u;
             ln.mp += im;
             ln.ma += im & (uint32_t)accepted;
         }
+        count_step(ln);
+    }
+    put_trace(a, ln, c, lp.s, move, idx, accepted, logA, logu);
+}
+
+// A perturbation step of the joint Langevin sampler: the lanes whose pick is an
+// interior vertex move all of theirs together, shared by the wave; the others'
+// end points are perturbed.
+template <class R>
+__device__ __forceinline__ void joint_step(const KArgs& a, const Tgt<R>& T, const PathRef<R, false>& ps,
+                                           const GlobalPath<R>& work, const WavePaths<R>& W, Lane<R>& ln,
+                                           const StepCtx& sc, const StepLoop& lp, int c) {
+    const uint64_t step = lp.step0 + (uint64_t)lp.s;
+    uint32_t r[8];
+    draw8<SAMP_JOINT>(sc, step, r);
+    const R logu = ln.live ? Mth<R>::log(unif<R>(r[1])) : -Mth<R>::ninf();
+    int move = MV_MALA, idx = 1 + pick(r[0], (uint32_t)(ln.n - 1)), accepted = 0;
+    R logA = Mth<R>::ninf();
+    const bool joint = idx != ln.n - 1;
+    if (!joint) perturb_move<R, false, SAMP_JOINT>(T, ps, work, ln, sc, step, r, logu, move, idx, accepted, logA);
+    joint_move<R>(T, ps, W, ln, sc, step, joint && ln.live, logu, accepted, logA);
+    if (lp.counted()) {
+        ln.ap += (uint32_t)accepted;
+        ln.mp += joint ? 1u : 0u;
+        ln.ma += joint ? (uint32_t)accepted : 0u;
         count_step(ln);
     }
     put_trace(a, ln, c, lp.s, move, idx, accepted, logA, logu);
@@ -1076,14 +983,14 @@ __device__ __forceinline__ void perturb_step(const KArgs& a, const Tgt<R>& T, co
 template <class R>
 __device__ __forceinline__ void tree_step(const KArgs& a, const Tgt<R>& T, const PathRef<R, false>& ps,
                                           const WavePaths<R>& W, Lane<R>& ln, const StepCtx& sc, const StepLoop& lp,
-                                          bool one_target, int c) {
+                                          int c) {
     const uint64_t step = lp.step0 + (uint64_t)lp.s;
     uint32_t r[8];
     draw8<SAMP_TREE>(sc, step, r);
     const R logu = ln.live ? Mth<R>::log(unif<R>(r[1])) : -Mth<R>::ninf();
     int accepted;
     R logA;
-    tree_move<R>(T, ps, W, ln, sc, step, r, logu, one_target, accepted, logA);
+    tree_move<R>(T, ps, W, ln, sc, step, r, logu, accepted, logA);
     if (lp.counted()) {
         ln.ap += (uint32_t)accepted;
         ln.mp += 1u;
@@ -1139,16 +1046,17 @@ template <class R, int MK, int SAMP, bool SL, bool EVEN> __device__ __forceinlin
     }
     const size_t C = (size_t)a.C;
     const int lane = tid % WAVE, cap = a.cap;
-    // the wave's first chain; a wave of the tree sampler owns a.cpw chains
-    // (its first lanes') and shares their whole-path moves over all 64 lanes
-    constexpr bool SHARED = SAMP == SAMP_TREE;
-    const int c0 = (int)blockIdx.x * (bs / WAVE) * (SHARED ? a.cpw : WAVE) + (tid / WAVE) * (SHARED ? a.cpw : WAVE);
+    // the wave's first chain; a wave of the whole-path samplers owns a.cpw
+    // chains (its first lanes') and shares their moves over all 64 lanes
+    constexpr bool SHARED = SAMP == SAMP_TREE || SAMP == SAMP_JOINT;
+    const int wave = SHARED ? __builtin_amdgcn_readfirstlane(tid / WAVE) : tid / WAVE; // (uniform: kept in SGPRs)
+    const int c0 = ((int)blockIdx.x * (bs / WAVE) + wave) * (SHARED ? a.cpw : WAVE);
     int c = c0 + lane;
     const bool own = c < a.C && (!SHARED || lane < a.cpw);
     if (!SHARED && !own) return;
     // this wave's tile, past its leading padding slot
     const LdsPtr<R> tiles = (LdsPtr<R>)((L4<R>*)(smem + tab_bytes));
-    const LdsPtr<R> tile = tiles + (size_t)(tid / WAVE) * (a.V + SLOT_PAD) * WAVE + WAVE;
+    const LdsPtr<R> tile = tiles + (size_t)wave * (a.V + SLOT_PAD) * WAVE + WAVE;
     const LdsPtr<R> lslots = tile + lane;
     int t = own ? a.target[c] : -1;
     Lane<R> ln{};
@@ -1156,18 +1064,23 @@ template <class R, int MK, int SAMP, bool SL, bool EVEN> __device__ __forceinlin
     // malformed chains are flagged and never touched
     const bool good = own && t >= 0 && t < a.T && ln.n >= 2 && ln.n <= cap && a.medium[t] >= 0 && a.medium[t] < a.n_media;
     if (own && !good) a.status[c] = 1;
+    LaneRun run = whole_wave();
     if (SHARED) {
         // lanes without a chain stay for the shared moves, as a dead chain of
-        // two equal vertices on the first good lane's target
+        // two equal vertices; before share_lanes() on the target of the good
+        // lane to their left (so that the lanes of a target stay neighbours),
+        // or of the first one
         const uint64_t m = __ballot(good);
         if (m == 0) return;
-        const int from = __ffsll((unsigned long long)m) - 1;
+        const uint64_t left = m & ((1ull << lane) - 1);
+        const int from = left ? 63 - __clzll((long long)left) : __ffsll((unsigned long long)m) - 1;
         const int t1 = __shfl(t, from, WAVE);
         if (!good) {
             t = t1;
             c = c0 + from;
             ln.n = 2;
         }
+        run = share_lanes(lane, a.cpw, good ? ln.n : 0, t);
     } else if (!good) {
         return;
     }
@@ -1202,7 +1115,6 @@ template <class R, int MK, int SAMP, bool SL, bool EVEN> __device__ __forceinlin
     const bool healthy = good && isfinite(ln.lp);
     if (good) a.status[c] = healthy ? 0 : 1;
     WavePaths<R> W{};
-    bool one_target = false;
     if constexpr (SHARED) {
         // proposals: the tile's columns from 32 on where the wave owns at most
         // 32 chains, else a.Vy slots' room behind the block's tiles
@@ -1210,7 +1122,7 @@ template <class R, int MK, int SAMP, bool SL, bool EVEN> __device__ __forceinlin
         W.x = tile;
         W.V = a.V;
         W.y = half ? tile + WAVE / 2
-                   : tiles + (size_t)(bs / WAVE) * (a.V + SLOT_PAD) * WAVE + (size_t)(tid / WAVE) * a.Vy * WAVE;
+                   : tiles + (size_t)(bs / WAVE) * (a.V + SLOT_PAD) * WAVE + (size_t)wave * a.Vy * WAVE;
         W.My = half ? a.V * (WAVE / 2) : a.Vy * WAVE;
         W.ymask = half ? ~(WAVE / 2 - 1) : 0;
         W.gx = (Vtx<R>*)a.verts + c0;
@@ -1220,7 +1132,7 @@ template <class R, int MK, int SAMP, bool SL, bool EVEN> __device__ __forceinlin
         W.cpw = a.cpw;
         W.chain0 = (uint32_t)c0;
         W.lane = lane;
-        one_target = __all(t == __builtin_amdgcn_readfirstlane(t));
+        W.run = run;
     }
 
     StepCtx sc;
@@ -1267,12 +1179,14 @@ template <class R, int MK, int SAMP, bool SL, bool EVEN> __device__ __forceinlin
         if (phase < a.n_perturb) {
             const int m = a.n_perturb - phase < left ? a.n_perturb - phase : left, end = lp.s + m;
             if constexpr (SHARED) {
-                if (phase == 0) {
-                    tree_step<R>(a, T, ps, W, ln, sc, lp, one_target, c);
+                if (SAMP == SAMP_TREE && phase == 0) {
+                    tree_step<R>(a, T, ps, W, ln, sc, lp, c);
                     ++lp.s;
                 }
             }
-            if (__all(ln.n < a.V)) {
+            if constexpr (SAMP == SAMP_JOINT) {
+                for (; lp.s < end; ++lp.s) joint_step<R>(a, T, ps, work, W, ln, sc, lp, c);
+            } else if (__all(ln.n < a.V)) {
                 for (; lp.s < end; ++lp.s) perturb_step<R, true, SAMP>(a, T, pl, work, ln, sc, lp, c);
             } else {
                 for (; lp.s < end; ++lp.s) perturb_step<R, false, SAMP>(a, T, ps, work, ln, sc, lp, c);

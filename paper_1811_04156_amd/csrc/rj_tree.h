@@ -2,7 +2,7 @@
 // rj_step.h, whose path storage and density factors it uses).
 #pragma once
 
-#include "rj_wave.h"
+#include "rj_paths.h"
 
 namespace rj {
 
@@ -36,117 +36,11 @@ namespace rj {
 // that reaches the level, 64 at a time; then the items are (chain, segment)
 // over both walks of log p, and over the accepted proposals' copy-back.  The
 // terms of log A are summed per chain in FP64 in the tile's leading padding
-// slot, which nothing else keeps.  The walks use the
-// lane's own target, so a wave with several targets walks its chains lane by
-// lane.  With fewer chains than two waves per SIMD a wave owns fewer than 64
-// chains (cpw), so that more waves share the work.
-//
-// Storage.  Neighbouring lanes work on neighbouring vertices of one chain, so
-// the proposals are kept chain after chain without gaps (a wave's chains need
-// the sum of their n, not 64 times the longest), the first My vertices in LDS
-// and the rest in the wave's part of the work buffer; the vertices of the paths
-// beyond their LDS slots, which lie 16 n_chains bytes apart, are copied behind
-// them in the same order first.  (Read in place, one cache line per vertex
-// and read, the two-region test's 80-vertex paths kept the waves waiting for
-// 75% of their cycles.)
+// slot, which nothing else keeps.  The walks need a chain's target, so the lanes
+// of one target share theirs (share_lanes).  With fewer chains than two waves
+// per SIMD a wave owns fewer than 64 chains (cpw), so that more waves share the
+// work.
 // ---------------------------------------------------------------------------
-template <class R> struct WavePaths {
-    LdsPtr<R> x, y;    // paths: slot 0 of column 0 of the wave's tile (stride WAVE); proposals: LDS vertex 0
-    Vtx<R>* gx;        // vertex 0 of the wave's first chain
-    Vtx<R>* part;      // the wave's part of the work buffer (cap vertices per chain)
-    int V, My, ymask;  // LDS vertex i of the proposals is y[i + (i & ymask)]
-    int cpw;           // chains of the wave (a power of two; the last wave may have fewer)
-    int room;          // vertices of the wave's part
-    size_t C;
-    uint32_t chain0;   // the wave's first chain
-    int lane;
-
-    __device__ __forceinline__ Vtx<R> ldy(int i) const {
-        if (i < My) return lds_ld<R>(y + (i + (i & ymask)));
-        return part[i];
-    }
-    __device__ __forceinline__ void sty(int i, const Vtx<R>& p) const {
-        if (i < My) lds_st<R>(y + (i + (i & ymask)), p);
-        else part[i] = p;
-    }
-    __device__ __forceinline__ void styw(int i, R w) const {
-        if (i < My) ((LdsScalar<R>)(y + (i + (i & ymask))))[3] = w;
-        else part[i].w = w;
-    }
-    // the chain's FP64 sums (padding slot -1 holds two)
-    __device__ __forceinline__ LdsScalar<double> sum(int q) const { return (LdsScalar<double>)(x - WAVE + q); }
-    __device__ __forceinline__ void add(int q, double v, int k = 0) const {
-        __hip_atomic_fetch_add(sum(q) + k, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    }
-};
-
-// Chain q of the wave during a move: its first vertex's place `at` among the
-// wave's proposals, and the offset of the copied paths (0: not copied).
-template <class R> struct WaveChain {
-    const WavePaths<R>& W;
-    int q, at, copy;
-    __device__ __forceinline__ V3<R> x(int v) const {
-        if (v < W.V) return pos(lds_ld<R>(W.x + v * WAVE + q));
-        return far_x(v);
-    }
-    __device__ __forceinline__ V3<R> far_x(int v) const {
-        const Vtx<R>* const p = copy ? W.part + (copy + at + v) : W.gx + ((size_t)v * W.C + q);
-        const L4<R> g = *(const L4<R>*)p;
-        return {g.x, g.y, g.z};
-    }
-    __device__ __forceinline__ V3<R> y(int v) const { return pos(W.ldy(at + v)); }
-    // Several vertices at once: LDS reads for all (the ones that lie elsewhere
-    // read some slot), then one branch that fetches those together.
-    template <int K> __device__ __forceinline__ void xs(const int (&v)[K], V3<R> (&o)[K]) const {
-        int hi = v[0];
-#pragma unroll
-        for (int i = 0; i < K; ++i) {
-            o[i] = pos(lds_ld<R>(W.x + (v[i] < W.V ? v[i] : W.V) * WAVE + q));
-            hi = max(hi, v[i]);
-        }
-        if (hi >= W.V) {
-            V3<R> g[K];
-#pragma unroll
-            for (int i = 0; i < K; ++i) g[i] = far_x(v[i]);
-#pragma unroll
-            for (int i = 0; i < K; ++i)
-                if (v[i] >= W.V) o[i] = g[i];
-        }
-    }
-    template <int K> __device__ __forceinline__ void ys(const int (&v)[K], V3<R> (&o)[K]) const {
-        int hi = v[0];
-#pragma unroll
-        for (int i = 0; i < K; ++i) hi = max(hi, v[i]);
-        if (W.My > 0) { // (uniform)
-#pragma unroll
-            for (int i = 0; i < K; ++i) {
-                const int j = min(at + v[i], W.My - 1);
-                o[i] = pos(lds_ld<R>(W.y + (j + (j & W.ymask))));
-            }
-        }
-        if (at + hi >= W.My) {
-            V3<R> g[K];
-#pragma unroll
-            for (int i = 0; i < K; ++i) {
-                const L4<R> p = *(const L4<R>*)(W.part + (at + v[i]));
-                g[i] = {p.x, p.y, p.z};
-            }
-#pragma unroll
-            for (int i = 0; i < K; ++i)
-                if (at + v[i] >= W.My) o[i] = g[i];
-        }
-    }
-};
-
-// One chain's path or proposal as the log p walk of a single lane reads it.
-template <class R, bool Y> struct LanePath {
-    WaveChain<R> c;
-    __device__ __forceinline__ V3<R> p(int v) const { return Y ? c.y(v) : c.x(v); }
-    __device__ __forceinline__ void stw(int v, R t) const {
-        if (Y) c.W.styw(c.at + v, t);
-    }
-};
-
 // frame (e2, e3) of interval (k, l) of a path: root -> onb of the axis;
 // otherwise from the parent interval (kp, lp) and its vertex fp.  Both are
 // formed and one is selected by value (a choice between output references
@@ -245,33 +139,12 @@ __device__ __forceinline__ void tree_node(const WaveChain<R>& c, const StepCtx& 
 template <class R>
 __device__ __forceinline__ void tree_move(const Tgt<R>& T, const PathRef<R, false>& ps, const WavePaths<R>& W,
                                           Lane<R>& ln, const StepCtx& sc, uint64_t step, const uint32_t r[8], R logu,
-                                          bool one_target, int& accepted, R& logA) {
+                                          int& accepted, R& logA) {
     const int n = ln.n, lane = W.lane;
     const bool act = ln.live;
-    accepted = 0;
-    logA = Mth<R>::ninf();
-    // (the chains' own lanes wrote the vertices beyond the LDS slots)
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
     const V3<R> x0 = ps.p(0), xe = ps.p(n - 1);
-    // the chains' places among the wave's vertices, and the paths' copy
-    const int mine = act ? n : 0;
-    const int upto = wave_prefix(mine), at = upto - mine;
-    const int all = __builtin_amdgcn_readlane(upto, WAVE - 1);
-    const int copy = 2 * all <= W.room && __any(mine > W.V) ? all : 0;
-    if (copy) {
-        // row by row, lanes over the wave's chains (whole cache lines), four rows in flight
-        const int q = lane & (W.cpw - 1), rows = WAVE / W.cpw;
-        const int nq = __shfl(mine, q, WAVE), to = copy + __shfl(at, q, WAVE);
-        for (int v = W.V + lane / W.cpw; __any(v < nq); v += 4 * rows) {
-            L4<R> g[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (v + i * rows < nq) g[i] = *(const L4<R>*)(W.gx + ((size_t)(v + i * rows) * W.C + q));
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (v + i * rows < nq) *(L4<R>*)(W.part + (to + v + i * rows)) = g[i];
-        }
-    }
+    const WavePlaces P = wave_places<R>(W, ps, act ? n : 0);
+    const int at = P.at, copy = P.copy, all = P.all;
     // end point: von Mises-Fisher step about the current sensor normal
     V3<R> yend;
     {
@@ -325,71 +198,27 @@ __device__ __forceinline__ void tree_move(const Tgt<R>& T, const PathRef<R, fals
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
     }
-    // log p(y) - log p(x)
-    if (one_target) {
-        // items: the segments of all chains in order
-        WaveItems it;
-        it.init(lane, N);
-        while (it.more()) {
-            int q, k;
-            const bool has = it.next(q, k);
-            const WaveChain<R> cq{W, q, __shfl(at, q, WAVE), copy};
-            const int nq = __shfl(n, q, WAVE);
-            if (has) {
-                const int v[3] = {k, k + 1, k + 2 < nq ? k + 2 : k + 1};
-                V3<R> x[3], y[3];
-                cq.xs(v, x);
-                cq.ys(v, y);
-                R tx, ty;
-                const double a = walk_term(T, nq, k, x[0], x[1], x[2], tx);
-                const double b = walk_term(T, nq, k, y[0], y[1], y[2], ty);
-                W.styw(cq.at + k, ty);
-                W.add(q, b - a);
-            }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-    } else if (act) {
-        double L;
-        const WaveChain<R> c{W, lane, at, copy};
-        const double lpx = full_logp(T, LanePath<R, false>{c}, n, L);
-        const double lpy = full_logp(T, LanePath<R, true>{c}, n, L);
-        *W.sum(lane) += lpy - lpx;
-    }
-    if (act) {
-        const double la = *W.sum(lane);
-        logA = isfinite(la) ? (R)la : Mth<R>::ninf();
-        accepted = logu < logA ? 1 : 0;
-        // (the sums of the accepted proposal's length and depths next)
-        W.sum(lane)[0] = 0.0;
-        W.sum(lane)[1] = 0.0;
-    }
-    // the accepted proposals, with the depths their walk left
+    // log p(y) - log p(x): the segments, by the lanes of the same target
     WaveItems it;
-    it.init(lane, accepted ? n : 0);
+    it.init(lane, N, W.run);
     while (it.more()) {
         int q, k;
         const bool has = it.next(q, k);
-        const int aq = __shfl(at, q, WAVE), nq = __shfl(n, q, WAVE);
+        const WaveChain<R> cq{W, q, __shfl(at, q, WAVE), copy};
+        const int nq = __shfl(n, q, WAVE);
         if (has) {
-            Vtx<R> f = W.ldy(aq + k);
-            if (k < nq - 1) {
-                const V3<R> d = pos(W.ldy(aq + k + 1)) - pos(f);
-                const R l2 = dot(d, d);
-                const R len = l2 * Mth<R>::rsqrt(l2);
-                W.add(q, (double)len, 0);
-                W.add(q, (double)f.w, 1);
-            } else {
-                f.w = (R)0;
-            }
-            if (k < W.V) lds_st<R>(W.x + k * WAVE + q, f);
-            else W.gx[(size_t)k * W.C + q] = f;
+            const int v[3] = {k, k + 1, k + 2 < nq ? k + 2 : k + 1};
+            V3<R> x[3], y[3];
+            cq.xs(v, x);
+            cq.ys(v, y);
+            R tx, ty;
+            const double a = walk_term(T, nq, k, x[0], x[1], x[2], tx);
+            const double b = walk_term(T, nq, k, y[0], y[1], y[2], ty);
+            W.styw(cq.at + k, ty);
+            W.add(q, b - a);
         }
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-    if (accepted) {
-        ln.L = W.sum(lane)[0];
-        ln.S = W.sum(lane)[1];
-    }
+    settle_shared<R>(W, P, ln, act, logu, accepted, logA);
 }
 
 } // namespace rj

@@ -207,6 +207,32 @@ def test_tree_moves_shared_by_any_number_of_chains(rj):
     assert a[2][:, 14].sum() > 1000  # tree moves were accepted
 
 
+@pytest.mark.parametrize("run", [1, 11])
+def test_joint_moves_shared_by_any_number_of_chains(rj, run):
+    """A wave of the joint Langevin sampler owns 64 chains of a large launch
+    and 8 of a small one, whose lanes without a chain help its targets.  The
+    first 5003 chains of a 140,001-chain launch take the paths that they take
+    as a launch of their own, with ``run`` neighbouring chains per target
+    (waves of up to 64 targets; of one or two of them).  The statistics' sums
+    differ by their rounding (1e-12)."""
+    w = W.layered_pairs(seed=8, pairs=70, chains=140_001, cap=40, n_layers=12, dz=4.0, dmin=4.0, dmax=25.0)
+    w.update(sampler=1, mala_h=0.01, burn_in=0, sigma=2.0)
+    w["c_target"] = (np.arange(140_001) // run % 70).astype(np.int32)
+    out = []
+    for ww in (w, W.subset_chains(w, 5003)):
+        s = rj.Sampler(ww, precision="f32")
+        s.run(100)
+        torch.cuda.synchronize()
+        k = 5003
+        used = torch.arange(s.cap, device=s.dev)[:, None] < s.n[:k]
+        out.append((s.n[:k].cpu().numpy(), torch.where(used[..., None], s.verts[:, :k, :3], 0.0).cpu().numpy(),
+                    s.stats[:k].cpu().numpy()))
+    a, b = out
+    assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+    assert np.allclose(a[2], b[2], rtol=1e-12)
+    assert a[2][:, 14].sum() > 1000  # joint moves were accepted
+
+
 @pytest.mark.parametrize("prec", ["f32", "f64"])
 def test_bridge_whatever_the_order_and_number_of_chains(rj, prec):
     """The bridge's waves share the vertices of 8 chains in a small launch and
