@@ -321,12 +321,12 @@ int device_cus() {
 // Chains per wave of the samplers whose waves share whole-path moves: as few
 // (from 64 down to 8) as keep the launch within so many waves per SIMD, so that
 // the shared moves use more of the chip.  Two are resident.  Tree moves: two
-// (the jumps and perturbations cost by the wave: the 65,536-chain two-region
-// test, 500 steps, takes 132 us per step with 32 chains per wave and 142 with
-// 16).  Joint Langevin moves: four, since most of the run is shared items and
-// a few waves of far targets outlast the rest (50,001 chains of the ragged
-// batch: 26.4 us per step within two, 21.7 within four, 26.2 within eight;
-// 100,000 chains 45.5, 32.7 and 33.6; 20,000 chains 14.8 in each).
+// (200 steps of 20,000, 50,000 and 100,000 chains of the ragged batch: 1.34,
+// 2.01 and 3.07 ms within two, 1.61, 2.12 and 2.59 within four; the jumps and
+// perturbations cost by the wave).  Joint Langevin moves, which are more of
+// the run: four (20,000, 50,001 and 100,000 chains: 2.53, 4.50 and 8.57 ms
+// within two, 2.19, 3.11 and 4.80 within four, 2.18, 4.36 and 5.54 within
+// eight).
 bool shares_moves(int sampler) { return sampler == RJPATH_TREE || sampler == RJPATH_MALA; }
 
 int shared_cpw(int sampler, int n_chains) {
@@ -380,6 +380,19 @@ void default_launch(const rjpath_chains* c, size_t tab_bytes, int sampler, int& 
     }
 }
 
+// Waves of a launch whose order is worth finding (launch_order, about 10 us): of
+// one with more blocks than the chip holds (two waves per SIMD, the CU's LDS),
+// and from ORDER_STEPS steps on (16 steps of 262,144 and 1,048,576 chains of the
+// ragged batch gain 1 to 2%, 200 steps 5 to 20%).  0: none.
+constexpr int ORDER_STEPS = 16;
+int ordered_waves(const KArgs& a, int block, int per, int precision) {
+    const size_t tile = (size_t)block * vtx_bytes(precision);
+    const size_t lds = a.tab_bytes + (size_t)(a.V + 2 + a.Vy) * tile;
+    const int per_cu = (int)std::max<size_t>(1, std::min<size_t>(LDS_MAX / lds, 512 / (size_t)block));
+    const int waves = (a.C + per - 1) / per;
+    return (waves + block / 64 - 1) / (block / 64) > device_cus() * per_cu && waves <= ORDER_WAVES ? waves : 0;
+}
+
 int run_impl(rjpath_medium* m, const rjpath_targets* t, const rjpath_chains* c, const rjpath_run_params* p,
              hipStream_t s, int block, int V) {
     KArgs a = make_args(m, t, c);
@@ -406,12 +419,18 @@ int run_impl(rjpath_medium* m, const rjpath_targets* t, const rjpath_chains* c, 
             a.Vy = (int)std::min<size_t>(V, (share - x) / per);
         }
     }
+    const int per = shares_moves(p->sampler) ? a.cpw : 64, waves = ordered_waves(a, block, per, c->precision);
     int chunk = p->chunk > 0 ? p->chunk : p->steps;
     for (int done = 0; done < p->steps; done += chunk) {
         // with a device counter, step0 carries the offset inside this call
         a.step0 = (p->step_counter ? 0 : p->step0) + (uint64_t)done;
         a.steps = std::min(chunk, p->steps - done);
         a.trace_off = done;
+        a.ordered = a.steps >= ORDER_STEPS ? waves : 0;
+        if (a.ordered) {
+            hipError_t e = launch_order(a, per, s);
+            if (e != hipSuccess) return hip_fail(e, "order kernel launch");
+        }
         hipError_t e = launch_run(a, block, s);
         if (e != hipSuccess) return hip_fail(e, "run kernel launch");
     }

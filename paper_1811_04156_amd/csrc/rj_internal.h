@@ -63,6 +63,7 @@ struct KArgs {
     size_t tab_bytes; // LDS bytes of the staged tables (0: read them from HBM)
     // whole-path samplers: chains per wave (64, 32, 16 or 8) and LDS slots of a proposal (64 chains per wave only)
     int32_t cpw, Vy;
+    int32_t ordered; // waves whose order the status words hold (launch_order), or 0
     // run
     uint64_t seed, step0;
     int64_t burn_in;

@@ -12,6 +12,10 @@ enum { RD_SAMPLES = 0, RD_A, RD_B, RD_L, RD_L2, RD_CHAINS, RD_NW };
 
 hipError_t launch_run(const KArgs& a, int block, hipStream_t s);
 hipError_t set_run_lds_limit();
+// the order of the waves of a launch, `per` chains each, into the status words
+// (at most ORDER_WAVES; rj_order.hip)
+constexpr int ORDER_BINS = 1024, ORDER_WAVES = 16 * ORDER_BINS;
+hipError_t launch_order(const KArgs& a, int per, hipStream_t s);
 // the step-kernel variants of one precision and interior move (0 plain, 1
 // joint Langevin, 2 single-vertex Langevin, 3 tree coordinates; defined in rj_run.h,
 // instantiated once each in the rj_run_*.hip units)

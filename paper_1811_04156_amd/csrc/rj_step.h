@@ -1033,6 +1033,26 @@ __device__ __forceinline__ void jump_step(const KArgs& a, const Tgt<R>& T, const
 // ---------------------------------------------------------------------------
 enum { MK_HOM = 0, MK_LAY = 1, MK_LAY_LDS = 2 };
 
+// The place of this wave's chains: an ordered launch's order stands in bits 8
+// and up of the status words, one per wave, and is cleared as it is read; bits
+// 0 to 7 are the status of the word's own chain, which another wave may have
+// stored already, so both sides store bytes.
+__device__ __forceinline__ int take_order(const KArgs& a, int wave) {
+    if (!a.ordered) return wave;
+    if (wave >= a.ordered) return wave; // (past the last chain)
+    int32_t* const word = a.status + wave;
+    const int w = *(volatile int32_t*)word >> 8;
+    if (threadIdx.x % WAVE == 0) {
+        ((volatile uint8_t*)word)[1] = 0;
+        ((volatile uint16_t*)word)[1] = 0;
+    }
+    return __builtin_amdgcn_readfirstlane(w);
+}
+__device__ __forceinline__ void put_status(const KArgs& a, int c, int v) {
+    if (c < a.ordered) *(volatile uint8_t*)(a.status + c) = (uint8_t)v;
+    else a.status[c] = v;
+}
+
 template <class R, int MK, int SAMP, bool SL, bool EVEN> __device__ __forceinline__ void run_body(const KArgs& a) {
     constexpr bool TAB = MK == MK_LAY_LDS;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -1049,8 +1069,8 @@ template <class R, int MK, int SAMP, bool SL, bool EVEN> __device__ __forceinlin
     // the wave's first chain; a wave of the whole-path samplers owns a.cpw
     // chains (its first lanes') and shares their moves over all 64 lanes
     constexpr bool SHARED = SAMP == SAMP_TREE || SAMP == SAMP_JOINT;
-    const int wave = SHARED ? __builtin_amdgcn_readfirstlane(tid / WAVE) : tid / WAVE; // (uniform: kept in SGPRs)
-    const int c0 = ((int)blockIdx.x * (bs / WAVE) + wave) * (SHARED ? a.cpw : WAVE);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / WAVE); // (uniform: kept in SGPRs)
+    const int c0 = take_order(a, (int)blockIdx.x * (bs / WAVE) + wave) * (SHARED ? a.cpw : WAVE);
     int c = c0 + lane;
     const bool own = c < a.C && (!SHARED || lane < a.cpw);
     if (!SHARED && !own) return;
@@ -1063,7 +1083,7 @@ template <class R, int MK, int SAMP, bool SL, bool EVEN> __device__ __forceinlin
     ln.n = own ? a.n[c] : 0;
     // malformed chains are flagged and never touched
     const bool good = own && t >= 0 && t < a.T && ln.n >= 2 && ln.n <= cap && a.medium[t] >= 0 && a.medium[t] < a.n_media;
-    if (own && !good) a.status[c] = 1;
+    if (own && !good) put_status(a, c, 1);
     LaneRun run = whole_wave();
     if (SHARED) {
         // lanes without a chain stay for the shared moves, as a dead chain of
@@ -1113,7 +1133,7 @@ template <class R, int MK, int SAMP, bool SL, bool EVEN> __device__ __forceinlin
 
     ln.lp = full_logp(T, ps, ln.n, ln.L, &ln.S);
     const bool healthy = good && isfinite(ln.lp);
-    if (good) a.status[c] = healthy ? 0 : 1;
+    if (good) put_status(a, c, healthy ? 0 : 1);
     WavePaths<R> W{};
     if constexpr (SHARED) {
         // proposals: the tile's columns from 32 on where the wave owns at most

@@ -233,6 +233,33 @@ def test_joint_moves_shared_by_any_number_of_chains(rj, run):
     assert a[2][:, 14].sum() > 1000  # joint moves were accepted
 
 
+@pytest.mark.parametrize("prec,sampler,chains", [("f32", 0, 140_001), ("f32", 2, 140_001), ("f64", 0, 140_001),
+                                                 ("f32", 1, 60_001)])
+def test_ordered_launch_leaves_no_trace(rj, prec, sampler, chains):
+    """A launch of more blocks than the chip holds takes its waves in the
+    order of their vertices, kept in the status words meanwhile.  Every chain
+    takes the same path as in launches of fewer steps than the order is made
+    for, malformed chains (the first and last among them) are flagged and
+    untouched, and the status words hold 0 and 1 alone."""
+    w = W.layered_pairs(seed=9, pairs=90, chains=chains, cap=40, n_layers=12, dz=4.0, dmin=4.0, dmax=25.0)
+    w.update(sampler=sampler, mala_h=0.05 if sampler == 2 else 0.01, burn_in=0, sigma=2.0)
+    out = []
+    for parts in ((32,), (8, 8, 8, 8)):
+        s = rj.Sampler(w, precision=prec)
+        bad = torch.tensor([0, 1, 63, 64, 2186, 2187, 2188, 30_000, chains - 1], device=s.dev)
+        s.n[bad] = torch.tensor([0, 1, -3, 41, 1000, 1, 0, 1, 41], dtype=s.n.dtype, device=s.dev)
+        s.status.fill_(0x7F7F7F)
+        for k in parts:
+            s.run(k)
+        torch.cuda.synchronize()
+        flagged = torch.zeros(chains, dtype=s.status.dtype, device=s.dev)
+        flagged[bad] = 1
+        assert torch.equal(s.status, flagged)
+        used = torch.arange(s.cap, device=s.dev)[:, None] < s.n
+        out.append((s.n.clone(), torch.where(used[..., None], s.verts[..., :3], 0.0).clone()))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
 @pytest.mark.parametrize("prec", ["f32", "f64"])
 def test_bridge_whatever_the_order_and_number_of_chains(rj, prec):
     """The bridge's waves share the vertices of 8 chains in a small launch and
