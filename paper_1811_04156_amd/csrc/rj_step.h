@@ -106,8 +106,35 @@ template <class R, bool LO> struct PathRef {
             if (i4 >= V) o4 = Vtx<R>{g4.x, g4.y, g4.z, g4.w};
         }
     }
-    // The vertex shifts of an accepted jump, split at the LDS/HBM boundary
-    // into loops that touch one memory each (no per-vertex branch on the
+    // The vertex shift of an accepted jump: slots lo..hi move one up (from the
+    // top), or slots lo+1..hi+1 one down (from the bottom).  In LDS births and
+    // deaths share one loop, which reads SHIFT vertices before it writes them
+    // and past the last one moves that one again: the wave waits once per
+    // SHIFT vertices of its longest shift.  (A loop for each, four vertices at
+    // a time and then one at a time: a jump step of 65,536 homogeneous chains
+    // took 3.55 us and takes 3.05.  With paths beyond the LDS slots the shared
+    // loop was slower, 76 against 65 us per jump step of the two-region test.)
+    static constexpr int SHIFT = 6;
+    __device__ __forceinline__ void shift(bool up, int lo, int hi) const {
+        if (!LO) {
+            if (up) shift_up(lo, hi);
+            else shift_down(lo, hi);
+            return;
+        }
+        const int dir = up ? -1 : 1;
+        for (int left = hi - lo, v = up ? hi : lo + 1; left >= 0; left -= SHIFT, v += dir * SHIFT) {
+            L4<R> x[SHIFT];
+            LdsPtr<R> at[SHIFT];
+#pragma unroll
+            for (int i = 0; i < SHIFT; ++i) at[i] = lds + (v + dir * (i < left ? i : left)) * WAVE;
+#pragma unroll
+            for (int i = 0; i < SHIFT; ++i) x[i] = *at[i];
+#pragma unroll
+            for (int i = 0; i < SHIFT; ++i) at[i][-dir * WAVE] = x[i];
+        }
+    }
+    // The vertex shifts of an accepted jump where some lie in HBM, split at the
+    // boundary into loops that touch one memory each (no per-vertex branch on the
     // address space), each reading four vertices before writing them (one
     // latency per four): slots lo..hi move one slot up (from the top) ...
     __device__ __forceinline__ void lds_up(int& v, int lo) const {
@@ -122,7 +149,7 @@ template <class R, bool LO> struct PathRef {
     }
     __device__ __forceinline__ void shift_up(int lo, int hi) const {
         int v = hi;
-        if (!LO) {
+        {
             L4<R>* const g = (L4<R>*)glb;
             for (; v - 3 >= lo && v - 3 >= V; v -= 4) {
                 const L4<R> a = g[(size_t)v * C], b = g[(size_t)(v - 1) * C], c = g[(size_t)(v - 2) * C],
@@ -143,7 +170,7 @@ template <class R, bool LO> struct PathRef {
     // ... or slots lo+1..hi+1 move one slot down (from the bottom).
     __device__ __forceinline__ void shift_down(int lo, int hi) const {
         int v = lo;
-        const int top = LO ? hi : (hi < V - 2 ? hi : V - 2); // the moves that stay in LDS
+        const int top = hi < V - 2 ? hi : V - 2; // the moves that stay in LDS
         for (; v + 3 <= top; v += 4) {
             const L4<R> a = lds[(v + 1) * WAVE], b = lds[(v + 2) * WAVE], c = lds[(v + 3) * WAVE],
                         d = lds[(v + 4) * WAVE];
@@ -153,7 +180,7 @@ template <class R, bool LO> struct PathRef {
             lds[(v + 3) * WAVE] = d;
         }
         for (; v <= top; ++v) lds[v * WAVE] = lds[(v + 1) * WAVE];
-        if (!LO) {
+        {
             L4<R>* const g = (L4<R>*)glb;
             if (v <= hi && v == V - 1) {
                 lds[v * WAVE] = g[(size_t)V * C];
@@ -898,29 +925,18 @@ __device__ __forceinline__ void jump_move(const Tgt<R>& T, const PathRef<R, LO>&
         accepted = 1;
         fold_run(ln, T.n0, sc, lp); // the steps spent at the old n
         const double dL = (double)sA.len + (double)sB.len - (double)AB.len;
-        if (birth) {
-            ps.shift_up(iB, n - 1);
-            ps.st(iB, Vtx<R>{fv.x, fv.y, fv.z, sB.tb});
-            ps.stw(iA, sA.tb);
-            ln.L += dL;
-            ln.S = (S - (double)wA) + ((double)sA.tb + (double)sB.tb);
-            ln.n = n + 1;
-            if (sc.logw) {
-                ln.lwm = ln.lw0;
-                ln.lw0 = ln.lwp;
-                ln.lwp = sc.logw[n + 2 <= sc.cap ? n + 2 : sc.cap];
-            }
-        } else {
-            ps.shift_down(jv, n - 2);
-            ps.stw(iA, AB.tb);
-            ln.L -= dL;
-            ln.S = Sx;
-            ln.n = n - 1;
-            if (sc.logw) {
-                ln.lwp = ln.lw0;
-                ln.lw0 = ln.lwm;
-                ln.lwm = sc.logw[n - 2];
-            }
+        ps.shift(birth, iA + 1, birth ? n - 1 : n - 2);
+        if (birth) ps.st(iB, Vtx<R>{fv.x, fv.y, fv.z, sB.tb});
+        ps.stw(iA, birth ? sA.tb : AB.tb);
+        ln.L += birth ? dL : -dL;
+        ln.S = birth ? (S - (double)wA) + ((double)sA.tb + (double)sB.tb) : Sx;
+        ln.n = birth ? n + 1 : n - 1;
+        if (sc.logw) {
+            const double lw = sc.logw[!birth ? n - 2 : n + 2 <= sc.cap ? n + 2 : sc.cap];
+            const double lw0 = birth ? ln.lwp : ln.lwm;
+            ln.lwm = birth ? ln.lw0 : lw;
+            ln.lwp = birth ? lw : ln.lw0;
+            ln.lw0 = lw0;
         }
         if (sc.logw) ln.invw = inv_tilt<R>(ln.lw0);
     }
