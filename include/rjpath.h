@@ -126,11 +126,11 @@ typedef struct {
  * verts[v * n_chains + c], four values (x, y, z, w) of the precision's type:
  * x, y, z relative to the chain's source (f_0 = 0), w is library-owned scratch
  * (the scattering depth of the segment leaving the vertex).  Slots v >= n[c]
- * are unused.  logp[c] receives log p of the final path; status[c] is 0 for a
+ * hold nothing (RJPATH_MALA and RJPATH_TREE runs write there).  logp[c] receives log p of the final path; status[c] is 0 for a
  * healthy chain and 1 if its starting path had zero or non-finite density
  * (such a chain is not moved and adds nothing to the statistics).
- * work: proposal buffer with the layout of verts (required for RJPATH_MALA
- * and RJPATH_TREE, else may be NULL). */
+ * work: scratch of the size of verts, contents of no meaning between the calls
+ * (required for RJPATH_MALA and RJPATH_TREE, else may be NULL). */
 typedef struct {
     int32_t n_chains;
     int32_t cap;       /* maximum vertex count, 2 <= cap <= 4096 */

@@ -23,7 +23,7 @@ __device__ __forceinline__ void joint_move(const Tgt<R>& T, const PathRef<R, fal
                                            const StepCtx& sc, uint64_t step, bool act, R logu, int& accepted, R& logA) {
     const int n = ln.n, lane = W.lane;
     const R h = (R)sc.mala_h, hh = (R)0.5 * h, sh = Mth<R>::sqrt(h);
-    const WavePlaces P = wave_places<R>(W, ps, act ? n : 0);
+    const WavePlaces P = wave_places<R>(W, act ? n : 0);
     if (act) {
         const Vtx<R> f = ps.ld(0), e = ps.ld(n - 1);
         W.sty(P.at, f);
@@ -41,7 +41,7 @@ __device__ __forceinline__ void joint_move(const Tgt<R>& T, const PathRef<R, fal
     while (it.more()) {
         int q, k;
         const bool has = it.next(q, k);
-        const WaveChain<R> c{W, q, __shfl(P.at, q, WAVE), P.copy};
+        const WaveChain<R> c{W, q, __shfl(P.at, q, WAVE)};
         const int nq = __shfl(n, q, WAVE);
         if (has) {
             int v[5];
@@ -68,7 +68,7 @@ __device__ __forceinline__ void joint_move(const Tgt<R>& T, const PathRef<R, fal
     while (it.more()) {
         int q, k;
         const bool has = it.next(q, k);
-        const WaveChain<R> c{W, q, __shfl(P.at, q, WAVE), P.copy};
+        const WaveChain<R> c{W, q, __shfl(P.at, q, WAVE)};
         const int nq = __shfl(n, q, WAVE);
         if (has) {
             int v[5];

@@ -199,14 +199,6 @@ template <class R, bool LO> struct PathRef {
     }
 };
 
-template <class R> struct GlobalPath {
-    Vtx<R>* glb;
-    size_t C;
-    __device__ __forceinline__ Vtx<R> ld(int v) const { return glb[(size_t)v * C]; }
-    __device__ __forceinline__ V3<R> p(int v) const { return pos(ld(v)); }
-    __device__ __forceinline__ void stw(int, R) const {}
-};
-
 // Full log p of the path (FP64 sum of the factors), refreshing the cached
 // segment scattering depths; also returns the path length L and, where Sb is
 // given, the FP64 sum of the refreshed depths in path order.
@@ -633,8 +625,8 @@ namespace rj {
 // n does not change.  Returns the move kind, log A, the vertex and whether it
 // was accepted.
 template <class R, bool LO, int SAMP>
-__device__ __forceinline__ void perturb_move(const Tgt<R>& T, const PathRef<R, LO>& ps, const GlobalPath<R>& work,
-                                             Lane<R>& ln, const StepCtx& sc, uint64_t step, const uint32_t r[8], R logu,
+__device__ __forceinline__ void perturb_move(const Tgt<R>& T, const PathRef<R, LO>& ps, Lane<R>& ln,
+                                             const StepCtx& sc, uint64_t step, const uint32_t r[8], R logu,
                                              int& move, int& idx, int& accepted, R& logA) {
     const int n = ln.n;
     idx = -1;
@@ -775,7 +767,8 @@ __device__ __forceinline__ void perturb_move(const Tgt<R>& T, const PathRef<R, L
 // map.  Returns the move kind, log A, the segment or vertex (-1: the proposal
 // is invalid) and whether it was accepted.
 template <class R, bool LO, int SAMP>
-__device__ __forceinline__ void jump_move(const Tgt<R>& T, const PathRef<R, LO>& ps, Lane<R>& ln, const StepCtx& sc,
+__device__ __forceinline__ void jump_move(const Tgt<R>& T, const PathRef<R, LO>& ps, const WavePaths<R>& W, Lane<R>& ln,
+                                          const StepCtx& sc,
                                           const StepLoop& lp, const uint32_t r[8], R logu, int& move, int& idx,
                                           int& accepted, R& logA) {
     const int n = ln.n;
@@ -921,11 +914,13 @@ __device__ __forceinline__ void jump_move(const Tgt<R>& T, const PathRef<R, LO>&
     R dlw = (sc.logw && valid) ? (R)(birth ? dlw_b : dlw_d) : (R)0;
     R logAb = (ty - tx) + jac + dlw + lpdn - lpup;
     logA = valid ? (birth ? logAb : -logAb) : Mth<R>::ninf();
-    if (logu < logA) {
-        accepted = 1;
+    accepted = logu < logA ? 1 : 0;
+    constexpr bool TOGETHER = !LO && (SAMP == SAMP_TREE || SAMP == SAMP_JOINT);
+    if (TOGETHER) shift_shared<R>(W, birth, birth ? n - 1 : iA + 2, accepted ? n - 2 - iA + (birth ? 1 : 0) : 0);
+    if (accepted) {
         fold_run(ln, T.n0, sc, lp); // the steps spent at the old n
         const double dL = (double)sA.len + (double)sB.len - (double)AB.len;
-        ps.shift(birth, iA + 1, birth ? n - 1 : n - 2);
+        if (!TOGETHER) ps.shift(birth, iA + 1, birth ? n - 1 : n - 2);
         if (birth) ps.st(iB, Vtx<R>{fv.x, fv.y, fv.z, sB.tb});
         ps.stw(iA, birth ? sA.tb : AB.tb);
         ln.L += birth ? dL : -dL;
@@ -947,7 +942,7 @@ __device__ __forceinline__ void jump_move(const Tgt<R>& T, const PathRef<R, LO>&
 // counts are touched only there.
 template <class R, bool LO, int SAMP>
 __device__ __forceinline__ void perturb_step(const KArgs& a, const Tgt<R>& T, const PathRef<R, LO>& ps,
-                                             const GlobalPath<R>& work, Lane<R>& ln, const StepCtx& sc,
+                                             Lane<R>& ln, const StepCtx& sc,
                                              const StepLoop& lp, int c) {
     const uint64_t step = lp.step0 + (uint64_t)lp.s;
     uint32_t r[8];
@@ -956,7 +951,7 @@ __device__ __forceinline__ void perturb_step(const KArgs& a, const Tgt<R>& T, co
     const R logu = ln.live ? Mth<R>::log(unif<R>(r[1])) : -Mth<R>::ninf();
     int move, idx, accepted;
     R logA;
-    perturb_move<R, LO, SAMP>(T, ps, work, ln, sc, step, r, logu, move, idx, accepted, logA);
+    perturb_move<R, LO, SAMP>(T, ps, ln, sc, step, r, logu, move, idx, accepted, logA);
     if (lp.counted()) {
         ln.ap += (uint32_t)accepted;
         if constexpr (SAMP == SAMP_LOCAL) {
@@ -974,7 +969,7 @@ __device__ __forceinline__ void perturb_step(const KArgs& a, const Tgt<R>& T, co
 // end points are perturbed.
 template <class R>
 __device__ __forceinline__ void joint_step(const KArgs& a, const Tgt<R>& T, const PathRef<R, false>& ps,
-                                           const GlobalPath<R>& work, const WavePaths<R>& W, Lane<R>& ln,
+                                           const WavePaths<R>& W, Lane<R>& ln,
                                            const StepCtx& sc, const StepLoop& lp, int c) {
     const uint64_t step = lp.step0 + (uint64_t)lp.s;
     uint32_t r[8];
@@ -983,7 +978,7 @@ __device__ __forceinline__ void joint_step(const KArgs& a, const Tgt<R>& T, cons
     int move = MV_MALA, idx = 1 + pick(r[0], (uint32_t)(ln.n - 1)), accepted = 0;
     R logA = Mth<R>::ninf();
     const bool joint = idx != ln.n - 1;
-    if (!joint) perturb_move<R, false, SAMP_JOINT>(T, ps, work, ln, sc, step, r, logu, move, idx, accepted, logA);
+    if (!joint) perturb_move<R, false, SAMP_JOINT>(T, ps, ln, sc, step, r, logu, move, idx, accepted, logA);
     joint_move<R>(T, ps, W, ln, sc, step, joint && ln.live, logu, accepted, logA);
     if (lp.counted()) {
         ln.ap += (uint32_t)accepted;
@@ -1017,14 +1012,15 @@ __device__ __forceinline__ void tree_step(const KArgs& a, const Tgt<R>& T, const
 }
 
 template <class R, bool LO, int SAMP>
-__device__ __forceinline__ void jump_step(const KArgs& a, const Tgt<R>& T, const PathRef<R, LO>& ps, Lane<R>& ln,
+__device__ __forceinline__ void jump_step(const KArgs& a, const Tgt<R>& T, const PathRef<R, LO>& ps,
+                                          const WavePaths<R>& W, Lane<R>& ln,
                                           const StepCtx& sc, const StepLoop& lp, int c) {
     uint32_t r[8];
     draw8<SAMP>(sc, lp.step0 + (uint64_t)lp.s, r);
     const R logu = ln.live ? Mth<R>::log(unif<R>(r[1])) : -Mth<R>::ninf();
     int move, idx, accepted;
     R logA;
-    jump_move<R, LO, SAMP>(T, ps, ln, sc, lp, r, logu, move, idx, accepted, logA);
+    jump_move<R, LO, SAMP>(T, ps, W, ln, sc, lp, r, logu, move, idx, accepted, logA);
     if (lp.counted()) {
         const uint32_t ib = move == MV_BIRTH ? 1u : 0u, ac = (uint32_t)accepted;
         ln.ne += idx < 0 ? 1u : 0u;
@@ -1133,13 +1129,17 @@ template <class R, int MK, int SAMP, bool SL, bool EVEN> __device__ __forceinlin
     }
     T.sl = SL;
     if (!SL) T.l0.fsl = (R)0;
-    PathRef<R, false> ps{lslots, (Vtx<R>*)a.verts + c, a.V, C};
-    PathRef<R, true> pl{lslots, (Vtx<R>*)a.verts + c, a.V, C};
-    GlobalPath<R> work{a.work ? (Vtx<R>*)a.work + c : nullptr, C};
+    // vertices beyond the LDS slots: in place (a chain's lie n_chains apart), or
+    // chain after chain in the work buffer (move_in)
+    Vtx<R>* const own_verts = (Vtx<R>*)a.verts + c;
+    Vtx<R>* const far = SHARED ? (Vtx<R>*)a.work + (size_t)c * cap : own_verts;
+    const size_t far_stride = SHARED ? 1 : C;
+    PathRef<R, false> ps{lslots, far, a.V, far_stride};
+    PathRef<R, true> pl{lslots, far, a.V, far_stride};
     // stage the LDS part of the path
     const int nl0 = ln.n < a.V ? ln.n : a.V;
     if (!SHARED || good) {
-        for (int v = 0; v < nl0; ++v) lds_st<R>(ps.lds + v * WAVE, ps.glb[(size_t)v * C]);
+        for (int v = 0; v < nl0; ++v) lds_st<R>(ps.lds + v * WAVE, own_verts[(size_t)v * C]);
     } else {
         for (int v = 0; v < nl0; ++v) lds_st<R>(ps.lds + v * WAVE, Vtx<R>{(R)0, (R)0, (R)0, (R)0});
     }
@@ -1147,9 +1147,6 @@ template <class R, int MK, int SAMP, bool SL, bool EVEN> __device__ __forceinlin
     for (int v = nl0; v <= a.V && v < scan_slots<R, SAMP>(); ++v) pl.stw(v, (R)0);
     if (a.V < scan_slots<R, SAMP>()) pl.stw(a.V, (R)0);
 
-    ln.lp = full_logp(T, ps, ln.n, ln.L, &ln.S);
-    const bool healthy = good && isfinite(ln.lp);
-    if (good) put_status(a, c, healthy ? 0 : 1);
     WavePaths<R> W{};
     if constexpr (SHARED) {
         // proposals: the tile's columns from 32 on where the wave owns at most
@@ -1161,16 +1158,23 @@ template <class R, int MK, int SAMP, bool SL, bool EVEN> __device__ __forceinlin
                    : tiles + (size_t)(bs / WAVE) * (a.V + SLOT_PAD) * WAVE + (size_t)wave * a.Vy * WAVE;
         W.My = half ? a.V * (WAVE / 2) : a.Vy * WAVE;
         W.ymask = half ? ~(WAVE / 2 - 1) : 0;
-        W.gx = (Vtx<R>*)a.verts + c0;
-        W.part = (Vtx<R>*)a.work + (size_t)c0 * cap;
-        W.room = (a.C - c0 < a.cpw ? a.C - c0 : a.cpw) * cap;
+        W.width = a.C - c0 < a.cpw ? a.C - c0 : a.cpw;
+        W.per_width = (0x80000000u + (uint32_t)W.width - 1u) / (uint32_t)W.width;
+        W.rows = (Vtx<R>*)a.verts + c0;
+        W.far = (Vtx<R>*)a.work + (size_t)c0 * cap;
         W.C = C;
+        W.cap = cap;
         W.cpw = a.cpw;
         W.chain0 = (uint32_t)c0;
         W.lane = lane;
         W.run = run;
+        // (malformed chains keep all their vertices)
+        W.move_in(own && !good ? 0 : a.V, good ? ln.n : own ? cap : 0);
     }
 
+    ln.lp = full_logp(T, ps, ln.n, ln.L, &ln.S);
+    const bool healthy = good && isfinite(ln.lp);
+    if (good) put_status(a, c, healthy ? 0 : 1);
     StepCtx sc;
     sc.chain = (uint32_t)c;
     sc.k0 = (uint32_t)a.seed;
@@ -1221,20 +1225,20 @@ template <class R, int MK, int SAMP, bool SL, bool EVEN> __device__ __forceinlin
                 }
             }
             if constexpr (SAMP == SAMP_JOINT) {
-                for (; lp.s < end; ++lp.s) joint_step<R>(a, T, ps, work, W, ln, sc, lp, c);
+                for (; lp.s < end; ++lp.s) joint_step<R>(a, T, ps, W, ln, sc, lp, c);
             } else if (__all(ln.n < a.V)) {
-                for (; lp.s < end; ++lp.s) perturb_step<R, true, SAMP>(a, T, pl, work, ln, sc, lp, c);
+                for (; lp.s < end; ++lp.s) perturb_step<R, true, SAMP>(a, T, pl, ln, sc, lp, c);
             } else {
-                for (; lp.s < end; ++lp.s) perturb_step<R, false, SAMP>(a, T, ps, work, ln, sc, lp, c);
+                for (; lp.s < end; ++lp.s) perturb_step<R, false, SAMP>(a, T, ps, ln, sc, lp, c);
             }
             phase += m;
         } else {
             const int m = a.cycle_len - phase < left ? a.cycle_len - phase : left, end = lp.s + m;
             for (; lp.s < end; ++lp.s) {
                 if (__all(ln.n < a.V))
-                    jump_step<R, true, SAMP>(a, T, pl, ln, sc, lp, c);
+                    jump_step<R, true, SAMP>(a, T, pl, W, ln, sc, lp, c);
                 else
-                    jump_step<R, false, SAMP>(a, T, ps, ln, sc, lp, c);
+                    jump_step<R, false, SAMP>(a, T, ps, W, ln, sc, lp, c);
             }
             phase += m;
         }
@@ -1249,10 +1253,14 @@ template <class R, int MK, int SAMP, bool SL, bool EVEN> __device__ __forceinlin
     fold_run(ln, T.n0, sc, lp);
     // log p of the final path (refreshed once rather than tracked per step)
     if (healthy) ln.lp = full_logp(T, ps, ln.n, ln.L);
-    if (SHARED && !good) return;
+    if constexpr (SHARED) {
+        W.move_out(own && !good ? 0 : a.V, good ? ln.n : own ? cap : 0);
+        if (!good) return;
+        asm volatile("" : "+v"(c)); // (formed again here rather than kept through the steps)
+    }
     // write back the LDS part, the vertex count, log p and the statistics
     const int nw = ln.n < a.V ? ln.n : a.V;
-    for (int v = 0; v < nw; ++v) ps.glb[(size_t)v * C] = lds_ld<R>(ps.lds + v * WAVE);
+    for (int v = 0; v < nw; ++v) ((Vtx<R>*)a.verts + c)[(size_t)v * C] = lds_ld<R>(ps.lds + v * WAVE);
     a.n[c] = ln.n;
     a.logp[c] = ln.lp;
     if (healthy) {

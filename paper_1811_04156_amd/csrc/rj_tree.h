@@ -143,8 +143,8 @@ __device__ __forceinline__ void tree_move(const Tgt<R>& T, const PathRef<R, fals
     const int n = ln.n, lane = W.lane;
     const bool act = ln.live;
     const V3<R> x0 = ps.p(0), xe = ps.p(n - 1);
-    const WavePlaces P = wave_places<R>(W, ps, act ? n : 0);
-    const int at = P.at, copy = P.copy, all = P.all;
+    const WavePlaces P = wave_places<R>(W, act ? n : 0);
+    const int at = P.at, all = P.all;
     // end point: von Mises-Fisher step about the current sensor normal
     V3<R> yend;
     {
@@ -180,7 +180,7 @@ __device__ __forceinline__ void tree_move(const Tgt<R>& T, const PathRef<R, fals
         for (int base = 0; base < total; base += WAVE) {
             const int i = base + lane;
             const int q = __shfl(nth, (i >> d) & (WAVE - 1), WAVE);
-            const WaveChain<R> cq{W, q, __shfl(at, q, WAVE), copy};
+            const WaveChain<R> cq{W, q, __shfl(at, q, WAVE)};
             const int nq = __shfl(n, q, WAVE);
             const R sq = __shfl(sig, q, WAVE);
             // interval of node i mod 2^d: left or right halves from the root, by its bits
@@ -204,7 +204,7 @@ __device__ __forceinline__ void tree_move(const Tgt<R>& T, const PathRef<R, fals
     while (it.more()) {
         int q, k;
         const bool has = it.next(q, k);
-        const WaveChain<R> cq{W, q, __shfl(at, q, WAVE), copy};
+        const WaveChain<R> cq{W, q, __shfl(at, q, WAVE)};
         const int nq = __shfl(n, q, WAVE);
         if (has) {
             const int v[3] = {k, k + 1, k + 2 < nq ? k + 2 : k + 1};

@@ -261,6 +261,35 @@ def test_ordered_launch_leaves_no_trace(rj, prec, sampler, chains):
 
 
 @pytest.mark.parametrize("prec", ["f32", "f64"])
+@pytest.mark.parametrize("sampler,h", [(1, 0.01), (3, 0.3)])
+def test_far_vertices_of_shared_waves(rj, prec, sampler, h):
+    """The whole-path samplers keep the vertices beyond the LDS slots in the
+    work buffer and use the chains' own rows meanwhile.  Whatever the slots
+    (1: all but one vertex; 40: none; the last wave has 3 chains) and however
+    often the launches end, the paths are the same bit for bit, and a
+    malformed chain beside them keeps every row it has."""
+    w = W.single_target(1.5, 0.165, 0.05, 50.0, 0.9, chains=131, cap=40, burn_in=0, seed=54)
+    w.update(sampler=sampler, mala_h=h)
+    out = []
+    for v, parts in ((40, 1), (16, 1), (3, 4), (1, 2)):
+        s = rj.Sampler(w, precision=prec)
+        bad = torch.tensor([5, 64, 129], device=s.dev)
+        s.n[bad] = torch.tensor([0, 1, 41], dtype=s.n.dtype, device=s.dev)
+        marks = torch.arange(40 * 3 * 4, device=s.dev, dtype=s.verts.dtype).reshape(40, 3, 4) + 0.5
+        s.verts[:, bad] = marks
+        for _ in range(parts):
+            s.run(1200 // parts, block=64, v_lds=v)
+        torch.cuda.synchronize()
+        assert torch.equal(s.verts[:, bad], marks) and s.status[bad].tolist() == [1, 1, 1]
+        used = torch.arange(s.cap, device=s.dev)[:, None] < s.n
+        used[:, bad] = False
+        out.append((s.n.clone(), torch.where(used[..., None], s.verts[..., :3], 0.0).clone()))
+    assert out[0][0].max() > 17
+    for n, x in out[1:]:
+        assert torch.equal(n, out[0][0]) and torch.equal(x, out[0][1])
+
+
+@pytest.mark.parametrize("prec", ["f32", "f64"])
 def test_bridge_whatever_the_order_and_number_of_chains(rj, prec):
     """The bridge's waves share the vertices of 8 chains in a small launch and
     of 64 in a large one, target by target: the same paths grouped by target,
