@@ -126,9 +126,10 @@ typedef struct {
  * verts[v * n_chains + c], four values (x, y, z, w) of the precision's type:
  * x, y, z relative to the chain's source (f_0 = 0), w is library-owned scratch
  * (the scattering depth of the segment leaving the vertex).  Slots v >= n[c]
- * hold nothing (RJPATH_MALA and RJPATH_TREE runs write there).  logp[c] receives log p of the final path; status[c] is 0 for a
- * healthy chain and 1 if its starting path had zero or non-finite density
- * (such a chain is not moved and adds nothing to the statistics).
+ * hold nothing (RJPATH_MALA and RJPATH_TREE runs write there).  logp[c]
+ * receives log p of the final path; status[c] is 0 for a healthy chain and 1 if
+ * its starting path had zero or non-finite density (such a chain is not moved
+ * and adds nothing to the statistics).
  * work: scratch of the size of verts, contents of no meaning between the calls
  * (required for RJPATH_MALA and RJPATH_TREE, else may be NULL). */
 typedef struct {

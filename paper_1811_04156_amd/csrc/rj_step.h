@@ -112,17 +112,13 @@ template <class R, bool LO> struct PathRef {
     // and past the last one moves that one again: the wave waits once per
     // SHIFT vertices of its longest shift.  (A loop for each, four vertices at
     // a time and then one at a time: a jump step of 65,536 homogeneous chains
-    // took 3.55 us and takes 3.05.  With paths beyond the LDS slots the shared
-    // loop was slower, 76 against 65 us per jump step of the two-region test.)
+    // took 3.55 us and takes 3.05.)
     static constexpr int SHIFT = 6;
     __device__ __forceinline__ void shift(bool up, int lo, int hi) const {
-        if (!LO) {
-            if (up) shift_up(lo, hi);
-            else shift_down(lo, hi);
-            return;
-        }
+        if (!LO && up) far_up(lo, hi);
+        const int top = LO || hi < V - 2 ? hi : V - 2; // the moves that stay in LDS
         const int dir = up ? -1 : 1;
-        for (int left = hi - lo, v = up ? hi : lo + 1; left >= 0; left -= SHIFT, v += dir * SHIFT) {
+        for (int left = top - lo, v = up ? top : lo + 1; left >= 0; left -= SHIFT, v += dir * SHIFT) {
             L4<R> x[SHIFT];
             LdsPtr<R> at[SHIFT];
 #pragma unroll
@@ -132,70 +128,40 @@ template <class R, bool LO> struct PathRef {
 #pragma unroll
             for (int i = 0; i < SHIFT; ++i) at[i][-dir * WAVE] = x[i];
         }
+        if (!LO && !up) far_down(lo, hi);
     }
-    // The vertex shifts of an accepted jump where some lie in HBM, split at the
-    // boundary into loops that touch one memory each (no per-vertex branch on the
-    // address space), each reading four vertices before writing them (one
-    // latency per four): slots lo..hi move one slot up (from the top) ...
-    __device__ __forceinline__ void lds_up(int& v, int lo) const {
-        for (; v - 3 >= lo; v -= 4) {
-            const L4<R> a = lds[v * WAVE], b = lds[(v - 1) * WAVE], c = lds[(v - 2) * WAVE], d = lds[(v - 3) * WAVE];
-            lds[(v + 1) * WAVE] = a;
-            lds[v * WAVE] = b;
-            lds[(v - 1) * WAVE] = c;
-            lds[(v - 2) * WAVE] = d;
-        }
-        for (; v >= lo; --v) lds[(v + 1) * WAVE] = lds[v * WAVE];
-    }
-    __device__ __forceinline__ void shift_up(int lo, int hi) const {
+    // The moves to and beyond slot V, one way each (in one loop for both, with
+    // the LDS ones, a jump step of the two-region test took 76 us instead of 65).
+    __device__ __forceinline__ void far_up(int lo, int hi) const {
         int v = hi;
-        {
-            L4<R>* const g = (L4<R>*)glb;
-            for (; v - 3 >= lo && v - 3 >= V; v -= 4) {
-                const L4<R> a = g[(size_t)v * C], b = g[(size_t)(v - 1) * C], c = g[(size_t)(v - 2) * C],
-                            d = g[(size_t)(v - 3) * C];
-                g[(size_t)(v + 1) * C] = a;
-                g[(size_t)v * C] = b;
-                g[(size_t)(v - 1) * C] = c;
-                g[(size_t)(v - 2) * C] = d;
-            }
-            for (; v >= lo && v >= V; --v) g[(size_t)(v + 1) * C] = g[(size_t)v * C];
-            if (v >= lo && v == V - 1) {
-                g[(size_t)V * C] = lds[v * WAVE];
-                --v;
-            }
+        L4<R>* const g = (L4<R>*)glb;
+        for (; v - 3 >= lo && v - 3 >= V; v -= 4) {
+            const L4<R> a = g[(size_t)v * C], b = g[(size_t)(v - 1) * C], c = g[(size_t)(v - 2) * C],
+                        d = g[(size_t)(v - 3) * C];
+            g[(size_t)(v + 1) * C] = a;
+            g[(size_t)v * C] = b;
+            g[(size_t)(v - 1) * C] = c;
+            g[(size_t)(v - 2) * C] = d;
         }
-        lds_up(v, lo);
+        for (; v >= lo && v >= V; --v) g[(size_t)(v + 1) * C] = g[(size_t)v * C];
+        if (v >= lo && v == V - 1) g[(size_t)V * C] = lds[v * WAVE];
     }
-    // ... or slots lo+1..hi+1 move one slot down (from the bottom).
-    __device__ __forceinline__ void shift_down(int lo, int hi) const {
-        int v = lo;
-        const int top = hi < V - 2 ? hi : V - 2; // the moves that stay in LDS
-        for (; v + 3 <= top; v += 4) {
-            const L4<R> a = lds[(v + 1) * WAVE], b = lds[(v + 2) * WAVE], c = lds[(v + 3) * WAVE],
-                        d = lds[(v + 4) * WAVE];
-            lds[v * WAVE] = a;
-            lds[(v + 1) * WAVE] = b;
-            lds[(v + 2) * WAVE] = c;
-            lds[(v + 3) * WAVE] = d;
+    __device__ __forceinline__ void far_down(int lo, int hi) const {
+        int v = lo > V - 1 ? lo : V - 1;
+        L4<R>* const g = (L4<R>*)glb;
+        if (v <= hi && v == V - 1) {
+            lds[v * WAVE] = g[(size_t)V * C];
+            ++v;
         }
-        for (; v <= top; ++v) lds[v * WAVE] = lds[(v + 1) * WAVE];
-        {
-            L4<R>* const g = (L4<R>*)glb;
-            if (v <= hi && v == V - 1) {
-                lds[v * WAVE] = g[(size_t)V * C];
-                ++v;
-            }
-            for (; v + 3 <= hi; v += 4) {
-                const L4<R> a = g[(size_t)(v + 1) * C], b = g[(size_t)(v + 2) * C], c = g[(size_t)(v + 3) * C],
-                            d = g[(size_t)(v + 4) * C];
-                g[(size_t)v * C] = a;
-                g[(size_t)(v + 1) * C] = b;
-                g[(size_t)(v + 2) * C] = c;
-                g[(size_t)(v + 3) * C] = d;
-            }
-            for (; v <= hi; ++v) g[(size_t)v * C] = g[(size_t)(v + 1) * C];
+        for (; v + 3 <= hi; v += 4) {
+            const L4<R> a = g[(size_t)(v + 1) * C], b = g[(size_t)(v + 2) * C], c = g[(size_t)(v + 3) * C],
+                        d = g[(size_t)(v + 4) * C];
+            g[(size_t)v * C] = a;
+            g[(size_t)(v + 1) * C] = b;
+            g[(size_t)(v + 2) * C] = c;
+            g[(size_t)(v + 3) * C] = d;
         }
+        for (; v <= hi; ++v) g[(size_t)v * C] = g[(size_t)(v + 1) * C];
     }
 };
 
