@@ -321,18 +321,21 @@ int device_cus() {
 // Chains per wave of the samplers whose waves share whole-path moves: as few
 // (from 64 down to 8) as keep the launch within so many waves per SIMD, so that
 // the shared moves use more of the chip.  Two are resident.  Tree moves: two
-// (200 steps of 20,000, 50,000 and 100,000 chains of the ragged batch: 1.34,
-// 2.01 and 3.07 ms within two, 1.61, 2.12 and 2.59 within four; the jumps and
+// (200 steps of 20,000, 30,000 and 50,000 chains of the ragged batch: 1.25,
+// 1.31 and 1.85 ms within two, 1.55, 1.89 and 1.96 within four; the jumps and
 // perturbations cost by the wave).  Joint Langevin moves, which are more of
 // the run: four (20,000, 50,001 and 100,000 chains: 2.53, 4.50 and 8.57 ms
 // within two, 2.19, 3.11 and 4.80 within four, 2.18, 4.36 and 5.54 within
-// eight).
+// eight).  Twice as many before a wave takes all 64, which leaves no lane to
+// deal out where its targets differ (100,000 and 131,072 chains of tree moves
+// with 64 and 32 per wave: 2.80 and 2.33 ms, 2.98 and 2.64; 200,000 of joint
+// moves: 8.65 and 8.01; 262,144 of tree moves, beyond the line: 4.28 and 5.37).
 bool shares_moves(int sampler) { return sampler == RJPATH_TREE || sampler == RJPATH_MALA; }
 
 int shared_cpw(int sampler, int n_chains) {
     const long long waves = (sampler == RJPATH_MALA ? 4LL : 2LL) * 4 * device_cus();
     int cpw = 8;
-    while (cpw < 64 && (long long)n_chains > waves * cpw) cpw *= 2;
+    while (cpw < 64 && (long long)n_chains > (cpw == 32 ? 2 : 1) * waves * cpw) cpw *= 2;
     return cpw;
 }
 

@@ -211,13 +211,13 @@ def test_tree_moves_shared_by_any_number_of_chains(rj):
 def test_joint_moves_shared_by_any_number_of_chains(rj, run):
     """A wave of the joint Langevin sampler owns 64 chains of a large launch
     and 8 of a small one, whose lanes without a chain help its targets.  The
-    first 5003 chains of a 140,001-chain launch take the paths that they take
+    first 5003 chains of a 262,201-chain launch take the paths that they take
     as a launch of their own, with ``run`` neighbouring chains per target
     (waves of up to 64 targets; of one or two of them).  The statistics' sums
     differ by their rounding (1e-12)."""
-    w = W.layered_pairs(seed=8, pairs=70, chains=140_001, cap=40, n_layers=12, dz=4.0, dmin=4.0, dmax=25.0)
+    w = W.layered_pairs(seed=8, pairs=70, chains=262_201, cap=40, n_layers=12, dz=4.0, dmin=4.0, dmax=25.0)
     w.update(sampler=1, mala_h=0.01, burn_in=0, sigma=2.0)
-    w["c_target"] = (np.arange(140_001) // run % 70).astype(np.int32)
+    w["c_target"] = (np.arange(262_201) // run % 70).astype(np.int32)
     out = []
     for ww in (w, W.subset_chains(w, 5003)):
         s = rj.Sampler(ww, precision="f32")
