@@ -184,15 +184,16 @@ __device__ __forceinline__ void block_sums_end(const BlockSums& b, double* out, 
 // the lanes beside it (windows of 62), so that the map's FP64 sine, cosine or
 // arc tangent is formed once per vertex and no lane waits for the longest
 // path.  One lane per chain, mapping every vertex twice, took 545 us for the
-// two-region test's 65,536 chains of 32 vertices; now about 150 us.
+// two-region test's 65,536 chains of 32 vertices; now 180 us.
 // ---------------------------------------------------------------------------
 template <class R> __device__ __forceinline__ V3<R> lane_v3(V3<R> p, int from) {
     return {__shfl(p.x, from, WAVE), __shfl(p.y, from, WAVE), __shfl(p.z, from, WAVE)};
 }
 
 template <class R>
-__global__ void __launch_bounds__(BLK, sizeof(R) == 4 ? 2 : 1) yield_kernel(KArgs a, int n_pairs, const int32_t* pairs, const int32_t* role,
-                                                    int groups, double* acc, double* logr, int cpw, int strip) {
+__global__ void __launch_bounds__(BLK, sizeof(R) == 4 ? 2 : 1)
+    yield_kernel(KArgs a, int n_pairs, const int32_t* pairs, const int32_t* role, int groups, double* acc, double* logr,
+                 int cpw, int strip) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ double tab[2 * 64 * 2];
     __shared__ double own[BLK], img[BLK];
@@ -344,13 +345,24 @@ __global__ void __launch_bounds__(BLK, sizeof(R) == 4 ? 2 : 1) yield_kernel(KArg
 // Path-length histogram: hist[t * (bins + 1) + b] += 1 / w(n) for
 // b = floor((L - l0) / width) in [0, bins), and hist[t * (bins + 1) + bins]
 // += 1 / w(n) for every sample (the normaliser).  L is summed in FP64.
+//
+// A chain's segments are split over 64 / cpw lanes, lane p * cpw + q taking
+// part p of the wave's chain q (rows of whole cache lines).  The rows come from
+// HBM one latency per four, so few chains with long paths need more waves than
+// one lane each gives; a block keeps 256 chains, so that its table is added
+// to the result as seldom.  The two-region test's 65,536 chains of 32 vertices:
+// 70 us with one lane each, 33 with four (the paths' 34 MB take 7 at the rate
+// of a large copy).
 // ---------------------------------------------------------------------------
+constexpr int LHIST_PARTS = 4;
+
 template <class R>
-__global__ void __launch_bounds__(BLK) lhist_kernel(KArgs a, int bins, double l0, double width, double* hist,
-                                                    int use_lds) {
+__global__ void __launch_bounds__(BLK * LHIST_PARTS) lhist_kernel(KArgs a, int bins, double l0, double width,
+                                                                  double* hist, int use_lds, int cpw) {
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ int smin[BLK / 64], smax[BLK / 64];
-    const int c = blockIdx.x * BLK + threadIdx.x;
+    __shared__ int smin[BLK * LHIST_PARTS / 64], smax[BLK * LHIST_PARTS / 64];
+    const int lane = threadIdx.x % WAVE, part = lane / cpw, parts = WAVE / cpw;
+    const int c = (blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE) * cpw + lane % cpw;
     int t = -1, n = 0;
     if (c < a.C) {
         t = a.target[c];
@@ -359,23 +371,28 @@ __global__ void __launch_bounds__(BLK) lhist_kernel(KArgs a, int bins, double l0
     }
     double L = 0;
     if (t >= 0) {
-        // four rows in flight (one at a time, each step waited for its row)
-        const Vtx<R>* base = (const Vtx<R>*)a.verts + c;
-        D3 p = vload(base, (size_t)a.C, 0);
-        for (int v = 1; v < n; v += 4) {
-            D3 q[4];
+        // segments first .. last - 1, four rows in flight
+        const int each = (n - 1 + parts - 1) / parts, first = part * each, last = min(first + each, n - 1);
+        if (first < last) {
+            const Vtx<R>* base = (const Vtx<R>*)a.verts + c;
+            D3 p = vload(base, (size_t)a.C, first);
+            for (int v = first + 1; v <= last; v += 4) {
+                D3 q[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (v + i < n) q[i] = vload(base, (size_t)a.C, v + i);
+                for (int i = 0; i < 4; ++i)
+                    if (v + i <= last) q[i] = vload(base, (size_t)a.C, v + i);
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (v + i < n) {
-                    const D3 d = q[i] - p;
-                    L += sqrt(dot(d, d));
-                    p = q[i];
-                }
+                for (int i = 0; i < 4; ++i)
+                    if (v + i <= last) {
+                        const D3 d = q[i] - p;
+                        L += sqrt(dot(d, d));
+                        p = q[i];
+                    }
+            }
         }
     }
+    for (int m = cpw; m < WAVE; m *= 2) L += __shfl_xor(L, m, WAVE);
+    if (part > 0) t = -1; // (the first part's lane counts the chain)
     const int nent = bins + 1;
     BlockSums b = block_sums_begin(t, use_lds ? (double*)smem : nullptr, nent, smin, smax);
     if (t >= 0) {
@@ -421,14 +438,18 @@ hipError_t launch_yield(const KArgs& a, int n_pairs, const int32_t* pairs, const
 
 hipError_t launch_lhist(const KArgs& a, int bins, double l0, double width, double* hist, hipStream_t s) {
     const int grid = (a.C + BLK - 1) / BLK;
+    // lanes per chain: as many as keep the launch within eight waves per SIMD
+    int parts = LHIST_PARTS;
+    while (parts > 1 && (long long)a.C * parts > 32LL * compute_units() * WAVE) parts /= 2;
+    const dim3 block(BLK * parts);
     const size_t lds = 2 * sizeof(double) * ((size_t)bins + 1);
     const int use = lds <= 64 * 1024;
     if (a.prec == RJPATH_F64)
-        hipLaunchKernelGGL(lhist_kernel<double>, dim3(grid), dim3(BLK), use ? lds : 0, s, a, bins, l0, width, hist,
-                           use);
+        hipLaunchKernelGGL(lhist_kernel<double>, dim3(grid), block, use ? lds : 0, s, a, bins, l0, width, hist, use,
+                           WAVE / parts);
     else
-        hipLaunchKernelGGL(lhist_kernel<float>, dim3(grid), dim3(BLK), use ? lds : 0, s, a, bins, l0, width, hist,
-                           use);
+        hipLaunchKernelGGL(lhist_kernel<float>, dim3(grid), block, use ? lds : 0, s, a, bins, l0, width, hist, use,
+                           WAVE / parts);
     return hipGetLastError();
 }
 

@@ -324,3 +324,23 @@ def test_bridge_whatever_the_order_and_number_of_chains(rj, prec):
     for x in out[1:]:
         assert np.allclose(out[0], x, rtol=1e-11, atol=1e-11, equal_nan=True)
     assert np.isfinite(out[0]).sum() > C // 2
+
+
+@pytest.mark.parametrize("chains", [1, 130, 131_073, 262_145])
+def test_length_hist_whatever_the_lanes_per_chain(rj, chains):
+    """Four lanes sum a chain's segments up to 131,072 chains, two up to
+    262,144, one beyond.  The bins equal a histogram of the state's own lengths
+    (a length within 1e-9 of an edge could fall on either side of it: none
+    does)."""
+    w = W.single_target(1.5, 0.165, 0.05, 50.0, 0.9, chains=chains, cap=24, burn_in=0, seed=55)
+    s = rj.Sampler(w, precision="f32")
+    s.run(300)
+    torch.cuda.synchronize()
+    h = s.length_hist(30, 1.0, 0.1).cpu().numpy().ravel()
+    used = torch.arange(1, s.cap, device=s.dev)[:, None] < s.n
+    x = s.verts[..., :3].double()
+    L = torch.where(used, (x[1:] - x[:-1]).norm(dim=-1), 0.0).sum(0).cpu().numpy()
+    at = (L - 1.0) / 0.1
+    assert np.abs(at - np.round(at)).min() > 1e-9
+    want = np.bincount(np.floor(at[(at >= 0) & (at < 30)]).astype(int), minlength=30)
+    assert np.array_equal(h[:30], want) and h[30] == chains
