@@ -41,26 +41,24 @@ namespace rj {
 // per SIMD a wave owns fewer than 64 chains (cpw), so that more waves share the
 // work.
 // ---------------------------------------------------------------------------
-// frame (e2, e3) of interval (k, l) of a path: root -> onb of the axis;
-// otherwise from the parent interval (kp, lp) and its vertex fp.  Both are
-// formed and one is selected by value (a choice between output references
-// would become a dynamically indexed stack slot).
+// frame (e2, e3) of interval (k, l) of a path: root (uniform over the wave) ->
+// onb of the axis; otherwise from the parent interval (kp, lp) and its vertex fp.
 template <class R> struct Frame2 {
     V3<R> e2, e3;
 };
 
 template <class R>
 __device__ __forceinline__ Frame2<R> tree_frame(bool root, V3<R> e1, V3<R> fkp, V3<R> flp, V3<R> fp) {
-    V3<R> r2, r3;
-    onb(e1, r2, r3);
-    const V3<R> ep = unit_dir(fkp, flp);
-    const V3<R> g = fp - fkp;
-    const V3<R> c = {ep.y * g.z - ep.z * g.y, ep.z * g.x - ep.x * g.z, ep.x * g.y - ep.y * g.x};
-    const V3<R> c3 = Mth<R>::rsqrt(dot(c, c)) * c;
-    const V3<R> c2 = {c3.y * e1.z - c3.z * e1.y, c3.z * e1.x - c3.x * e1.z, c3.x * e1.y - c3.y * e1.x};
     Frame2<R> f;
-    f.e2 = {root ? r2.x : c2.x, root ? r2.y : c2.y, root ? r2.z : c2.z};
-    f.e3 = {root ? r3.x : c3.x, root ? r3.y : c3.y, root ? r3.z : c3.z};
+    if (root) {
+        onb(e1, f.e2, f.e3);
+    } else {
+        const V3<R> ep = unit_dir(fkp, flp);
+        const V3<R> g = fp - fkp;
+        const V3<R> c = {ep.y * g.z - ep.z * g.y, ep.z * g.x - ep.x * g.z, ep.x * g.y - ep.y * g.x};
+        f.e3 = Mth<R>::rsqrt(dot(c, c)) * c;
+        f.e2 = {f.e3.y * e1.z - f.e3.z * e1.y, f.e3.z * e1.x - f.e3.x * e1.z, f.e3.x * e1.y - f.e3.y * e1.x};
+    }
     return f;
 }
 
