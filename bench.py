@@ -59,6 +59,7 @@ FLOP_JUMP_PER_VERTEX = 2.0
 # the one recorded with it.
 KERNEL_SOURCES = ["include/rjpath.h", "paper_1811_04156_amd/csrc/rj_internal.h",
                   "paper_1811_04156_amd/csrc/rj_device.h", "paper_1811_04156_amd/csrc/rj_step.h",
+                  "paper_1811_04156_amd/csrc/rj_wave.h", "paper_1811_04156_amd/csrc/rj_paths.h",
                   "paper_1811_04156_amd/csrc/rj_run.h", "paper_1811_04156_amd/csrc/rj_run_f32.hip"]
 TRAFFIC_PROFILE = "profiles/run_kernel_lay_f32_layered_batch_traffic.md"
 

@@ -61,7 +61,8 @@ template <class R> struct WavePaths {
             L4<R> g[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                if (v + i * step < end) g[i] = *(const L4<R>*)(IN ? row + (size_t)(v + i * step) * C : mine + (v + i * step));
+                if (v + i * step < end)
+                    g[i] = *(const L4<R>*)(IN ? row + (size_t)(v + i * step) * C : mine + (v + i * step));
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 if (v + i * step < end) *(L4<R>*)(IN ? mine + (v + i * step) : row + (size_t)(v + i * step) * C) = g[i];

@@ -591,9 +591,9 @@ namespace rj {
 // n does not change.  Returns the move kind, log A, the vertex and whether it
 // was accepted.
 template <class R, bool LO, int SAMP>
-__device__ __forceinline__ void perturb_move(const Tgt<R>& T, const PathRef<R, LO>& ps, Lane<R>& ln,
-                                             const StepCtx& sc, uint64_t step, const uint32_t r[8], R logu,
-                                             int& move, int& idx, int& accepted, R& logA) {
+__device__ __forceinline__ void perturb_move(const Tgt<R>& T, const PathRef<R, LO>& ps, Lane<R>& ln, const StepCtx& sc,
+                                             uint64_t step, const uint32_t r[8], R logu, int& move, int& idx,
+                                             int& accepted, R& logA) {
     const int n = ln.n;
     idx = -1;
     accepted = 0;
@@ -734,9 +734,8 @@ __device__ __forceinline__ void perturb_move(const Tgt<R>& T, const PathRef<R, L
 // is invalid) and whether it was accepted.
 template <class R, bool LO, int SAMP>
 __device__ __forceinline__ void jump_move(const Tgt<R>& T, const PathRef<R, LO>& ps, const WavePaths<R>& W, Lane<R>& ln,
-                                          const StepCtx& sc,
-                                          const StepLoop& lp, const uint32_t r[8], R logu, int& move, int& idx,
-                                          int& accepted, R& logA) {
+                                          const StepCtx& sc, const StepLoop& lp, const uint32_t r[8], R logu, int& move,
+                                          int& idx, int& accepted, R& logA) {
     const int n = ln.n;
     idx = -1;
     accepted = 0;
@@ -908,8 +907,7 @@ __device__ __forceinline__ void jump_move(const Tgt<R>& T, const PathRef<R, LO>&
 // counts are touched only there.
 template <class R, bool LO, int SAMP>
 __device__ __forceinline__ void perturb_step(const KArgs& a, const Tgt<R>& T, const PathRef<R, LO>& ps,
-                                             Lane<R>& ln, const StepCtx& sc,
-                                             const StepLoop& lp, int c) {
+                                             Lane<R>& ln, const StepCtx& sc, const StepLoop& lp, int c) {
     const uint64_t step = lp.step0 + (uint64_t)lp.s;
     uint32_t r[8];
     draw8<SAMP>(sc, step, r);
@@ -935,8 +933,8 @@ __device__ __forceinline__ void perturb_step(const KArgs& a, const Tgt<R>& T, co
 // end points are perturbed.
 template <class R>
 __device__ __forceinline__ void joint_step(const KArgs& a, const Tgt<R>& T, const PathRef<R, false>& ps,
-                                           const WavePaths<R>& W, Lane<R>& ln,
-                                           const StepCtx& sc, const StepLoop& lp, int c) {
+                                           const WavePaths<R>& W, Lane<R>& ln, const StepCtx& sc, const StepLoop& lp,
+                                           int c) {
     const uint64_t step = lp.step0 + (uint64_t)lp.s;
     uint32_t r[8];
     draw8<SAMP_JOINT>(sc, step, r);
@@ -979,8 +977,8 @@ __device__ __forceinline__ void tree_step(const KArgs& a, const Tgt<R>& T, const
 
 template <class R, bool LO, int SAMP>
 __device__ __forceinline__ void jump_step(const KArgs& a, const Tgt<R>& T, const PathRef<R, LO>& ps,
-                                          const WavePaths<R>& W, Lane<R>& ln,
-                                          const StepCtx& sc, const StepLoop& lp, int c) {
+                                          const WavePaths<R>& W, Lane<R>& ln, const StepCtx& sc, const StepLoop& lp,
+                                          int c) {
     uint32_t r[8];
     draw8<SAMP>(sc, lp.step0 + (uint64_t)lp.s, r);
     const R logu = ln.live ? Mth<R>::log(unif<R>(r[1])) : -Mth<R>::ninf();

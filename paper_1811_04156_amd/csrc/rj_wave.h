@@ -86,8 +86,8 @@ __device__ __forceinline__ LaneRun share_lanes(int lane, int cpw, int items, int
     int hlo = cpw & 63, helpers = 0;
     if (cpw < 64) {
         const int end = wave_prefix(lane < cpw ? items : 0);
-        const int all = __shfl(end, cpw - 1, 64), last = __shfl(end, lo + own - 1, 64), first = __shfl(end, lo > 0 ? lo - 1 : 0, 64);
-        const int mine = last - (lo > 0 ? first : 0);
+        const int all = __shfl(end, cpw - 1, 64), last = __shfl(end, lo + own - 1, 64);
+        const int first = __shfl(end, lo > 0 ? lo - 1 : 0, 64), mine = last - (lo > 0 ? first : 0);
         // lanes that the run lacks, scaled by all items; in its first lane
         const bool leads = lane < cpw && lane == lo;
         const float lacks = leads ? fmaxf((float)mine * 64.0f / (float)all - (float)own, 0.0f) : 0.0f;
@@ -158,8 +158,8 @@ struct WaveItems {
         const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane(wave_prefix((int)(uint32_t)bit), 63);
         const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane(wave_prefix((int)(uint32_t)(bit >> 32)), 63);
         mask = ((uint64_t)hi << 32 | lo) & run.mask();
-        const int upto = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u)) +
-                         (int)((mask >> lane) & 1u);
+        const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+        const int upto = (int)below + (int)((mask >> lane) & 1u);
         q = __shfl(nth, (seen + upto - 1) & 63, 64);
         const int i = base + run.place(lane);
         k = i - __shfl(first, q, 64);
