@@ -354,9 +354,9 @@ int shared_cpw(int sampler, int n_chains) {
 //    (eight waves) share a CU's LDS, so that two waves are resident per SIMD
 //    (the step kernel's register use allows two).
 //  - the whole-path samplers: the same with their waves counted (shared_cpw
-//    chains each).  (Halving the slots so that the proposals of 64-chain waves fit LDS too
-//    made the tree step itself no faster, 122 against 113 us for 262,144 chains
-//    of the ragged batch, and the jumps slower.)
+//    chains each).  (Halving the slots so that the proposals of 64-chain waves
+//    fit LDS too made the tree step itself no faster, 122 against 113 us for
+//    262,144 chains of the ragged batch then, and the jumps slower.)
 void default_launch(const rjpath_chains* c, size_t tab_bytes, int sampler, int& block, int& V) {
     const int cap = c->cap;
     const int cus = device_cus();
