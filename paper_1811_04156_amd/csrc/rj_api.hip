@@ -320,7 +320,11 @@ int device_cus() {
 
 // Chains per wave of the samplers whose waves share whole-path moves: as few
 // (from 64 down to 8) as keep the launch within so many waves per SIMD, so that
-// the shared moves use more of the chip.  Two are resident.  Tree moves: two
+// the shared moves use more of the chip, and down to 1 within one wave per SIMD
+// (the two-region test with 500 chains, 50 steps: 1.28 ms with 8 per wave, 0.72
+// with 1; 300 chains of the ragged batch, 200 steps: tree moves 0.75 and 0.68,
+// joint moves 1.14 and 0.91; 8,000 chains of tree moves, beyond the line: 0.97
+// with 8, 1.11 with 4).  Two are resident.  Tree moves: two
 // (200 steps of 20,000, 30,000 and 50,000 chains of the ragged batch: 1.25,
 // 1.31 and 1.85 ms within two, 1.55, 1.89 and 1.96 within four; the jumps and
 // perturbations cost by the wave).  Joint Langevin moves, which are more of
@@ -334,8 +338,9 @@ bool shares_moves(int sampler) { return sampler == RJPATH_TREE || sampler == RJP
 
 int shared_cpw(int sampler, int n_chains) {
     const long long waves = (sampler == RJPATH_MALA ? 4LL : 2LL) * 4 * device_cus();
-    int cpw = 8;
-    while (cpw < 64 && (long long)n_chains > (cpw == 32 ? 2 : 1) * waves * cpw) cpw *= 2;
+    int cpw = 1;
+    while (cpw < 8 && (long long)n_chains > 4LL * device_cus() * cpw) cpw *= 2;
+    while (cpw >= 8 && cpw < 64 && (long long)n_chains > (cpw == 32 ? 2 : 1) * waves * cpw) cpw *= 2;
     return cpw;
 }
 

@@ -61,7 +61,7 @@ struct KArgs {
     int32_t even;    // every medium has several layers, evenly spaced
     int32_t has_sl;  // some layer has a Rayleigh-like fraction f_SL > 0
     size_t tab_bytes; // LDS bytes of the staged tables (0: read them from HBM)
-    // whole-path samplers: chains per wave (64, 32, 16 or 8) and LDS slots of a proposal (64 chains per wave only)
+    // whole-path samplers: chains per wave (a power of two up to 64) and LDS slots of a proposal (64 chains per wave only)
     int32_t cpw, Vy;
     int32_t ordered; // waves whose order the status words hold (launch_order), or 0
     // run

@@ -290,6 +290,29 @@ def test_far_vertices_of_shared_waves(rj, prec, sampler, h):
 
 
 @pytest.mark.parametrize("prec", ["f32", "f64"])
+@pytest.mark.parametrize("sampler,h", [(1, 0.01), (3, 0.3)])
+def test_few_chains_of_shared_moves(rj, prec, sampler, h):
+    """Small launches of the whole-path samplers give each chain, or 2, 4 or 8,
+    a wave.  The first chains of a 70,001-chain launch (32 per wave) take the
+    paths that they take as launches of 1, 63, 1300, 3001 and 9001 chains."""
+    w = W.layered_pairs(seed=10, pairs=50, chains=70_001, cap=40, n_layers=12, dz=4.0, dmin=4.0, dmax=25.0)
+    w.update(sampler=sampler, mala_h=h, burn_in=0, sigma=2.0)
+    w["c_target"] = (np.arange(70_001) % 50).astype(np.int32)
+    state = []
+    for k in (70_001, 1, 63, 1300, 3001, 9001):
+        s = rj.Sampler(W.subset_chains(w, k), precision=prec)
+        s.run(100)
+        torch.cuda.synchronize()
+        used = torch.arange(s.cap, device=s.dev)[:, None] < s.n
+        state.append((s.n.clone(), torch.where(used[..., None], s.verts[..., :3], 0.0).clone(), s.stats.clone()))
+    n, x, st = state[0]
+    for a, b, c in state[1:]:
+        k = len(a)
+        assert torch.equal(a, n[:k]) and torch.equal(b, x[:, :k])
+        assert torch.allclose(c, st[:k], rtol=1e-12)
+
+
+@pytest.mark.parametrize("prec", ["f32", "f64"])
 def test_bridge_whatever_the_order_and_number_of_chains(rj, prec):
     """The bridge's waves share the vertices of 8 chains in a small launch and
     of 64 in a large one, target by target: the same paths grouped by target,
