@@ -220,7 +220,8 @@ __global__ void __launch_bounds__(BLK, sizeof(R) == 4 ? 2 : 1)
             }
         }
     }
-    // log p of the path; log p of its image +- log |dT/dx|; left T's domain
+    // log p of the path; log p of its image +- log |dT/dx|; 1: outside T's
+    // domain (log r = -inf, whatever the densities), 2: no map for the pair
     double* const sown = own + wave * WAVE;
     double* const simg = img + wave * WAVE;
     int* const sout = outside + wave * WAVE;
@@ -310,9 +311,8 @@ __global__ void __launch_bounds__(BLK, sizeof(R) == 4 ? 2 : 1)
                             R tb;
                             term += walk_term(T, nq, k, e, e1, e2, tb);
                         }
-                        if (w == 0 && !M.ok) term = __builtin_nan("");
                         atomicAdd((w == 0 ? sown : simg) + q, term);
-                        if (!in) sout[q] = 1;
+                        if (!in || !M.ok) sout[q] = M.ok ? 1 : 2;
                     }
                     term = 0.0;
                     e = f;
@@ -323,7 +323,7 @@ __global__ void __launch_bounds__(BLK, sizeof(R) == 4 ? 2 : 1)
     __syncthreads();
     double lr = __builtin_nan("");
     if (key >= 0) {
-        lr = sout[lane] && sown[lane] == sown[lane] ? -__builtin_inf() : simg[lane] - sown[lane];
+        if (sout[lane] != 2) lr = sout[lane] ? -__builtin_inf() : simg[lane] - sown[lane];
         if (lr != lr || lr == __builtin_inf()) key = -1; // a non-finite own density, or no map: not a sample
     }
     if (mine && logr) logr[c] = lr;

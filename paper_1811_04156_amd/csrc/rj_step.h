@@ -201,7 +201,9 @@ __device__ __forceinline__ double full_logp(const Tgt<R>& T, const P& ps, int n,
 
 // The factors of log p that belong to segment k of a path of n vertices (the
 // segment, the emission at k = 0, the turn or the end at vertex k + 1), as
-// full_logp forms them; -inf for a segment without length.
+// full_logp forms them; -inf where the segment or the next one, whose direction
+// the turn needs, has no length, so that the sum over a path with such a segment
+// is -inf, as full_logp's, and never NaN.
 template <class R>
 __device__ __forceinline__ double walk_term(const Tgt<R>& T, int n, int k, V3<R> f0, V3<R> f1, V3<R> f2, R& tb) {
     const LPt<R> l0 = lpt(T, f0), l1 = lpt(T, f1);
@@ -209,13 +211,17 @@ __device__ __forceinline__ double walk_term(const Tgt<R>& T, int n, int k, V3<R>
     tb = s.tb;
     double t = (double)seg_term(s);
     if (k == 0) t += (double)emit_term(T, s.u);
+    bool length = s.len > (R)0;
     if (k <= n - 3) {
         const LayV<R> ly = lay_at(T, l1.l);
-        t += (double)(ly.logb + turn_term(ly, s.u, unit_dir(f1, f2)));
+        const V3<R> r = f2 - f1;
+        const R l2 = dot(r, r), il = Mth<R>::rsqrt(l2);
+        t += (double)(ly.logb + turn_term(ly, s.u, il * r));
+        length &= l2 * il > (R)0;
     } else {
         t += (double)end_term(T, s.u, f1);
     }
-    return s.len > (R)0 ? t : -__builtin_inf();
+    return length ? t : -__builtin_inf();
 }
 
 // q(s) of the bi-spherical proposal with concentration beta, in the two
@@ -347,7 +353,7 @@ __device__ __forceinline__ V3<R> vertex_grad(const Tgt<R>& T, int km1, const Lay
 // log p's factors of segment k of a path of n vertices and the gradient of its
 // vertex j = k + 1, with the terms in path order
 // f: vertices k - 1 .. k + 3 (any value where the path has none), A: the
-// segment.
+// segment.  -inf where walk_term gives it.
 template <class R>
 __device__ __forceinline__ double segment_grad(const Tgt<R>& T, int n, int k, const V3<R> (&f)[5], V3<R>& grad, Seg<R>& A) {
     const int j = k + 1;
@@ -360,6 +366,7 @@ __device__ __forceinline__ double segment_grad(const Tgt<R>& T, int n, int k, co
     const R ilA = (R)2 * Mth<R>::rcp(A.len);
     const V3<R> z = {(R)0, (R)0, (R)0};
     V3<R> g = z - dQ - ilA * A.u;
+    bool length = A.len > (R)0;
     if (k == 0) {
         t += (double)emit_term(T, A.u);
         if (T.ek == RJPATH_EMIT_VMF) g = g + T.kappa * dunit(A.u, A.len, T.ed);
@@ -372,6 +379,7 @@ __device__ __forceinline__ double segment_grad(const Tgt<R>& T, int n, int k, co
         const V3<R> f2 = f[3];
         const LPt<R> p2 = lpt(T, f2);
         const Seg<R> B = make_seg_lp(T, f1, f2, p1, p2);
+        length &= B.len > (R)0;
         seg_depth_grad_lp(T, p1, p2, B, dP, dQ);
         const R ilB = (R)2 * Mth<R>::rcp(B.len);
         g = g - dP + ilB * B.u;
@@ -406,7 +414,7 @@ __device__ __forceinline__ double segment_grad(const Tgt<R>& T, int n, int k, co
         }
     }
     grad = g;
-    return A.len > (R)0 ? t : -__builtin_inf();
+    return length ? t : -__builtin_inf();
 }
 
 // Per-lane constants of the step kernel.
