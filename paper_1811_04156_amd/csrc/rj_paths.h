@@ -78,12 +78,23 @@ template <class R> struct WavePaths {
     }
 };
 
+// Between a window's loads and its stores, where lanes write what others read:
+// the fence keeps the wave's memory operations on their sides of it, the
+// barrier the lanes together, so that no branch of the loads runs after a
+// branch of the stores.
+__device__ __forceinline__ void window_loaded() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // The vertex shift of the wave's accepted jumps (all 64 lanes call it): `cnt`
 // vertices of this lane's chain (0: none) move one slot up, from slot `from`
 // downwards, or one down, from slot `from` upwards.  The items are (chain,
 // vertex) in that order, so every window reads vertices that no earlier one
-// has written over.  (Each lane its own chain's: a jump step of the two-region
-// test, 65,536 chains, took 60 us and takes 42.)
+// has written over; within a window the lanes write vertices that others read,
+// so all its loads come before its first store (window_loaded).  (Each lane its
+// own chain's: a jump step of the two-region test, 65,536 chains, took 60 us
+// and takes 42.)
 template <class R> __device__ __forceinline__ void shift_shared(const WavePaths<R>& W, bool up, int from, int cnt) {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
     WaveItems it;
@@ -100,7 +111,8 @@ template <class R> __device__ __forceinline__ void shift_shared(const WavePaths<
             if (src < W.V) v = W.x[src * WAVE + q];
             else v = *(const L4<R>*)(path + src);
         }
-        if (has) { // (the window's loads are done: their values are stored)
+        window_loaded();
+        if (has) {
             if (dst < W.V) W.x[dst * WAVE + q] = v;
             else *(L4<R>*)(path + dst) = v;
         }
@@ -180,6 +192,7 @@ template <class R> __device__ __forceinline__ WavePlaces wave_places(const WaveP
     P.at = upto - mine;
     P.all = __builtin_amdgcn_readlane(upto, WAVE - 1);
     if (mine > 0) *W.sum(W.lane) = 0.0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); // (other lanes add to it)
     return P;
 }
 
@@ -199,6 +212,7 @@ __device__ __forceinline__ void settle_shared(const WavePaths<R>& W, const WaveP
         W.sum(lane)[0] = 0.0;
         W.sum(lane)[1] = 0.0;
     }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     WaveItems it;
     it.init(lane, taken ? n : 0);
     while (it.more()) {
