@@ -472,8 +472,13 @@ __global__ void __launch_bounds__(64) anchor_sum_kernel(int nchunk, const double
 
 // Blocks per target: enough that a few targets still fill the chip (about 16
 // blocks per CU over all targets) and that the rim targets' fourfold
-// work is spread, at most one direction per wave.
-int anchor_chunks(int T) { return T > (1 << 24) ? 1 : std::max(16, std::min(256, 4096 / T)); }
+// work is spread, at most one direction per wave.  From 2^14 targets on their
+// number alone fills it many times over, and 2^18 blocks are kept to as long
+// as every target has one: a launch must stay below 2^32 threads (2^24 blocks,
+// which 16 for each of 2^20 targets would reach), and the chunk sums within 2 MiB
+// or one double per target.  (100-layer cone targets, 16 blocks each and by this
+// rule: 20,000 1.46 and 1.29 s, 40,000 2.90 and 2.70 s.)
+int anchor_chunks(int T) { return std::max(1, std::max(std::min(16, (1 << 18) / T), std::min(256, 4096 / T))); }
 
 hipError_t launch_anchor(const KArgs& a, const double* gl_x, const double* gl_w, double* anchor, double* part,
                          int nchunk, hipStream_t s) {
