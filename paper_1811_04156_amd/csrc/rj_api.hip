@@ -17,6 +17,13 @@
 
 using namespace rj;
 
+int rj::device_cus() {
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 256;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return 256;
+    return cus;
+}
+
 namespace {
 
 thread_local std::string g_err;
@@ -308,14 +315,6 @@ const size_t LDS_MAX = 160 * 1024;
 // LDS left for the per-lane vertex slots once the media tables are staged
 size_t slot_budget(const rjpath_medium* m, const rjpath_targets* t, const rjpath_chains* c) {
     return LDS_MAX - make_args(m, t, c).tab_bytes;
-}
-
-// Compute units of the current device (the occupancy rule below needs them).
-int device_cus() {
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 256;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return 256;
-    return cus;
 }
 
 // Chains per wave of the samplers whose waves share whole-path moves: as few

@@ -10,6 +10,8 @@ namespace rj {
 // Reduction slots per (target, group) of rjpath_intensity.
 enum { RD_SAMPLES = 0, RD_A, RD_B, RD_L, RD_L2, RD_CHAINS, RD_NW };
 
+// compute units of the current device (the launch rules count in them)
+int device_cus();
 hipError_t launch_run(const KArgs& a, int block, hipStream_t s);
 hipError_t set_run_lds_limit();
 // the order of the waves of a launch, `per` chains each, into the status words

@@ -408,21 +408,13 @@ __global__ void __launch_bounds__(BLK * LHIST_PARTS) lhist_kernel(KArgs a, int b
 
 } // namespace
 
-// Compute units of the current device.
-static int compute_units() {
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 256;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return 256;
-    return cus;
-}
-
 template <class R>
 static hipError_t launch_yield_t(const KArgs& a, int n_pairs, const int32_t* pairs, const int32_t* role, int groups,
                                  double* acc, double* logr, hipStream_t s) {
     // chains per wave: 64 from two waves per SIMD on, fewer below, down to 8;
     // a strip of 8 KiB per wave, so that two waves per SIMD fit
     int cpw = WAVE;
-    while (cpw > 8 && (long long)a.C < 8LL * compute_units() * cpw) cpw /= 2;
+    while (cpw > 8 && (long long)a.C < 8LL * device_cus() * cpw) cpw /= 2;
     const int strip = 8 * 1024 / (int)sizeof(Vtx<R>);
     const int chains = BLK / WAVE * cpw, grid = (a.C + chains - 1) / chains;
     hipLaunchKernelGGL(yield_kernel<R>, dim3(grid), dim3(BLK), (size_t)(BLK / WAVE) * 8 * 1024, s, a, n_pairs, pairs, role,
@@ -440,7 +432,7 @@ hipError_t launch_lhist(const KArgs& a, int bins, double l0, double width, doubl
     const int grid = (a.C + BLK - 1) / BLK;
     // lanes per chain: as many as keep the launch within eight waves per SIMD
     int parts = LHIST_PARTS;
-    while (parts > 1 && (long long)a.C * parts > 32LL * compute_units() * WAVE) parts /= 2;
+    while (parts > 1 && (long long)a.C * parts > 32LL * device_cus() * WAVE) parts /= 2;
     const dim3 block(BLK * parts);
     const size_t lds = 2 * sizeof(double) * ((size_t)bins + 1);
     const int use = lds <= 64 * 1024;

@@ -13,13 +13,16 @@ namespace rj {
 // ---------------------------------------------------------------------------
 // Score kernel: log p, d log p / d vertices and the per-layer parameter score.
 //
-// Work split.  A wave takes 64 chains.  Their vertices are read row by row
-// (whole cache lines) into an LDS strip, chain after chain without gaps, and
-// the (chain, segment) items go over all lanes: one lane per chain waits for the
-// wave's longest path (mean n 6, longest 25 to 40 on the ragged batches), which
-// is where the 443 us of 2^20 chains went (19 us at the rate of a large copy),
-// with FP64 layer lookups and two to four FP64 atomics of every lane per
-// vertex; now 205 us (tables read from HBM and two waves per SIMD: 315).
+// Work split.  A wave takes 64 chains, in one of two forms (shares_segments).
+// Shared: their vertices are read row by row (whole cache lines) into an LDS
+// strip, chain after chain without gaps, and the (chain, segment) items go over
+// all lanes: one lane per chain waits for the wave's longest path (mean n 6,
+// longest 25 to 40 on the ragged batches).  The kernel alone, 2^20 chains of the
+// ragged layered batch, score sums: 443 us by lanes, 205 shared (tables read from
+// HBM and two waves per SIMD: 315; a large copy moves the paths in 19).
+// A lane per chain (PathWalk): where the lengths of a wave are alike, where
+// they overflow the strip and where neighbouring chains have different targets
+// that form is the better one (below).
 //
 // The score sums of a block whose chains belong to at most two targets go to
 // an LDS table, per target the sum of the weights and per layer the weighted
@@ -73,9 +76,9 @@ __device__ __forceinline__ double dturn_dg(double g, double fsl, double q) {
 
 // The score contributions of the segment P -> Q of weight w: its length per
 // layer and, where `turn`, the scattering at P, which the unit vector um leads
-// to.
+// to.  Returns the segment's direction.
 template <class R>
-__device__ __forceinline__ void segment_score(const Tgt<R>& T, int off, const ScoreDst& D, double w, V3<R> P, V3<R> Q,
+__device__ __forceinline__ V3<R> segment_score(const Tgt<R>& T, int off, const ScoreDst& D, double w, V3<R> P, V3<R> Q,
                                               bool turn, V3<R> um) {
     const V3<R> r = Q - P;
     const R l2 = dot(r, r), il = Mth<R>::rsqrt(l2);
@@ -101,7 +104,85 @@ __device__ __forceinline__ void segment_score(const Tgt<R>& T, int off, const Sc
         const V3<R> dd = um - u;
         D.scatter(off + lP, w, dturn_dg((double)ly.g, (double)ly.fsl, (double)dot(dd, dd)), (double)ly.b);
     }
+    return u;
 }
+
+// The score of one path by one lane, fed a vertex at a time: step(f_k) takes
+// vertex k >= 1 and, with G, gives the gradient of vertex k - 2, finish() adds
+// the end term and gives log p and the gradients of vertices n - 2 and n - 1.
+// The terms and their order within a vertex are segment_grad's.
+template <class R, bool G> struct PathWalk {
+    V3<R> gA, gB; // gradients of vertices k - 2 and k - 1 so far
+    V3<R> fprev, uprev;
+    R lprev;
+    LPt<R> pprev;
+    double lp = 0.0;
+    bool length = true; // every segment so far has one
+    int k = 1;
+
+    __device__ __forceinline__ PathWalk(const Tgt<R>& T, V3<R> f0) : fprev(f0), pprev(lpt(T, f0)) {
+        gA = gB = uprev = V3<R>{(R)0, (R)0, (R)0};
+        lprev = (R)0;
+    }
+    __device__ __forceinline__ void step(const Tgt<R>& T, V3<R> f, V3<R>& out) {
+        const LPt<R> p = lpt(T, f);
+        const Seg<R> s = make_seg_lp(T, fprev, f, pprev, p);
+        length &= s.len > (R)0;
+        lp += (double)seg_term(s);
+        V3<R> gC;
+        if (G) {
+            V3<R> dP, dQ;
+            seg_depth_grad_lp(T, pprev, p, s, dP, dQ);
+            const R il = (R)2 * Mth<R>::rcp(s.len);
+            const V3<R> z = {(R)0, (R)0, (R)0};
+            gB = gB - dP + il * s.u;
+            gC = z - dQ - il * s.u;
+        }
+        if (k == 1) {
+            lp += (double)emit_term(T, s.u);
+            if (G && T.ek == RJPATH_EMIT_VMF) gC = gC + T.kappa * dunit(s.u, s.len, T.ed);
+        } else {
+            const LayV<R> ly = lay_at(T, pprev.l);
+            lp += (double)(ly.logb + turn_term(ly, uprev, s.u));
+            if (G) {
+                const V3<R> dd = uprev - s.u;
+                const R h = dturn_dmu(ly, dot(dd, dd));
+                const V3<R> da = dunit(uprev, lprev, s.u), db = dunit(s.u, s.len, uprev);
+                gA = gA - h * da;
+                gB = gB + h * da - h * db;
+                gC = gC + h * db;
+            }
+        }
+        if (G) {
+            out = gA;
+            gA = gB;
+            gB = gC;
+        }
+        uprev = s.u;
+        lprev = s.len;
+        fprev = f;
+        pprev = p;
+        ++k;
+    }
+    __device__ __forceinline__ double finish(const Tgt<R>& T, V3<R>& g2, V3<R>& g1) {
+        lp += (double)end_term(T, uprev, fprev);
+        if (G) {
+            const V3<R> d = from_eta(T, fprev);
+            const R dn2 = dot(d, d), idn = Mth<R>::rsqrt(dn2);
+            const V3<R> nu = idn * d;
+            const R ic = Mth<R>::rcp(-dot(uprev, nu));
+            const V3<R> dcr = (R)-1 * dunit(uprev, lprev, nu), dcd = (R)-1 * dunit(nu, dn2 * idn, uprev);
+            g2 = gA - ic * dcr;
+            g1 = gB + ic * dcr + ic * dcd;
+            if (T.dk == RJPATH_DET_PAPER) {
+                const R cr = dot(nu, T.dd);
+                const R th = tanh((R)2 * cr + (R)0.7);
+                g1 = g1 + ((R)3 - (R)2 * th) * dunit(nu, dn2 * idn, T.dd);
+            }
+        }
+        return length ? lp : -__builtin_inf();
+    }
+};
 
 // The wave's vertices: vertex i of its chains in order, the first `M` in LDS.
 template <class R> struct WaveStrip {
@@ -117,14 +198,53 @@ template <class R> struct WaveStrip {
     }
 };
 
+// Layers of a medium from which a score pass whose sums go straight to the
+// caller's array (chains of more than two targets in the block) shares
+// segments: with fewer, the items of a window, which are one path's, add to the
+// same few sums, while the lanes' own segments go to as many targets (16,384
+// homogeneous chains, mean n 16, 16 neighbours per target: 629 us shared, 301 by
+// lanes; of 100 layers, each chain with another target: 307 and 317).
+constexpr int SCORE_LAYERS = 16;
+
+// Whether a wave shares its chains' segments, or each lane walks its own chain.
+// An item of the shared form costs more than a step of a walk, which keeps what
+// the segment before left (both form a direction and two layer points, the
+// gradients three segments instead of one), and a window of items of several
+// targets loads a target per lane; a walk waits for the wave's longest path.
+// The weights are fitted to both forms over mean lengths of 3 to 42, ragged and
+// even, 1, 4, 16 and 64 targets per wave, 16,384 and 524,288 chains; they leave
+// the choice of the shared form where the two are close, since a launch of both
+// forms fetches the code of both.  us, shared and by lanes: log p, even layers,
+// 524,288 chains, mean n 6, longest of a wave 16: 68 and 67, all 12: 82 and 40;
+// homogeneous, mean 42: 572 and 232; mixture, 16,384 chains, mean 11: 52 and 80;
+// FP64 gradients, 16,384 chains, even layers, mean 17: 92 and 129, all 12: 50 and 26;
+// score sums, 524,288 chains, all 12: 167 and 121.
+template <class R, bool DV, int KIND, bool SCORE>
+__device__ __forceinline__ bool shares_segments(int n, int t, int lane, int total, int strip, bool few) {
+    constexpr bool F64 = sizeof(R) == 8;
+    const int left = __shfl_up(t, 1, WAVE);
+    const int more = __popcll(__ballot(lane > 0 && t >= 0 && left != t)); // targets after the first
+    const int chains = __popcll(__ballot(n > 0)), windows = (total - chains + WAVE - 1) / WAVE;
+    // in eighths of a step of a walk
+    int item = SCORE ? 13
+               : DV  ? (F64 || KIND == GK_ANY ? 14 : 18)
+               : F64 ? (KIND == GK_ANY ? 10 : 12)
+                     : KIND == GK_ANY ? (few ? 12 : 17) : KIND == GK_EVEN ? (few ? 18 : 24) : (few ? 20 : 28);
+    const int load = F64 ? 5 : 8;
+    if (total > strip) item += F64 ? item / 8 : item / 4;
+    const int cost = item * windows + load * min(windows, more);
+    return __any(8 * (n - 1) >= cost);
+}
+
 // LDS of a block: the media tables (tab_bytes, 0: read from HBM), the waves'
 // strips (`strip` vertices each), per wave and chain log p and (lweight) the
 // path length, the score table (lds_rows rows).
-// DV: the vertex gradients are wanted too.
-template <class R, bool DV, int KIND>
+// DV: the vertex gradients are wanted too; SCORE: the score sums.
+template <class R, bool DV, int KIND, bool SCORE>
 __global__ void __launch_bounds__(256, sizeof(R) == 4 ? 3 : 1) grad_kernel(KArgs a, double* logp_out, Vtx<R>* dv,
                                                                           double* score, int L_total, int lds_rows,
-                                                                          int lweight, int strip, int tab_bytes) {
+                                                                          int lweight, int strip, int tab_bytes,
+                                                                          int few) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int tmin_s[4], tmax_s[4];
     const size_t C = (size_t)a.C;
@@ -150,7 +270,7 @@ __global__ void __launch_bounds__(256, sizeof(R) == 4 ? 3 : 1) grad_kernel(KArgs
     // block-uniform choice of the score destination
     bool local = false;
     int tmin = 0;
-    if (score && lds_rows > 0) {
+    if (SCORE && lds_rows > 0) {
         tmin = block_min_i32(t < 0 ? 0x7fffffff : t, tmin_s);
         const int tmax = block_max_i32(t, tmax_s);
         local = tmax >= 0 && tmax - tmin < lds_rows;
@@ -160,11 +280,15 @@ __global__ void __launch_bounds__(256, sizeof(R) == 4 ? 3 : 1) grad_kernel(KArgs
     __syncthreads();
     const uint64_t some = __ballot(t >= 0);
     if (some) {
-        // the strip
         const int upto = wave_prefix(n), at = upto - n;
+        const int total = __builtin_amdgcn_readlane(upto, WAVE - 1);
+        const bool share = SCORE && !local ? KIND != GK_HOM && L_total >= SCORE_LAYERS * a.n_media
+                                           : shares_segments<R, DV, KIND, SCORE>(n, t, lane, total, strip, few);
+        // the strip: all vertices, or nothing where a lane per chain reads the
+        // paths' rows as they lie
         const WaveStrip<R> S{(LdsPtr<R>)((L4<R>*)(smem + tab_bytes) + (size_t)wave * strip), (const Vtx<R>*)a.verts + c0, C,
-                             strip};
-        for (int v = 0; __any(v < n); v += 4) {
+                             share || total <= strip ? strip : 0};
+        for (int v = 0; S.M > 0 && __any(v < n); v += 4) {
             L4<R> x[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i)
@@ -177,11 +301,7 @@ __global__ void __launch_bounds__(256, sizeof(R) == 4 ? 3 : 1) grad_kernel(KArgs
         if (lweight) sL[lane] = 0.0;
         if (DV && t >= 0) dv[c] = Vtx<R>{(R)0, (R)0, (R)0, (R)0}; // (vertex 0 never moves)
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-        // the lane's target at the moment: its item's, loaded when it changes
-        // (the chains of a target are neighbours, so mostly once)
-        Tgt<R> T;
-        int tc = __builtin_amdgcn_readlane(t, __ffsll((unsigned long long)some) - 1);
-        auto load = [&](int tt) __attribute__((always_inline)) {
+        auto load = [&](int tt, Tgt<R>& T) __attribute__((always_inline)) {
             load_target(a, tt, T, mt);
             if (KIND == GK_HOM) {
                 T.mcnt = 1;
@@ -194,73 +314,120 @@ __global__ void __launch_bounds__(256, sizeof(R) == 4 ? 3 : 1) grad_kernel(KArgs
             T.sl = KIND == GK_ANY;
             if (KIND != GK_ANY) T.l0.fsl = (R)0;
         };
-        load(tc);
-        WaveItems it;
-        it.init(lane, n > 0 ? n - 1 : 0);
-        while (it.more()) {
-            int q, k;
-            const bool has = it.next(q, k);
-            const int aq = __shfl(at, q, WAVE), nq = __shfl(n, q, WAVE), tq = __shfl(t, q, WAVE);
-            if (__any(has && tq != tc)) {
-                tc = has ? tq : tc;
-                load(tc);
-            }
-            if (has) {
-                auto p = [&](int v) __attribute__((always_inline)) { return S.p(aq, v, q); };
-                double f;
-                if constexpr (DV) {
-                    V3<R> g;
-                    const V3<R> f5[5] = {p(k > 0 ? k - 1 : 0), p(k), p(k + 1), p(k + 2 < nq ? k + 2 : k + 1),
-                                         p(k + 3 < nq ? k + 3 : k + 1)};
-                    Seg<R> A;
-                    f = segment_grad(T, nq, k, f5, g, A);
-                    dv[(size_t)(k + 1) * C + c0 + q] = Vtx<R>{g.x, g.y, g.z, (R)0};
-                } else {
-                    R tb;
-                    f = walk_term(T, nq, k, p(k), p(k + 1), p(k + 2 < nq ? k + 2 : k + 1), tb);
-                }
-                atomicAdd(slp + q, f);
-                if (lweight) {
-                    // weight by the path length (FP64 sum of the segment lengths)
-                    const V3<R> d = p(k + 1) - p(k);
-                    atomicAdd(sL + q, sqrt((double)dot(d, d)));
-                }
-            }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-        const double lp = slp[lane];
-        if (t >= 0 && logp_out) logp_out[c] = lp;
-        if (score) {
-            // the weight of a chain in the score (0: it does not count)
+        auto dst = [&](int tt) __attribute__((always_inline)) {
+            return ScoreDst{local ? tab + (size_t)(tt - tmin) * row : score + (size_t)tt * row, local};
+        };
+        // the weight of a chain in the score (0: it does not count), added to its target's
+        auto weight = [&](double lp, double L) __attribute__((always_inline)) {
             double w = 0.0;
             if (t >= 0 && isfinite(lp) && a.status[c] == 0) {
                 const double* lw = a.logw ? a.logw + (size_t)t * (a.cap + 1) : nullptr;
                 w = lw ? exp(-lw[n]) : 1.0;
-                if (lweight) w *= sL[lane];
+                if (lweight) w *= L;
             }
-            auto dst = [&](int tt) __attribute__((always_inline)) {
-                return ScoreDst{local ? tab + (size_t)(tt - tmin) * row : score + (size_t)tt * row, local};
-            };
             if (w != 0.0) atomicAdd(dst(t).row, w);
-            it.init(lane, w != 0.0 ? n - 1 : 0);
+            return w;
+        };
+        if (!share && t >= 0) {
+            Tgt<R> T;
+            load(t, T);
+            PathWalk<R, DV> walk(T, S.p(at, 0, lane));
+            V3<R> f = S.p(at, 1, lane), g, g1;
+            double L = 0.0;
+            for (int k = 1; k < n; ++k) {
+                const V3<R> next = S.p(at, k + 1 < n ? k + 1 : k, lane);
+                if (lweight) {
+                    const V3<R> d = f - walk.fprev;
+                    L += sqrt((double)dot(d, d));
+                }
+                walk.step(T, f, g);
+                if (DV && k >= 3) dv[(size_t)(k - 2) * C + c] = Vtx<R>{g.x, g.y, g.z, (R)0};
+                f = next;
+            }
+            const double lp = walk.finish(T, g, g1);
+            if (logp_out) logp_out[c] = lp;
+            if (DV) {
+                if (n >= 3) dv[(size_t)(n - 2) * C + c] = Vtx<R>{g.x, g.y, g.z, (R)0};
+                dv[(size_t)(n - 1) * C + c] = Vtx<R>{g1.x, g1.y, g1.z, (R)0};
+            }
+            if (SCORE) {
+                const double w = weight(lp, L);
+                if (w != 0.0) {
+                    const ScoreDst D = dst(t);
+                    const int off = a.minfo[a.medium[t]].off;
+                    V3<R> f0 = S.p(at, 0, lane), f1 = S.p(at, 1, lane), um = f0;
+                    for (int k = 0; k < n - 1; ++k) {
+                        const V3<R> next = S.p(at, k + 2 < n ? k + 2 : k + 1, lane);
+                        um = segment_score(T, off, D, w, f0, f1, k > 0, um);
+                        f0 = f1;
+                        f1 = next;
+                    }
+                }
+            }
+        }
+        if (share) {
+            // the lane's target at the moment: its item's, loaded when it changes
+            // (the chains of a target are neighbours, so mostly once)
+            Tgt<R> T;
+            int tc = __builtin_amdgcn_readlane(t, __ffsll((unsigned long long)some) - 1);
+            load(tc, T);
+            WaveItems it;
+            it.init(lane, n > 0 ? n - 1 : 0);
             while (it.more()) {
                 int q, k;
                 const bool has = it.next(q, k);
-                const int aq = __shfl(at, q, WAVE), tq = __shfl(t, q, WAVE);
-                const double wq = __shfl(w, q, WAVE);
+                const int aq = __shfl(at, q, WAVE), nq = __shfl(n, q, WAVE), tq = __shfl(t, q, WAVE);
                 if (__any(has && tq != tc)) {
                     tc = has ? tq : tc;
-                    load(tc);
+                    load(tc, T);
                 }
                 if (has) {
-                    const V3<R> f0 = S.p(aq, k, q), f1 = S.p(aq, k + 1, q);
-                    const V3<R> um = unit_dir(S.p(aq, k > 0 ? k - 1 : 0, q), f0);
-                    segment_score(T, a.minfo[a.medium[tc]].off, dst(tc), wq, f0, f1, k > 0, um);
+                    auto p = [&](int v) __attribute__((always_inline)) { return S.p(aq, v, q); };
+                    double f;
+                    if constexpr (DV) {
+                        V3<R> g;
+                        const V3<R> f5[5] = {p(k > 0 ? k - 1 : 0), p(k), p(k + 1), p(k + 2 < nq ? k + 2 : k + 1),
+                                             p(k + 3 < nq ? k + 3 : k + 1)};
+                        Seg<R> A;
+                        f = segment_grad(T, nq, k, f5, g, A);
+                        dv[(size_t)(k + 1) * C + c0 + q] = Vtx<R>{g.x, g.y, g.z, (R)0};
+                    } else {
+                        R tb;
+                        f = walk_term(T, nq, k, p(k), p(k + 1), p(k + 2 < nq ? k + 2 : k + 1), tb);
+                    }
+                    atomicAdd(slp + q, f);
+                    if (lweight) {
+                        // weight by the path length (FP64 sum of the segment lengths)
+                        const V3<R> d = p(k + 1) - p(k);
+                        atomicAdd(sL + q, sqrt((double)dot(d, d)));
+                    }
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+            const double lp = slp[lane];
+            if (t >= 0 && logp_out) logp_out[c] = lp;
+            if (SCORE) {
+                const double w = weight(lp, lweight ? sL[lane] : 0.0);
+                it.init(lane, w != 0.0 ? n - 1 : 0);
+                while (it.more()) {
+                    int q, k;
+                    const bool has = it.next(q, k);
+                    const int aq = __shfl(at, q, WAVE), tq = __shfl(t, q, WAVE);
+                    const double wq = __shfl(w, q, WAVE);
+                    if (__any(has && tq != tc)) {
+                        tc = has ? tq : tc;
+                        load(tc, T);
+                    }
+                    if (has) {
+                        const V3<R> f0 = S.p(aq, k, q), f1 = S.p(aq, k + 1, q);
+                        const V3<R> um = unit_dir(S.p(aq, k > 0 ? k - 1 : 0, q), f0);
+                        segment_score(T, a.minfo[a.medium[tc]].off, dst(tc), wq, f0, f1, k > 0, um);
+                    }
                 }
             }
         }
     }
-    if (local) {
+    if (SCORE && local) {
         // layer sums to derivatives
         __syncthreads();
         for (size_t i = threadIdx.x; i < (size_t)lds_rows * (1 + (size_t)L_total); i += blockDim.x) {
@@ -301,9 +468,13 @@ hipError_t launch_run(const KArgs& a, int block, hipStream_t s) {
 }
 
 template <class R> static hipError_t set_grad_lds_limit() {
-    const void* fns[] = {(const void*)grad_kernel<R, false, GK_ANY>,  (const void*)grad_kernel<R, true, GK_ANY>,
-                         (const void*)grad_kernel<R, false, GK_EVEN>, (const void*)grad_kernel<R, true, GK_EVEN>,
-                         (const void*)grad_kernel<R, false, GK_HOM>,  (const void*)grad_kernel<R, true, GK_HOM>};
+    const void* fns[] = {
+        (const void*)grad_kernel<R, false, GK_ANY, false>,  (const void*)grad_kernel<R, true, GK_ANY, false>,
+        (const void*)grad_kernel<R, false, GK_EVEN, false>, (const void*)grad_kernel<R, true, GK_EVEN, false>,
+        (const void*)grad_kernel<R, false, GK_HOM, false>,  (const void*)grad_kernel<R, true, GK_HOM, false>,
+        (const void*)grad_kernel<R, false, GK_ANY, true>,   (const void*)grad_kernel<R, true, GK_ANY, true>,
+        (const void*)grad_kernel<R, false, GK_EVEN, true>,  (const void*)grad_kernel<R, true, GK_EVEN, true>,
+        (const void*)grad_kernel<R, false, GK_HOM, true>,   (const void*)grad_kernel<R, true, GK_HOM, true>};
     for (const void* f : fns) {
         hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 144 * 1024);
         if (e != hipSuccess) return e;
@@ -347,12 +518,10 @@ static hipError_t launch_grad_t(const KArgs& a, double* logp_out, void* dv, doub
     const int strip = (sizeof(R) == 4 ? 7 : 6) * WAVE;
     size_t strips = 4 * (size_t)strip * sizeof(Vtx<R>);
     const size_t lds = media + strips + (lweight ? 8 : 4) * WAVE * sizeof(double) + rows * row_bytes;
-    if (dv)
-        hipLaunchKernelGGL((grad_kernel<R, true, KIND>), dim3(grid), dim3(block), lds, s, a, logp_out, (Vtx<R>*)dv, score,
-                           L_total, rows, lweight, strip, (int)media);
-    else
-        hipLaunchKernelGGL((grad_kernel<R, false, KIND>), dim3(grid), dim3(block), lds, s, a, logp_out, (Vtx<R>*)nullptr,
-                           score, L_total, rows, lweight, strip, (int)media);
+    const auto fn = score ? (dv ? grad_kernel<R, true, KIND, true> : grad_kernel<R, false, KIND, true>)
+                          : (dv ? grad_kernel<R, true, KIND, false> : grad_kernel<R, false, KIND, false>);
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(block), lds, s, a, logp_out, (Vtx<R>*)dv, score, L_total, rows, lweight, strip,
+                       (int)media, grid <= 2 * device_cus());
     return hipGetLastError();
 }
 

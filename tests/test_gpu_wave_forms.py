@@ -1,0 +1,87 @@
+"""Kernels whose waves either share their chains' items or give each lane its
+own chain: both forms on the same paths."""
+import numpy as np
+import pytest
+
+from gpu_helpers import mixed_workload, random_paths
+from paper_1811_04156_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def rj():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1811_04156_amd import rjpath
+    rjpath.load()
+    return rjpath
+
+
+def _workload(medium, chains, cap):
+    if medium == "homogeneous":
+        return W.homogeneous_groups(seed=2, groups=4, per_group=chains // 4, cap=cap)
+    if medium == "mixture":
+        return mixed_workload(cap=cap, chains=chains)  # 12 layers
+    w = W.layered_pairs(seed=2, pairs=4, chains=chains, cap=cap, n_layers=20, dz=2.0, dmin=4.0, dmax=15.0)
+    if medium == "uneven":
+        w["edges"] = w["edges"] + np.where(np.arange(21) % 2 == 1, 0.3, 0.0)
+    return w
+
+
+@pytest.mark.parametrize("medium", ["homogeneous", "even", "uneven", "mixture"])
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+def test_score_pass_by_items_and_by_lanes(rj, prec, medium):
+    """The same paths with every wave's lengths alike (a lane per chain; up to
+    20 vertices, which the wave's LDS strip does not hold) and with long ones
+    beside short ones (shared), for one, two and 64 targets per wave: the same
+    vertex gradients bit for bit, log p up to the order of its FP64 terms
+    (1e-13 relative), the score sums likewise (1e-12)."""
+    from oracle import oracle as O
+    C, cap = 512, 24
+    w = _workload(medium, C, cap)
+    T = len(w["t_src"])
+    w["c_target"] = np.zeros(C, np.int32)
+    orc = O.Oracle(w)
+    rng = np.random.default_rng(11)
+    n, V = random_paths(orc, w, rng, 20)
+    lw = np.tile(0.05 * np.arange(cap + 1), (T, 1))
+    alike, ragged = np.argsort(n, kind="stable"), np.argsort(rng.permutation(C), kind="stable")
+    out = []
+    for order in (alike, ragged):
+        s = rj.Sampler(w, precision=prec, logw=lw)
+        s.set_state(n[order], V[order])
+        lp, g, _ = s.grad(logp=True, dv=True)
+        lp2, _, sc = s.grad(logp=True, score=True)
+        lp3, g3, sc3 = s.grad(logp=True, dv=True, score=True)
+        lp4, _, _ = s.grad(logp=True)
+        back = np.argsort(order, kind="stable")
+        out.append(([x.cpu().numpy()[back] for x in (lp, lp2, lp3, lp4)], [x.cpu().numpy()[:, back] for x in (g, g3)],
+                    [x.cpu().numpy() for x in (sc, sc3, s.score_length())]))
+    a, b = out
+    for x, y in zip(a[0], b[0]):
+        assert np.allclose(x, y, rtol=1e-13, atol=1e-13)
+    assert np.all(np.isfinite(a[0][0])) and np.array_equal(a[1][0], b[1][0]) and np.array_equal(a[1][1], b[1][1])
+    for x, y in zip(a[2], b[2]):
+        assert np.allclose(x, y, rtol=1e-12, atol=1e-12 * np.abs(x).max())
+    for c in range(0, C, 37):
+        ref = orc.logp(0, V[c, : n[c]])
+        assert abs(a[0][0][c] - ref) < (1e-9 if prec == "f64" else 2e-3), (c, a[0][0][c], ref)
+    # targets dealt out: a score table per block no more, sums of few layers by lanes
+    for run in (1, 64):
+        wd = dict(w)
+        wd["c_target"] = (np.arange(C) // run % T).astype(np.int32)
+        n2, V2 = random_paths(O.Oracle(wd), wd, np.random.default_rng(12), 20)
+        res = []
+        for order in (np.arange(C), np.argsort(wd["c_target"], kind="stable")):
+            wo = dict(wd)
+            wo["c_target"] = wd["c_target"][order]
+            s = rj.Sampler(wo, precision=prec, logw=lw)
+            s.set_state(n2[order], V2[order])
+            lp, g, sc = s.grad(logp=True, dv=True, score=True)
+            back = np.argsort(order, kind="stable")
+            res.append((lp.cpu().numpy()[back], g.cpu().numpy()[:, back], sc.cpu().numpy()))
+        assert np.allclose(res[0][0], res[1][0], rtol=1e-13, atol=1e-13) and np.array_equal(res[0][1], res[1][1])
+        assert np.allclose(res[0][2], res[1][2], rtol=1e-12, atol=1e-12 * np.abs(res[0][2]).max())
