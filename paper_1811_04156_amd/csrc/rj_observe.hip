@@ -183,11 +183,77 @@ __device__ __forceinline__ void block_sums_end(const BlockSums& b, double* out, 
 // maps one vertex and takes the next two, of the path and of its image, from
 // the lanes beside it (windows of 62), so that the map's FP64 sine, cosine or
 // arc tangent is formed once per vertex and no lane waits for the longest
-// path.  One lane per chain, mapping every vertex twice, took 545 us for the
-// two-region test's 65,536 chains of 32 vertices; now 180 us.
+// path.  One lane per chain, mapping every vertex twice, took the kernel 545 us
+// for the two-region test's 65,536 chains of 32 vertices; shared, 180 us.
+// Where a wave has many targets or short paths of one length, a lane per chain
+// is the better form (lane_densities, which maps a vertex once).
 // ---------------------------------------------------------------------------
 template <class R> __device__ __forceinline__ V3<R> lane_v3(V3<R> p, int from) {
     return {__shfl(p.x, from, WAVE), __shfl(p.y, from, WAVE), __shfl(p.z, from, WAVE)};
+}
+
+// Whether a wave shares its chains' vertices, or each lane maps its own chain's.
+// A window of 62 shared vertices takes about as long as two of a lane's own, and
+// every target of the wave has windows and a map to itself.  The call in us,
+// shared and by lanes (262,144 chains of the two-region geometry, FP32): mean n
+// 42, chains of a target together 850 and 1185, every n 6 119 and 80; dealt out
+// over 128 targets, mean n 42, 2060 and 1260, mean 4 1605 and 107 (FP64, 65,536
+// chains of mean n 10: 850 and 245).
+template <class R> __device__ __forceinline__ bool shares_vertices(int items, int tc, int total) {
+    constexpr int WINDOW = sizeof(R) == 4 ? 18 : 13, TARGET = sizeof(R) == 4 ? 4 : 3; // eighths of a lane's vertex
+    int targets = 0;
+    for (uint64_t rest = __ballot(items > 0); rest; ++targets) {
+        const int tq = __builtin_amdgcn_readlane(tc, __ffsll((unsigned long long)rest) - 1);
+        rest &= ~__ballot(tc == tq);
+    }
+    const int windows = max(targets, (total + (WAVE - 2) / 2 * (targets + 1)) / (WAVE - 2));
+    return __any(8 * (items + 2) >= WINDOW * windows + TARGET * targets);
+}
+
+// One chain by one lane: `f(v)` is vertex v of its path of n vertices.  lp: log p
+// of the path; img: of its image, +- log |dT/dx|; returns the chain's `outside`.
+template <class R, class F>
+__device__ __forceinline__ int lane_densities(const KArgs& a, int own, int other, int side, int n, F f, double& lp,
+                                              double& img) {
+    lp = img = 0.0;
+    {
+        const YMap M = ymap(a, side == 0 ? own : other, side == 0 ? other : own);
+        if (!M.ok) return 2;
+        Tgt<R> T;
+        load_target(a, other, T, hbm_tab<R>(a));
+        double lj = M.le + (n - 2) * M.lc;
+        PathWalk<R, false> walk(T, f(0));
+        V3<R> x = f(1), g;
+        for (int k = 1; k < n; ++k) {
+            const V3<R> next = f(k + 1 < n ? k + 1 : k);
+            const D3 d = {(double)x.x, (double)x.y, (double)x.z};
+            D3 y;
+            if (k == n - 1) {
+                y = side == 0 ? yend_fwd(M, d) : yend_inv(M, d);
+            } else {
+                double rad;
+                bool in = true;
+                if (side == 0) y = yfwd(M, d, rad, in);
+                else y = yinv(M, d, rad);
+                if (!in) return 1;
+                lj += log(rad);
+            }
+            walk.step(T, V3<R>{(R)y.x, (R)y.y, (R)y.z}, g);
+            x = next;
+        }
+        img = walk.finish(T, g, g) + (side == 0 ? lj : -lj);
+    }
+    Tgt<R> T;
+    load_target(a, own, T, hbm_tab<R>(a));
+    PathWalk<R, false> walk(T, f(0));
+    V3<R> x = f(1), g;
+    for (int k = 1; k < n; ++k) {
+        const V3<R> next = f(k + 1 < n ? k + 1 : k);
+        walk.step(T, x, g);
+        x = next;
+    }
+    lp = walk.finish(T, g, g);
+    return 0;
 }
 
 template <class R>
@@ -230,7 +296,14 @@ __global__ void __launch_bounds__(BLK, sizeof(R) == 4 ? 2 : 1)
     sout[lane] = 0;
     const int items = key >= 0 ? n : 0;
     const int upto = wave_prefix(items), at = upto - items, total = __builtin_amdgcn_readlane(upto, WAVE - 1);
-    if (total > 0) {
+    if (!shares_vertices<R>(items, tc, total)) {
+        if (key >= 0) {
+            const Vtx<R>* const path = (const Vtx<R>*)a.verts + c;
+            sout[lane] = lane_densities<R>(
+                a, tc, to, key & 1, n, [&](int v) __attribute__((always_inline)) { return pos(path[(size_t)v * a.C]); },
+                sown[lane], simg[lane]);
+        }
+    } else if (total > 0) {
         // the vertices, read row by row into the wave's strip
         const LdsPtr<R> lds = (LdsPtr<R>)((L4<R>*)smem + (size_t)wave * strip);
         const Vtx<R>* const g = (const Vtx<R>*)a.verts + c0;
@@ -270,6 +343,8 @@ __global__ void __launch_bounds__(BLK, sizeof(R) == 4 ? 2 : 1)
             {
                 const YMap m = ymap(a, side == 0 ? tq : oq, side == 0 ? oq : tq);
                 if (lane == 0) map[wave] = m;
+                if (in_target && !m.ok) sout[lane] = 2;
+                if (!__builtin_amdgcn_readfirstlane(m.ok)) continue;
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
             WaveItems it;
@@ -312,7 +387,7 @@ __global__ void __launch_bounds__(BLK, sizeof(R) == 4 ? 2 : 1)
                             term += walk_term(T, nq, k, e, e1, e2, tb);
                         }
                         atomicAdd((w == 0 ? sown : simg) + q, term);
-                        if (!in || !M.ok) sout[q] = M.ok ? 1 : 2;
+                        if (!in) sout[q] = 1;
                     }
                     term = 0.0;
                     e = f;
@@ -411,10 +486,13 @@ __global__ void __launch_bounds__(BLK * LHIST_PARTS) lhist_kernel(KArgs a, int b
 template <class R>
 static hipError_t launch_yield_t(const KArgs& a, int n_pairs, const int32_t* pairs, const int32_t* role, int groups,
                                  double* acc, double* logr, hipStream_t s) {
-    // chains per wave: 64 from two waves per SIMD on, fewer below, down to 8;
-    // a strip of 8 KiB per wave, so that two waves per SIMD fit
+    // chains per wave: 64 from the resident waves on (two per SIMD, one in FP64,
+    // where 65,536 chains of 32 per wave took two rounds: mean n 10 149 us instead
+    // of 135), fewer below, down to 8; a strip of 8 KiB per wave, so that two per
+    // SIMD fit
+    const int resident = (sizeof(R) == 4 ? 8 : 4) * device_cus();
     int cpw = WAVE;
-    while (cpw > 8 && (long long)a.C < 8LL * device_cus() * cpw) cpw /= 2;
+    while (cpw > 8 && (long long)a.C < (long long)resident * cpw) cpw /= 2;
     const int strip = 8 * 1024 / (int)sizeof(Vtx<R>);
     const int chains = BLK / WAVE * cpw, grid = (a.C + chains - 1) / chains;
     hipLaunchKernelGGL(yield_kernel<R>, dim3(grid), dim3(BLK), (size_t)(BLK / WAVE) * 8 * 1024, s, a, n_pairs, pairs, role,

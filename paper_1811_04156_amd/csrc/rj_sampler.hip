@@ -107,83 +107,6 @@ __device__ __forceinline__ V3<R> segment_score(const Tgt<R>& T, int off, const S
     return u;
 }
 
-// The score of one path by one lane, fed a vertex at a time: step(f_k) takes
-// vertex k >= 1 and, with G, gives the gradient of vertex k - 2, finish() adds
-// the end term and gives log p and the gradients of vertices n - 2 and n - 1.
-// The terms and their order within a vertex are segment_grad's.
-template <class R, bool G> struct PathWalk {
-    V3<R> gA, gB; // gradients of vertices k - 2 and k - 1 so far
-    V3<R> fprev, uprev;
-    R lprev;
-    LPt<R> pprev;
-    double lp = 0.0;
-    bool length = true; // every segment so far has one
-    int k = 1;
-
-    __device__ __forceinline__ PathWalk(const Tgt<R>& T, V3<R> f0) : fprev(f0), pprev(lpt(T, f0)) {
-        gA = gB = uprev = V3<R>{(R)0, (R)0, (R)0};
-        lprev = (R)0;
-    }
-    __device__ __forceinline__ void step(const Tgt<R>& T, V3<R> f, V3<R>& out) {
-        const LPt<R> p = lpt(T, f);
-        const Seg<R> s = make_seg_lp(T, fprev, f, pprev, p);
-        length &= s.len > (R)0;
-        lp += (double)seg_term(s);
-        V3<R> gC;
-        if (G) {
-            V3<R> dP, dQ;
-            seg_depth_grad_lp(T, pprev, p, s, dP, dQ);
-            const R il = (R)2 * Mth<R>::rcp(s.len);
-            const V3<R> z = {(R)0, (R)0, (R)0};
-            gB = gB - dP + il * s.u;
-            gC = z - dQ - il * s.u;
-        }
-        if (k == 1) {
-            lp += (double)emit_term(T, s.u);
-            if (G && T.ek == RJPATH_EMIT_VMF) gC = gC + T.kappa * dunit(s.u, s.len, T.ed);
-        } else {
-            const LayV<R> ly = lay_at(T, pprev.l);
-            lp += (double)(ly.logb + turn_term(ly, uprev, s.u));
-            if (G) {
-                const V3<R> dd = uprev - s.u;
-                const R h = dturn_dmu(ly, dot(dd, dd));
-                const V3<R> da = dunit(uprev, lprev, s.u), db = dunit(s.u, s.len, uprev);
-                gA = gA - h * da;
-                gB = gB + h * da - h * db;
-                gC = gC + h * db;
-            }
-        }
-        if (G) {
-            out = gA;
-            gA = gB;
-            gB = gC;
-        }
-        uprev = s.u;
-        lprev = s.len;
-        fprev = f;
-        pprev = p;
-        ++k;
-    }
-    __device__ __forceinline__ double finish(const Tgt<R>& T, V3<R>& g2, V3<R>& g1) {
-        lp += (double)end_term(T, uprev, fprev);
-        if (G) {
-            const V3<R> d = from_eta(T, fprev);
-            const R dn2 = dot(d, d), idn = Mth<R>::rsqrt(dn2);
-            const V3<R> nu = idn * d;
-            const R ic = Mth<R>::rcp(-dot(uprev, nu));
-            const V3<R> dcr = (R)-1 * dunit(uprev, lprev, nu), dcd = (R)-1 * dunit(nu, dn2 * idn, uprev);
-            g2 = gA - ic * dcr;
-            g1 = gB + ic * dcr + ic * dcd;
-            if (T.dk == RJPATH_DET_PAPER) {
-                const R cr = dot(nu, T.dd);
-                const R th = tanh((R)2 * cr + (R)0.7);
-                g1 = g1 + ((R)3 - (R)2 * th) * dunit(nu, dn2 * idn, T.dd);
-            }
-        }
-        return length ? lp : -__builtin_inf();
-    }
-};
-
 // The wave's vertices: vertex i of its chains in order, the first `M` in LDS.
 template <class R> struct WaveStrip {
     LdsPtr<R> lds;

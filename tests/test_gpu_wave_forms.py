@@ -85,3 +85,40 @@ def test_score_pass_by_items_and_by_lanes(rj, prec, medium):
             res.append((lp.cpu().numpy()[back], g.cpu().numpy()[:, back], sc.cpu().numpy()))
         assert np.allclose(res[0][0], res[1][0], rtol=1e-13, atol=1e-13) and np.array_equal(res[0][1], res[1][1])
         assert np.allclose(res[0][2], res[1][2], rtol=1e-12, atol=1e-12 * np.abs(res[0][2]).max())
+
+
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+def test_bridge_by_vertices_and_by_lanes(rj, prec):
+    """The bridge's waves share their chains' vertices or give each lane its
+    own chain's, by their lengths and targets.  The same paths grouped by
+    target with every wave's lengths alike, mixed, and dealt out over six
+    targets give the same log r (FP64 sums of about 60 terms of magnitude up to
+    1e2 in another order: 1e-11), NaN for the pair whose second sensor lies on
+    the emission axis (no map), and the same sums.  FP64: the oracle's log r to
+    1e-8."""
+    from oracle import oracle as O
+    from paper_1811_04156_amd.table1 import replicate
+    w = replicate(W.two_region(b1=0.3, scale=0.1, radius=(0.15, 0.3), chains_per_sensor=1, cap=24), 3, 256)
+    C = len(w["c_target"])
+    orc = O.Oracle(w)
+    n, V = random_paths(orc, w, np.random.default_rng(5), 20)
+    t = np.asarray(w["c_target"])
+    orders = [np.lexsort((n, t)), np.lexsort((np.arange(C) * 7919 % C, t)), np.arange(C) % 6 * 256 + np.arange(C) // 6]
+    out = []
+    for order in orders:
+        wo = dict(w)
+        wo["c_target"] = t[order]
+        s = rj.Sampler(wo, precision=prec)
+        s.set_state(n[order], V[order])
+        acc, lr = s.yield_accumulate(s.yield_pairs([(0, 1), (2, 3), (5, 4)]), groups=2, logr=True)
+        out.append((lr.cpu().numpy()[np.argsort(order, kind="stable")], acc.cpu().numpy().sum(2)))
+    a, sums = out[0]
+    assert np.all(np.isnan(a[t >= 4])) and np.all(sums[2] == 0)
+    assert np.isfinite(a[t < 4]).sum() > 400
+    for b, other in out[1:]:
+        assert np.allclose(a, b, rtol=1e-11, atol=1e-11, equal_nan=True)
+        assert np.allclose(sums, other, rtol=1e-10)
+    if prec == "f64":
+        for c in range(0, 4 * 256, 29):
+            ref = orc.yield_log_ratio(t[c] // 2 * 2, t[c] // 2 * 2 + 1, t[c] % 2, V[c, : n[c]])
+            assert (a[c] == -np.inf and not np.isfinite(ref)) or abs(a[c] - ref) < 1e-8, (c, a[c], ref)
