@@ -408,59 +408,72 @@ __global__ void __launch_bounds__(256, 2) anchor_lean_kernel(KArgs a, const doub
     if (threadIdx.x == 0) out[blockIdx.x] = s;
 }
 
+// n0 = 2: a 64 x 64 product rule, one block per target.  Targets without an
+// anchor sector: NaN.  (The call for 200 direct sectors: 62 us, 7 of them the
+// other kernels' launches; with the rule spread over the chunks of the general
+// kernel, whose blocks read their targets each for themselves, 100; with all
+// three in one kernel 83.)
+__global__ void __launch_bounds__(256) anchor_direct_kernel(KArgs a, const double* gx, const double* gw,
+                                                            double* anchor) {
+    const int t = blockIdx.x;
+    // block-uniform guards: every thread of the block leaves together
+    if (a.medium[t] < 0 || a.medium[t] >= a.n_media || (a.n0[t] != 2 && a.n0[t] != 3)) {
+        if (threadIdx.x == 0) anchor[t] = __builtin_nan("");
+        return;
+    }
+    if (a.n0[t] != 2) return;
+    Tgt<double> T;
+    load_target<double>(a, t, T, MedTab<double>{a.lay64, a.edge, a.pre});
+    __shared__ double red[256];
+    const double* x64 = gx + 56; const double* w64 = gw + 56;
+    double part = 0.0;
+    // one direction per thread-iteration
+    for (int i = threadIdx.x; i < 64 * 64; i += blockDim.x) {
+        int iv = i / 64, ip = i % 64;
+        V3<double> dv = T.eta;
+        double D = sqrt(dot(dv, dv)), Rr = (double)T.rad;
+        V3<double> ax = (1.0 / D) * dv, e2, e3;
+        frame(ax, e2, e3);
+        double k2 = Rr * Rr / (D * D);
+        double v = x64[iv], wv = w64[iv];
+        double s2 = k2 * (1 - v * v), ct = sqrt(1 - s2), st = sqrt(s2);
+        double len = D * ct - Rr * v, jac = k2 * v / ct;
+        double ps = 2 * PI * (ip + 0.5) / 64, sp, cp;
+        sincos(ps, &sp, &cp);
+        V3<double> u = ct * ax + st * (cp * e2 + sp * e3);
+        V3<double> hit = len * u;
+        V3<double> nu = (1.0 / Rr) * (hit - T.eta);
+        double le = emit_term(T, u);
+        if (le == -__builtin_inf()) continue;
+        V3<double> o = {0, 0, 0};
+        part += wv * (2 * PI / 64) * jac * exp(le - depth_c(T, o, hit) + log_rho(T, nu));
+    }
+    const double s = block_sum(part, red);
+    if (threadIdx.x == 0) anchor[t] = s;
+}
+
 __global__ void __launch_bounds__(256) anchor_kernel(KArgs a, const double* gx, const double* gw, int nchunk,
                                                      double* out) {
     const int t = blockIdx.x / nchunk, chunk = blockIdx.x % nchunk;
-    // block-uniform guard: every thread of the block leaves together
-    if (a.medium[t] < 0 || a.medium[t] >= a.n_media || (a.n0[t] != 2 && a.n0[t] != 3)) {
-        if (threadIdx.x == 0) out[blockIdx.x] = __builtin_nan("");
-        return;
-    }
+    if (a.medium[t] < 0 || a.medium[t] >= a.n_media || a.n0[t] != 3) return;
     Tgt<double> T;
     load_target<double>(a, t, T, MedTab<double>{a.lay64, a.edge, a.pre});
     if (lean_target(a, t, T, sensor_layers(T))) return;
     __shared__ double red[256];
-    double part = 0.0;
-    // Gauss-Legendre tables on [0,1]: rule k of size m_k at offset o_k
-    // (sizes 8, 16, 32, 64 stored back to back)
-    const double* x8 = gx;       const double* w8 = gw;
-    const double* x64 = gx + 56; const double* w64 = gw + 56;
-    if (a.n0[t] == 2) {
-        // 64 x 64 product rule, one direction per thread-iteration
-        for (int i = chunk * blockDim.x + threadIdx.x; i < 64 * 64; i += nchunk * blockDim.x) {
-            int iv = i / 64, ip = i % 64;
-            V3<double> dv = T.eta;
-            double D = sqrt(dot(dv, dv)), Rr = (double)T.rad;
-            V3<double> ax = (1.0 / D) * dv, e2, e3;
-            frame(ax, e2, e3);
-            double k2 = Rr * Rr / (D * D);
-            double v = x64[iv], wv = w64[iv];
-            double s2 = k2 * (1 - v * v), ct = sqrt(1 - s2), st = sqrt(s2);
-            double len = D * ct - Rr * v, jac = k2 * v / ct;
-            double ps = 2 * PI * (ip + 0.5) / 64, sp, cp;
-            sincos(ps, &sp, &cp);
-            V3<double> u = ct * ax + st * (cp * e2 + sp * e3);
-            V3<double> hit = len * u;
-            V3<double> nu = (1.0 / Rr) * (hit - T.eta);
-            double le = emit_term(T, u);
-            if (le == -__builtin_inf()) continue;
-            V3<double> o = {0, 0, 0};
-            part += wv * (2 * PI / 64) * jac * exp(le - depth_c(T, o, hit) + log_rho(T, nu));
-        }
-    } else {
-        part = one_scatter(T, gx, gw, chunk, nchunk, [&](const LayV<double>& ly, V3<double> f1, int l, V3<double> w0,
-                                                         double uP, double half) {
-            return cap_quad(T, f1, x8, w8, 8, half > 0 ? 0 : 4, 4, 8,
-                            [&](V3<double> u) { return turn_term(ly, w0, u); });
-        });
-    }
+    const double* x8 = gx;
+    const double* w8 = gw;
+    const double part = one_scatter(T, gx, gw, chunk, nchunk, [&](const LayV<double>& ly, V3<double> f1, int l,
+                                                                  V3<double> w0, double uP, double half) {
+        return cap_quad(T, f1, x8, w8, 8, half > 0 ? 0 : 4, 4, 8, [&](V3<double> u) { return turn_term(ly, w0, u); });
+    });
     const double s = block_sum(part, red);
     if (threadIdx.x == 0) out[blockIdx.x] = s;
 }
 
-// anchor[t] = the sum of its chunks, in a fixed order
-__global__ void __launch_bounds__(64) anchor_sum_kernel(int nchunk, const double* part, double* anchor) {
+// anchor[t] = the sum of its chunks, in a fixed order (targets of one scattering vertex)
+__global__ void __launch_bounds__(64) anchor_sum_kernel(KArgs a, int nchunk, const double* part, double* anchor) {
     const int t = blockIdx.x;
+    if (a.medium[t] < 0 || a.medium[t] >= a.n_media || a.n0[t] != 3) return;
     double s = 0.0;
     for (int i = threadIdx.x; i < nchunk; i += 64) s += part[(size_t)t * nchunk + i];
 #pragma unroll
@@ -486,11 +499,12 @@ hipError_t launch_anchor(const KArgs& a, const double* gl_x, const double* gl_w,
         nchunk = 1;
         part = anchor;
     }
+    hipLaunchKernelGGL(anchor_direct_kernel, dim3(a.T), dim3(256), 0, s, a, gl_x, gl_w, anchor);
     hipLaunchKernelGGL(anchor_lean_kernel, dim3(a.T * nchunk), dim3(256), 0, s, a, gl_x, gl_w, nchunk, part);
     hipLaunchKernelGGL(anchor_kernel, dim3(a.T * nchunk), dim3(256), 0, s, a, gl_x, gl_w, nchunk, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || nchunk == 1) return e;
-    hipLaunchKernelGGL(anchor_sum_kernel, dim3(a.T), dim3(64), 0, s, nchunk, part, anchor);
+    hipLaunchKernelGGL(anchor_sum_kernel, dim3(a.T), dim3(64), 0, s, a, nchunk, part, anchor);
     return hipGetLastError();
 }
 

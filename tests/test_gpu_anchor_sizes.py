@@ -42,3 +42,37 @@ def test_anchor_of_many_targets(rj, targets):
     rest[at] = False
     assert np.all(np.isnan(an[rest]))
     assert np.allclose(an[at], few[at % 8], rtol=1e-12, atol=0)
+
+
+@pytest.mark.parametrize("targets", [1, 7, 300])
+def test_anchor_of_mixed_sectors(rj, targets):
+    """Direct sectors, one-scatter sectors of both cap forms and targets
+    without an anchor sector side by side, each by the kernel of its own: what
+    a call with the one target gives (its sum over as many blocks as a call of
+    all has: 1e-12), the same bits in a second call, and the device call's
+    (rjpath_intensity_noalloc's anchors: 1e-12)."""
+    w = W.layered_pairs(seed=13, pairs=8, chains=8, cap=8, n_layers=9, dz=4.0, dmin=4.0, dmax=25.0)
+    w["t_n0"] = np.array([2, 3, 3, 0, 2, 3, 7, 3], np.int32)
+    w["t_emit_kind"] = np.where(w["t_n0"] == 2, W.EMIT_ISO, w["t_emit_kind"]).astype(np.int32)
+    w["t_det_kind"] = np.array([0, 1, 0, 0, 1, 0, 0, 1], np.int32)
+    w["t_det_dir"] = np.tile([0.0, -1.0, 0.0], (8, 1))
+
+    def pick(ix):
+        v = dict(w)
+        for k in w:
+            if k.startswith("t_"):
+                v[k] = np.asarray(w[k])[ix]
+        v["c_target"] = np.zeros(64, np.int32)
+        return v
+
+    one = np.array([rj.Sampler(pick(np.array([t])), precision="f32").anchor()[0] for t in range(8)])
+    none = ~np.isin(w["t_n0"], (2, 3))
+    assert np.array_equal(np.isnan(one), none)
+    ix = (np.arange(targets) * 3 + 1) % 8
+    s = rj.Sampler(pick(ix), precision="f32")
+    an = s.anchor()
+    assert np.allclose(an, one[ix], rtol=1e-12, atol=0, equal_nan=True)
+    assert np.array_equal(s.anchor(refresh=True), an, equal_nan=True)
+    s.run(200, run=dict(burn_in=0))
+    I = [s.intensity_noalloc(anchor=x)["I"].cpu().numpy() for x in (None, torch.as_tensor(an, device=s.dev))]
+    assert np.allclose(I[0], I[1], rtol=1e-12, atol=0, equal_nan=True)
