@@ -508,9 +508,12 @@ hipError_t launch_yield(const KArgs& a, int n_pairs, const int32_t* pairs, const
 
 hipError_t launch_lhist(const KArgs& a, int bins, double l0, double width, double* hist, hipStream_t s) {
     const int grid = (a.C + BLK - 1) / BLK;
-    // lanes per chain: as many as keep the launch within eight waves per SIMD
+    // lanes per chain: as many as keep the launch within four waves per SIMD
+    // (chains of mean n 10 and 42, 1, 2 and 4 lanes each, us: 65,536 25, 21, 19 and
+    // 98, 67, 52; 131,072 34, 27, 25 and 107, 92, 85, but 17, 17, 18 at mean n 4;
+    // 262,144 37, 38, 43 and 165, 165, 193)
     int parts = LHIST_PARTS;
-    while (parts > 1 && (long long)a.C * parts > 32LL * device_cus() * WAVE) parts /= 2;
+    while (parts > 1 && (long long)a.C * parts > 16LL * device_cus() * WAVE) parts /= 2;
     const dim3 block(BLK * parts);
     const size_t lds = 2 * sizeof(double) * ((size_t)bins + 1);
     const int use = lds <= 64 * 1024;

@@ -122,3 +122,22 @@ def test_bridge_by_vertices_and_by_lanes(rj, prec):
         for c in range(0, 4 * 256, 29):
             ref = orc.yield_log_ratio(t[c] // 2 * 2, t[c] // 2 * 2 + 1, t[c] % 2, V[c, : n[c]])
             assert (a[c] == -np.inf and not np.isfinite(ref)) or abs(a[c] - ref) < 1e-8, (c, a[c], ref)
+
+
+@pytest.mark.parametrize("chains", [65_537, 131_072, 131_073])
+def test_length_hist_at_its_lines(rj, chains):
+    """Four lanes sum a chain's segments up to 65,536 chains (256 CUs), two up
+    to 131,072, one beyond: every chain is counted once, in the bin of its own
+    length (none lies within 1e-9 of an edge)."""
+    w = W.single_target(1.5, 0.165, 0.05, 50.0, 0.9, chains=chains, cap=24, burn_in=0, seed=56)
+    s = rj.Sampler(w, precision="f32")
+    s.run(200)
+    torch.cuda.synchronize()
+    h = s.length_hist(30, 1.0, 0.1).cpu().numpy().ravel()
+    used = torch.arange(1, s.cap, device=s.dev)[:, None] < s.n
+    x = s.verts[..., :3].double()
+    L = torch.where(used, (x[1:] - x[:-1]).norm(dim=-1), 0.0).sum(0).cpu().numpy()
+    at = (L - 1.0) / 0.1
+    assert np.abs(at - np.round(at)).min() > 1e-9
+    want = np.bincount(np.floor(at[(at >= 0) & (at < 30)]).astype(int), minlength=30)
+    assert np.array_equal(h[:30], want) and h[30] == chains
