@@ -333,13 +333,23 @@ size_t slot_budget(const rjpath_medium* m, const rjpath_targets* t, const rjpath
 // deal out where its targets differ (100,000 and 131,072 chains of tree moves
 // with 64 and 32 per wave: 2.80 and 2.33 ms, 2.98 and 2.64; 200,000 of joint
 // moves: 8.65 and 8.01; 262,144 of tree moves, beyond the line: 4.28 and 5.37).
+// A launch also loads its paths and forms their log p, by lane, at its begin and
+// end, so one of few steps takes more chains per wave: no doubling before all
+// 64 below 16 steps (131,072 chains of tree moves with 32 and 64 per wave: 2 steps
+// 111 and 96 us, 10 steps 257 and 245, 20 steps 376 and 446; 262,144 of joint
+// moves: 1 step 196 and 162, 5 steps 482 and 472, 20 steps 1236 and 1637), and two
+// waves per SIMD for joint moves too below 4 (131,072: 1 step 121 and 108).
 bool shares_moves(int sampler) { return sampler == RJPATH_TREE || sampler == RJPATH_MALA; }
 
-int shared_cpw(int sampler, int n_chains) {
-    const long long waves = (sampler == RJPATH_MALA ? 4LL : 2LL) * 4 * device_cus();
+// steps of a launch of the call
+int launch_steps(const rjpath_run_params* p) { return p->chunk > 0 ? std::min(p->chunk, p->steps) : p->steps; }
+
+int shared_cpw(int sampler, int n_chains, int steps) {
+    const long long waves = (sampler == RJPATH_MALA && steps >= 4 ? 4LL : 2LL) * 4 * device_cus();
+    const int most = steps >= 16 ? 2 : 1;
     int cpw = 1;
     while (cpw < 8 && (long long)n_chains > 4LL * device_cus() * cpw) cpw *= 2;
-    while (cpw >= 8 && cpw < 64 && (long long)n_chains > (cpw == 32 ? 2 : 1) * waves * cpw) cpw *= 2;
+    while (cpw >= 8 && cpw < 64 && (long long)n_chains > (cpw == 32 ? most : 1) * waves * cpw) cpw *= 2;
     return cpw;
 }
 
@@ -361,11 +371,11 @@ int shared_cpw(int sampler, int n_chains) {
 //    chains each).  (Halving the slots so that the proposals of 64-chain waves
 //    fit LDS too made the tree step itself no faster, 122 against 113 us for
 //    262,144 chains of the ragged batch then, and the jumps slower.)
-void default_launch(const rjpath_chains* c, size_t tab_bytes, int sampler, int& block, int& V) {
+void default_launch(const rjpath_chains* c, size_t tab_bytes, int sampler, int steps, int& block, int& V) {
     const int cap = c->cap;
     const int cus = device_cus();
     const bool shared = shares_moves(sampler);
-    const int cpw = shared ? shared_cpw(sampler, c->n_chains) : 64;
+    const int cpw = shared ? shared_cpw(sampler, c->n_chains, steps) : 64;
     block = 64;
     V = std::min(cap, c->precision == RJPATH_F64 ? 16 : 32);
     const long long blocks = ((long long)c->n_chains + cpw - 1) / cpw;
@@ -418,7 +428,7 @@ int run_impl(rjpath_medium* m, const rjpath_targets* t, const rjpath_chains* c, 
     a.hist = p->hist;
     a.step_dev = p->step_counter;
     if (shares_moves(p->sampler)) {
-        a.cpw = shared_cpw(p->sampler, c->n_chains);
+        a.cpw = shared_cpw(p->sampler, c->n_chains, launch_steps(p));
         if (a.cpw == 64) {
             // LDS slots for the proposals: what the blocks that fit a CU leave
             const size_t per = (size_t)block * vtx_bytes(c->precision), x = a.tab_bytes + (size_t)(V + 2) * per;
@@ -482,7 +492,7 @@ int rjpath_run_chains(rjpath_medium* m, const rjpath_targets* t, const rjpath_ch
     if (r) return r;
     if (p->steps == 0) return RJPATH_OK;
     int block, V;
-    default_launch(c, make_args(m, t, c).tab_bytes, p->sampler, block, V);
+    default_launch(c, make_args(m, t, c).tab_bytes, p->sampler, launch_steps(p), block, V);
     auto it = m->tuned.find(TuneKey{c->cap, c->precision, p->sampler});
     if (it != m->tuned.end()) {
         block = it->second.first;
@@ -511,7 +521,7 @@ int rjpath_autotune(rjpath_medium* m, const rjpath_targets* t, const rjpath_chai
     {
         // the default launch is always a candidate
         int db, dv;
-        default_launch(c, make_args(m, t, c).tab_bytes, p->sampler, db, dv);
+        default_launch(c, make_args(m, t, c).tab_bytes, p->sampler, launch_steps(p), db, dv);
         if ((size_t)(dv + 2) * db * vtx_bytes(c->precision) <= budget) cand.push_back({db, dv});
     }
     for (int b : {64, 256})

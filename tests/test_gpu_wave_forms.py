@@ -141,3 +141,24 @@ def test_length_hist_at_its_lines(rj, chains):
     assert np.abs(at - np.round(at)).min() > 1e-9
     want = np.bincount(np.floor(at[(at >= 0) & (at < 30)]).astype(int), minlength=30)
     assert np.array_equal(h[:30], want) and h[30] == chains
+
+
+@pytest.mark.parametrize("sampler,h,chains", [(3, 0.3, 131_072), (1, 0.01, 131_073)])
+def test_launches_of_few_steps(rj, sampler, h, chains):
+    """Launches of fewer than 4 and 16 steps of the whole-path samplers take
+    more chains per wave (tree moves 64 instead of 32, joint Langevin moves 64
+    at 1 step, 32 at 4): the same paths however the steps are cut, by calls and
+    by the chunks of one."""
+    w = W.layered_pairs(seed=14, pairs=60, chains=chains, cap=40, n_layers=12, dz=4.0, dmin=4.0, dmax=25.0)
+    w.update(sampler=sampler, mala_h=h, burn_in=0, sigma=2.0)
+    out = []
+    for parts, chunk in (((24,), 0), ((1, 3, 4, 15, 1), 0), ((24,), 3)):
+        s = rj.Sampler(w, precision="f32")
+        for k in parts:
+            s.run(k, chunk=chunk)
+        torch.cuda.synchronize()
+        used = torch.arange(s.cap, device=s.dev)[:, None] < s.n
+        out.append((s.n.clone(), torch.where(used[..., None], s.verts[..., :3], 0.0).clone(), s.status.clone()))
+    for x in out[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(x, out[0]))
+    assert out[0][0].max() > 4 and out[0][2].sum() == 0
