@@ -129,7 +129,9 @@ typedef struct {
  * hold nothing (RJPATH_MALA and RJPATH_TREE runs write there).  logp[c]
  * receives log p of the final path; status[c] is 0 for a healthy chain and 1 if
  * its starting path had zero or non-finite density (such a chain is not moved
- * and adds nothing to the statistics).
+ * and adds nothing to the statistics).  A run of many chains keeps the order of
+ * its waves in bits 8 and up of the status words while it is in flight: read them
+ * behind it on its stream.
  * work: scratch of the size of verts, contents of no meaning between the calls
  * (required for RJPATH_MALA and RJPATH_TREE, else may be NULL). */
 typedef struct {

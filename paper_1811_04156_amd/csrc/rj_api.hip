@@ -398,8 +398,8 @@ void default_launch(const rjpath_chains* c, size_t tab_bytes, int sampler, int s
 }
 
 // Waves of a launch whose order is worth finding (launch_order, about 10 us): of
-// one with more blocks than the chip holds (two waves per SIMD, the CU's LDS),
-// and from ORDER_STEPS steps on (16 steps of 262,144 and 1,048,576 chains of the
+// one with more blocks than the chip holds (two waves per SIMD, the CU's LDS), of
+// at most ORDER_WAVES waves, and from ORDER_STEPS steps on (16 steps of 262,144 and 1,048,576 chains of the
 // ragged batch gain 1 to 2%, 200 steps 5 to 20%).  0: none.
 constexpr int ORDER_STEPS = 16;
 int ordered_waves(const KArgs& a, int block, int per, int precision) {
@@ -446,10 +446,16 @@ int run_impl(rjpath_medium* m, const rjpath_targets* t, const rjpath_chains* c, 
         a.ordered = a.steps >= ORDER_STEPS ? waves : 0;
         if (a.ordered) {
             hipError_t e = launch_order(a, per, s);
-            if (e != hipSuccess) return hip_fail(e, "order kernel launch");
+            if (e != hipSuccess) {
+                clear_order(a, per, s);
+                return hip_fail(e, "order kernel launch");
+            }
         }
         hipError_t e = launch_run(a, block, s);
-        if (e != hipSuccess) return hip_fail(e, "run kernel launch");
+        if (e != hipSuccess) {
+            if (a.ordered) clear_order(a, per, s);
+            return hip_fail(e, "run kernel launch");
+        }
     }
     if (p->step_counter) {
         hipError_t e = launch_advance(p->step_counter, (uint64_t)p->steps, s);

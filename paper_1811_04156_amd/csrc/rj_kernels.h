@@ -18,6 +18,7 @@ hipError_t set_run_lds_limit();
 // (at most ORDER_WAVES; rj_order.hip)
 constexpr int ORDER_BINS = 1024, ORDER_WAVES = 16 * ORDER_BINS;
 hipError_t launch_order(const KArgs& a, int per, hipStream_t s);
+void clear_order(const KArgs& a, int per, hipStream_t s);
 // the step-kernel variants of one precision and interior move (0 plain, 1
 // joint Langevin, 2 single-vertex Langevin, 3 tree coordinates; defined in rj_run.h,
 // instantiated once each in the rj_run_*.hip units)

@@ -19,12 +19,23 @@ namespace {
 // blocks, 4.78, 1.80, 3.30 and 5.23.)
 // The order lies in the status words of the first chains until the waves have
 // read it (take_order): bits 8 and up of word i are the place of wave i's chains.
+// Bits 0 to 7, the status itself, are nobody's but the chain's.
+// One block sorts, with 16 weights per thread in registers: launches of more than
+// ORDER_WAVES waves keep the order of the chains.  (The gain falls with the rounds
+// that a launch takes: above, 7 to 16% at two rounds and 5% at eight, which
+// ORDER_WAVES waves are.)
 
-// vertices of each wave's chains into word b
+// bits 8 and up of a status word
+__device__ __forceinline__ void put_order(int32_t* word, uint32_t v) {
+    ((volatile uint8_t*)word)[1] = (uint8_t)v;
+    ((volatile uint16_t*)word)[1] = (uint16_t)(v >> 8);
+}
+
+// vertices of each wave's chains (at most 64 x 4096) into word b
 __global__ void __launch_bounds__(64) weight_kernel(const int32_t* n, int C, int cap, int per, int32_t* status) {
     const int b = blockIdx.x, lane = threadIdx.x, c = b * per + lane;
     const int all = wave_prefix(lane < per && c < C ? min(max(n[c], 0), cap) : 0);
-    if (lane == 63) status[b] = all;
+    if (lane == 63) put_order(status + b, (uint32_t)all);
 }
 
 // most vertices first: a counting sort of the nb <= ORDER_WAVES weights over
@@ -37,7 +48,7 @@ __global__ void __launch_bounds__(ORDER_BINS) order_kernel(int nb, int32_t* stat
 #pragma unroll
     for (int i = 0; i < K; ++i) {
         const int b = i * ORDER_BINS + tid;
-        w[i] = b < nb ? status[b] : 0;
+        w[i] = b < nb ? (int)((uint32_t)status[b] >> 8) : 0;
         big = max(big, w[i]);
     }
     bins[tid] = 0;
@@ -62,11 +73,22 @@ __global__ void __launch_bounds__(ORDER_BINS) order_kernel(int nb, int32_t* stat
 #pragma unroll
     for (int i = 0; i < K; ++i) {
         const int b = i * ORDER_BINS + tid;
-        if (b < nb) status[atomicAdd(&bins[w[i]], 1)] = b << 8;
+        if (b < nb) put_order(status + atomicAdd(&bins[w[i]], 1), (uint32_t)b);
     }
 }
 
+__global__ void __launch_bounds__(256) clear_kernel(int nb, int32_t* status) {
+    const int b = blockIdx.x * 256 + threadIdx.x;
+    if (b < nb) put_order(status + b, 0u);
+}
+
 } // namespace
+
+// Takes the order back where no launch follows to read it.
+void clear_order(const KArgs& a, int per, hipStream_t s) {
+    const int nb = (a.C + per - 1) / per;
+    hipLaunchKernelGGL(clear_kernel, dim3((nb + 255) / 256), dim3(256), 0, s, nb, a.status);
+}
 
 hipError_t launch_order(const KArgs& a, int per, hipStream_t s) {
     const int nb = (a.C + per - 1) / per;

@@ -162,3 +162,28 @@ def test_launches_of_few_steps(rj, sampler, h, chains):
     for x in out[1:]:
         assert all(torch.equal(a, b) for a, b in zip(x, out[0]))
     assert out[0][0].max() > 4 and out[0][2].sum() == 0
+
+
+def test_order_at_its_largest_launch(rj):
+    """A launch of 16,384 waves is ordered, one of a wave more is not: the same
+    paths, and status words of 0 and 1 alone.  The order is kept beside the
+    status in its words, so a chain that was flagged before the launch and one
+    with other bits set end as flagged or not by this launch."""
+    chains = 64 * 16_384 + 1
+    w = W.layered_pairs(seed=15, pairs=90, chains=chains, cap=12, n_layers=12, dz=4.0, dmin=4.0, dmax=25.0)
+    w.update(burn_in=0, sigma=2.0)
+    out = []
+    for k in (chains, chains - 1):
+        s = rj.Sampler(W.subset_chains(w, k), precision="f32")
+        s.n[5] = 13
+        s.status.fill_(1)
+        s.status[::3] = 0x01020304
+        s.run(20)
+        torch.cuda.synchronize()
+        flagged = torch.zeros(k, dtype=s.status.dtype, device=s.dev)
+        flagged[5] = 1
+        assert torch.equal(s.status, flagged)
+        used = torch.arange(s.cap, device=s.dev)[:, None] < s.n
+        used[:, 5] = False
+        out.append((s.n[: chains - 1].clone(), torch.where(used[..., None], s.verts[..., :3], 0.0)[:, : chains - 1].clone()))
+    assert all(torch.equal(a, b) for a, b in zip(*out))
