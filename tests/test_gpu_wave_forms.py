@@ -187,3 +187,46 @@ def test_order_at_its_largest_launch(rj):
         used[:, 5] = False
         out.append((s.n[: chains - 1].clone(), torch.where(used[..., None], s.verts[..., :3], 0.0)[:, : chains - 1].clone()))
     assert all(torch.equal(a, b) for a, b in zip(*out))
+
+
+@pytest.mark.parametrize("per", [8, 16, 32, 64])
+@pytest.mark.parametrize("prec,sampler,h", [("f32", 1, 0.01), ("f64", 1, 0.01), ("f32", 3, 0.3), ("f64", 3, 0.3)])
+def test_far_vertices_of_waves_of_many_chains(rj, prec, sampler, h, per):
+    """Waves of 8 to 64 chains whose paths and proposals leave the LDS slots:
+    the paths are the same bit for bit whatever the slots (40: nothing leaves
+    them), malformed chains beside healthy ones in a wave keep every row they
+    have, and the proposals do lie in other chains' rows (a run without jumps,
+    where a chain of its own wave would write rows below its own n alone)."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    lines = {3: {8: 40, 16: 100, 32: 300, 64: 520}, 1: {8: 100, 16: 200, 32: 600, 64: 1030}}
+    chains = lines[sampler][per] * cus + 3
+    cap = 40
+    w = W.single_target(1.5, 0.165, 0.05, 50.0, 0.9, chains=chains, cap=cap, burn_in=0, seed=57)
+    w.update(sampler=sampler, mala_h=h)
+    bad = torch.tensor([5, per - 1, per, 3 * per + 2, 3 * per + 3, chains - 2])
+    out = []
+    for v in (cap, 3, 1):
+        s = rj.Sampler(w, precision=prec)
+        bad = bad.to(s.dev)
+        s.n[bad] = torch.tensor([0, 1, cap + 1, -7, 2**30, 1], dtype=s.n.dtype, device=s.dev)
+        marks = torch.arange(cap * 6 * 4, device=s.dev, dtype=s.verts.dtype).reshape(cap, 6, 4) + 0.5
+        s.verts[:, bad] = marks
+        for k in (100, 60):
+            s.run(k, block=64, v_lds=v)
+        torch.cuda.synchronize()
+        assert torch.equal(s.verts[:, bad], marks) and s.status[bad].tolist() == [1] * 6
+        assert s.status.sum() == 6
+        used = torch.arange(cap, device=s.dev)[:, None] < s.n
+        used[:, bad] = False
+        out.append((s.n.clone(), torch.where(used[..., None], s.verts[..., :3], 0.0).clone()))
+    assert out[0][0][out[0][0] < 41].max() > 8
+    for n, x in out[1:]:
+        assert torch.equal(n, out[0][0]) and torch.equal(x, out[0][1])
+    # (s: one slot) no jumps: n stays, rows from n on are written by others
+    rest = ~used
+    rest[:, bad] = False
+    s.verts[rest] = 0.0
+    s.run(20, run=dict(n_perturb=int(w["cycle_len"])), block=64, v_lds=1)
+    torch.cuda.synchronize()
+    assert torch.equal(s.n, out[0][0]) and torch.equal(s.verts[:, bad], marks)
+    assert (s.verts[..., :3].abs().sum(-1)[rest] > 0).sum() > chains // per
