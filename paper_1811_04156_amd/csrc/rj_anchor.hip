@@ -19,6 +19,7 @@
 
 #include "rj_device.h"
 #include "rj_kernels.h"
+#include "rj_math64.h"
 
 namespace rj {
 
@@ -88,37 +89,14 @@ __device__ V3<double> emit_dir_icdf(const Tgt<double>& T, double x, double ps) {
 }
 
 // FP64 reciprocal, reciprocal square root and exponential from the hardware's
-// starting values (good to about 2^-24) with one third-order correction, and
-// from the power series; arguments here are ordinary positive numbers, so the
-// library forms' handling of zeros, infinities and subnormals is not needed.
-// Relative errors stay below a few 2^-53.
-__device__ __forceinline__ double rcp64(double x) {
-    const double y = __builtin_amdgcn_rcp(x), e = fma(-x, y, 1.0);
-    return fma(y, fma(e, e, e), y); // y (1 + e + e^2)
-}
-__device__ __forceinline__ double rsq64(double x) {
-    const double y = __builtin_amdgcn_rsq(x), e = fma(-(x * y), y, 1.0);
-    return fma(y * e, fma(e, 0.375, 0.5), y); // y (1 + e / 2 + 3 e^2 / 8)
-}
+// starting values (good to 2^-24); arguments here are ordinary positive numbers,
+// so the library forms' handling of zeros, infinities and subnormals is not
+// needed.  Relative errors stay below 1, 1.5 and 2 times 2^-53.
+__device__ __forceinline__ double rcp64(double x) { return rcp_from(x, __builtin_amdgcn_rcp(x)); }
+__device__ __forceinline__ double rsq64(double x) { return rsq_from(x, __builtin_amdgcn_rsq(x)); }
 __device__ __forceinline__ double exp64(double x) {
-    const double k = rint(x * 1.4426950408889634074);
-    // ln 2 in two pieces (the first with 21 trailing zero bits, so k times it is exact)
-    double r = fma(k, -0x1.62e42fee00000p-1, x);
-    r = fma(k, -0x1.a39ef35793c76p-33, r);
-    double p = 1.0 / 6227020800.0; // 1 / 13!
-    p = fma(p, r, 1.0 / 479001600.0);
-    p = fma(p, r, 1.0 / 39916800.0);
-    p = fma(p, r, 1.0 / 3628800.0);
-    p = fma(p, r, 1.0 / 362880.0);
-    p = fma(p, r, 1.0 / 40320.0);
-    p = fma(p, r, 1.0 / 5040.0);
-    p = fma(p, r, 1.0 / 720.0);
-    p = fma(p, r, 1.0 / 120.0);
-    p = fma(p, r, 1.0 / 24.0);
-    p = fma(p, r, 1.0 / 6.0);
-    p = fma(p, r, 0.5);
-    p = fma(p, r, 1.0);
-    p = fma(p, r, 1.0);
+    double k;
+    const double p = exp_series(x, k);
     return __builtin_amdgcn_ldexp(p, (int)fmax(k, -3000.0));
 }
 
