@@ -203,8 +203,9 @@ __device__ __forceinline__ double full_logp(const Tgt<R>& T, const P& ps, int n,
 // segment, the emission at k = 0, the turn or the end at vertex k + 1), as
 // full_logp forms them; -inf where the segment or the next one, whose direction
 // the turn needs, has no length, so that the sum over a path with such a segment
-// is -inf, as full_logp's, and never NaN.
-template <class R>
+// is -inf, as full_logp's, and never NaN.  (NEXT false: NaN there; for a proposal,
+// which is rejected either way, 1% of a tree step.)
+template <class R, bool NEXT = true>
 __device__ __forceinline__ double walk_term(const Tgt<R>& T, int n, int k, V3<R> f0, V3<R> f1, V3<R> f2, R& tb) {
     const LPt<R> l0 = lpt(T, f0), l1 = lpt(T, f1);
     const Seg<R> s = make_seg_lp(T, f0, f1, l0, l1);
@@ -217,7 +218,7 @@ __device__ __forceinline__ double walk_term(const Tgt<R>& T, int n, int k, V3<R>
         const V3<R> r = f2 - f1;
         const R l2 = dot(r, r), il = Mth<R>::rsqrt(l2);
         t += (double)(ly.logb + turn_term(ly, s.u, il * r));
-        length &= l2 * il > (R)0;
+        if (NEXT) length &= l2 * il > (R)0;
     } else {
         t += (double)end_term(T, s.u, f1);
     }

@@ -210,8 +210,8 @@ __device__ __forceinline__ void tree_move(const Tgt<R>& T, const PathRef<R, fals
             cq.xs(v, x);
             cq.ys(v, y);
             R tx, ty;
-            const double a = walk_term(T, nq, k, x[0], x[1], x[2], tx);
-            const double b = walk_term(T, nq, k, y[0], y[1], y[2], ty);
+            const double a = walk_term<R, false>(T, nq, k, x[0], x[1], x[2], tx);
+            const double b = walk_term<R, false>(T, nq, k, y[0], y[1], y[2], ty);
             W.styw(cq.at + k, ty);
             W.add(q, b - a);
         }
