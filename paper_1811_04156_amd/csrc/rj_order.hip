@@ -25,17 +25,11 @@ namespace {
 // that a launch takes: above, 7 to 16% at two rounds and 5% at eight, which
 // ORDER_WAVES waves are.)
 
-// bits 8 and up of a status word
-__device__ __forceinline__ void put_order(int32_t* word, uint32_t v) {
-    ((volatile uint8_t*)word)[1] = (uint8_t)v;
-    ((volatile uint16_t*)word)[1] = (uint16_t)(v >> 8);
-}
-
 // vertices of each wave's chains (at most 64 x 4096) into word b
 __global__ void __launch_bounds__(64) weight_kernel(const int32_t* n, int C, int cap, int per, int32_t* status) {
     const int b = blockIdx.x, lane = threadIdx.x, c = b * per + lane;
     const int all = wave_prefix(lane < per && c < C ? min(max(n[c], 0), cap) : 0);
-    if (lane == 63) put_order(status + b, (uint32_t)all);
+    if (lane == 63) status[b] = all << 8 | (status[b] & 0xff);
 }
 
 // most vertices first: a counting sort of the nb <= ORDER_WAVES weights over
@@ -43,12 +37,15 @@ __global__ void __launch_bounds__(64) weight_kernel(const int32_t* n, int C, int
 __global__ void __launch_bounds__(ORDER_BINS) order_kernel(int nb, int32_t* status) {
     constexpr int K = ORDER_WAVES / ORDER_BINS;
     __shared__ int bins[ORDER_BINS], waves[ORDER_BINS / 64], most;
+    __shared__ uint8_t low[ORDER_WAVES]; // the words' own bits
     const int tid = threadIdx.x, lane = tid & 63;
     int w[K], big = 0;
 #pragma unroll
     for (int i = 0; i < K; ++i) {
         const int b = i * ORDER_BINS + tid;
-        w[i] = b < nb ? (int)((uint32_t)status[b] >> 8) : 0;
+        const uint32_t word = b < nb ? (uint32_t)status[b] : 0u;
+        low[b] = (uint8_t)word;
+        w[i] = (int)(word >> 8);
         big = max(big, w[i]);
     }
     bins[tid] = 0;
@@ -73,13 +70,16 @@ __global__ void __launch_bounds__(ORDER_BINS) order_kernel(int nb, int32_t* stat
 #pragma unroll
     for (int i = 0; i < K; ++i) {
         const int b = i * ORDER_BINS + tid;
-        if (b < nb) put_order(status + atomicAdd(&bins[w[i]], 1), (uint32_t)b);
+        if (b < nb) {
+            const int place = atomicAdd(&bins[w[i]], 1);
+            status[place] = b << 8 | low[place];
+        }
     }
 }
 
 __global__ void __launch_bounds__(256) clear_kernel(int nb, int32_t* status) {
     const int b = blockIdx.x * 256 + threadIdx.x;
-    if (b < nb) put_order(status + b, 0u);
+    if (b < nb) status[b] &= 0xff;
 }
 
 } // namespace

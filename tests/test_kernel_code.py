@@ -122,7 +122,7 @@ BUDGETS = {
                        (r"advance_kernel", 64, 0)],
     "rj_observe.hip": [(r"yield_kernelIf", TWO, 112), (r"yield_kernelId", ONE, 24), (r"lhist_kernelI[fd]", 64, 0)],
     "rj_anchor.hip": [(r"anchor_(lean_|direct_)?kernel", TWO, 0), (r"anchor_sum_kernel", 64, 0)],
-    "rj_order.hip": [(r"(weight|order)_kernel", 64, 0)],
+    "rj_order.hip": [(r"(weight|order|clear)_kernel", 64, 0)],
 }
 
 
