@@ -362,7 +362,7 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
 // with one ray per thread, the library's log, exp and sincos per node and two
 // layer lookups per node took 1.23 s for 200 targets of the 100-layer cone
 // batch (200 blocks on 256 CUs, one wave per SIMD, the rim targets four times
-// the rest); this form takes 17.3 ms (two waves per SIMD; forced to three or
+// the rest); this form takes 17.3 ms (15 to 19 over drawn targets; two waves per SIMD; forced to three or
 // four, with spills, 18.1 and 19.5 ms; the full exponential at every node 20.7).
 __global__ void __launch_bounds__(256, 2) anchor_lean_kernel(KArgs a, const double* gx, const double* gw, int nchunk,
                                                           double* out) {

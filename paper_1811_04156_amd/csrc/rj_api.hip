@@ -398,10 +398,10 @@ void default_launch(const rjpath_chains* c, size_t tab_bytes, int sampler, int s
 }
 
 // Waves of a launch whose order is worth finding (launch_order, 14 us for 4,096
-// waves, 26 for 16,384): of
-// one with more blocks than the chip holds (two waves per SIMD, the CU's LDS), of
-// at most ORDER_WAVES waves, and from ORDER_STEPS steps on (16 steps of 262,144 and 1,048,576 chains of the
-// ragged batch gain 1 to 2%, 200 steps 5 to 20%).  0: none.
+// waves, 26 for 16,384): of one with more blocks than the chip holds (two waves per
+// SIMD, the CU's LDS), of at most ORDER_WAVES waves, and from ORDER_STEPS steps on
+// (16 steps of 262,144 and 1,048,576 chains of the ragged batch gain 1 to 2%, 200
+// steps 5 to 20%).  0: none.
 constexpr int ORDER_STEPS = 16;
 int ordered_waves(const KArgs& a, int block, int per, int precision) {
     const size_t tile = (size_t)block * vtx_bytes(precision);

@@ -15,9 +15,9 @@ namespace rj {
 // vertex, then over the proposals, in both by the lanes of the chain's target
 // (share_lanes).  One lane per chain, walking path and proposal together, ran
 // each step until the wave's longest path was done: a joint step of 50,001
-// chains of the ragged layered batch (mean 6.4 vertices, longest 32) took 62 us
-// and takes 29, of which the slowest waves' far targets are about 20 (a median
-// wave's share is 8).  Where every chain's neighbours have other targets a lane is
+// chains of the ragged layered batch (mean 6.4 vertices, longest 32) took 62 us,
+// 29 once the items were shared (a median wave's share was 8, the slowest waves'
+// far targets about 20), and takes 20 since long waves start first (rj_order.hip).  Where every chain's neighbours have other targets a lane is
 // left with its own chain and still pays for items: 60 steps of 262,144 such
 // chains take 1.08 (layered) to 1.3 times (homogeneous, two-region) what one lane
 // per chain took in a kernel without items; with both forms in this one a lane per

@@ -16,7 +16,8 @@ namespace rj {
 // work buffer meanwhile.  Where they lie between the launches one cache line
 // holds one vertex of a chain.  (65,536 chains of the two-region test, per
 // step: a tree move, for which the paths were copied into this order each time,
-// took 468 us and takes 379, a perturbation 80 and takes 33; move_in and
+// took 468 us and takes 379 (368 since the root's frame has a branch of its own), a
+// perturbation 80 and takes 33; move_in and
 // move_out are about 50 us of a launch.)
 template <class R> struct WavePaths {
     LdsPtr<R> x, y;    // paths: slot 0 of column 0 of the wave's tile (stride WAVE); proposals: LDS vertex 0

@@ -17,9 +17,10 @@ namespace rj {
 // Shared: their vertices are read row by row (whole cache lines) into an LDS
 // strip, chain after chain without gaps, and the (chain, segment) items go over
 // all lanes: one lane per chain waits for the wave's longest path (mean n 6,
-// longest 25 to 40 on the ragged batches).  The kernel alone, 2^20 chains of the
-// ragged layered batch, score sums: 443 us by lanes, 205 shared (tables read from
-// HBM and two waves per SIMD: 315; a large copy moves the paths in 19).
+// longest 25 to 40 on the ragged batches).  The kernel alone, score sums of 2^20
+// chains: of a run of the ragged layered batch 443 us by lanes, 205 shared (tables
+// read from HBM and two waves per SIMD: 315); of snapshot paths of mean n 6, whose
+// 109 MB a large copy moves in 23, 460 and 241.
 // A lane per chain (PathWalk): where the lengths of a wave are alike, where
 // they overflow the strip and where neighbouring chains have different targets
 // that form is the better one (below).

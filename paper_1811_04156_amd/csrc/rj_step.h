@@ -5,7 +5,8 @@
 // launch.  The first V vertices of each chain live in LDS in a vertex-major,
 // lane-minor layout ([slot][lane]: per-lane random slots stay conflict-free),
 // the rest stay in the caller's HBM array (same [v][C] layout, read and
-// written coalesced at launch start and end).  When every lane of a wave fits
+// written coalesced at launch start and end; the samplers of whole-path moves keep
+// them chain after chain in the work buffer meanwhile, rj_paths.h).  When every lane of a wave fits
 // its LDS slots (a wave vote per step) the step runs a branch-free LDS-only
 // instantiation.  Layered media are staged in LDS once per block; a
 // homogeneous medium lives in registers.

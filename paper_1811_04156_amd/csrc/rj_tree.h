@@ -37,9 +37,9 @@ namespace rj {
 // over both walks of log p, and over the accepted proposals' copy-back.  The
 // terms of log A are summed per chain in FP64 in the tile's leading padding
 // slot, which nothing else keeps.  The walks need a chain's target, so the lanes
-// of one target share theirs (share_lanes).  With fewer chains than two waves
-// per SIMD a wave owns fewer than 64 chains (cpw), so that more waves share the
-// work.
+// of one target share theirs (share_lanes).  Where waves of 64 chains would leave
+// the chip waves short, a wave owns fewer (cpw, by shared_cpw in rj_api.hip).  The
+// same step takes 79 us.
 // ---------------------------------------------------------------------------
 // frame (e2, e3) of interval (k, l) of a path: root (uniform over the wave) ->
 // onb of the axis; otherwise from the parent interval (kp, lp) and its vertex fp.
