@@ -17,8 +17,8 @@ namespace rj {
 // each step until the wave's longest path was done: a joint step of 50,001
 // chains of the ragged layered batch (mean 6.4 vertices, longest 32) took 62 us,
 // 29 once the items were shared (a median wave's share was 8, the slowest waves'
-// far targets about 20), and takes 20 since long waves start first (rj_order.hip).  Where every chain's neighbours have other targets a lane is
-// left with its own chain and still pays for items: 60 steps of 262,144 such
+// far targets about 20), and takes 20 since long waves start first (rj_order.hip).
+// Where every chain's neighbours have other targets a lane is left with its own chain and still pays for items: 60 steps of 262,144 such
 // chains take 1.08 (layered) to 1.3 times (homogeneous, two-region) what one lane
 // per chain took in a kernel without items; with both forms in this one a lane per
 // chain takes 1.2 to 1.7 times as long.

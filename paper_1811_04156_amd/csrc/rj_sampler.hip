@@ -138,7 +138,10 @@ constexpr int SCORE_LAYERS = 16;
 // The weights are fitted to both forms over mean lengths of 3 to 42, ragged and
 // even, 1, 4, 16 and 64 targets per wave, 16,384 and 524,288 chains; they leave
 // the choice of the shared form where the two are close, since a launch of both
-// forms fetches the code of both.  us, shared and by lanes: log p, even layers,
+// forms fetches the code of both.  Vertices beyond the strip are read where they
+// lie, once for each of their segments, so an item costs more the more of them
+// there are (from four strips on; two regions, 524,288 ragged chains of mean 42,
+// log p: 732 and 390).  us, shared and by lanes: log p, even layers,
 // 524,288 chains, mean n 6, longest of a wave 16: 68 and 67, all 12: 82 and 40;
 // homogeneous, mean 42: 572 and 232; mixture, 16,384 chains, mean 11: 52 and 80;
 // FP64 gradients, 16,384 chains, even layers, mean 17: 92 and 129, all 12: 50 and 26;
@@ -155,7 +158,7 @@ __device__ __forceinline__ bool shares_segments(int n, int t, int lane, int tota
                : F64 ? (KIND == GK_ANY ? 10 : 12)
                      : KIND == GK_ANY ? (few ? 12 : 17) : KIND == GK_EVEN ? (few ? 18 : 24) : (few ? 20 : 28);
     const int load = F64 ? 5 : 8;
-    if (total > strip) item += F64 ? item / 8 : item / 4;
+    if (total > strip) item += F64 ? item / 8 : SCORE || total <= 4 * strip ? item / 4 : 3 * item / 4;
     const int cost = item * windows + load * min(windows, more);
     return __any(8 * (n - 1) >= cost);
 }

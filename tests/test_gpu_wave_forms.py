@@ -87,6 +87,46 @@ def test_score_pass_by_items_and_by_lanes(rj, prec, medium):
         assert np.allclose(res[0][2], res[1][2], rtol=1e-12, atol=1e-12 * np.abs(res[0][2]).max())
 
 
+@pytest.mark.parametrize("medium", ["homogeneous", "even", "uneven", "mixture"])
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+def test_score_pass_of_long_paths(rj, prec, medium):
+    """Ragged paths of up to 80 vertices, all in two waves (more than four of a
+    wave's LDS strips) and spread over eight among paths of up to 4: the same
+    vertex gradients bit for bit, log p up to the order of its FP64 terms (1e-13
+    relative), the score sums likewise (1e-12).  Against the oracle the bound of 20
+    vertices (2e-3 in FP32) times four."""
+    from oracle import oracle as O
+    C, cap = 512, 80
+    w = _workload(medium, C, cap)
+    w["c_target"] = np.zeros(C, np.int32)
+    orc = O.Oracle(w)
+    rng = np.random.default_rng(13)
+    n, V = random_paths(orc, w, rng, 80)
+    short, Vs = random_paths(orc, w, rng, 4)
+    n[128:], V[128:] = short[128:], Vs[128:]
+    assert all(n[c : c + 64].sum() > 4 * 7 * 64 for c in (0, 64))
+    out = []
+    for order in (np.arange(C), np.argsort(np.arange(C) % 128, kind="stable")):
+        s = rj.Sampler(w, precision=prec)
+        s.set_state(n[order], V[order])
+        lp, g, _ = s.grad(logp=True, dv=True)
+        lp2, _, sc = s.grad(logp=True, score=True)
+        lp3, g3, sc3 = s.grad(logp=True, dv=True, score=True)
+        lp4, _, _ = s.grad(logp=True)
+        back = np.argsort(order, kind="stable")
+        out.append(([x.cpu().numpy()[back] for x in (lp, lp2, lp3, lp4)], [x.cpu().numpy()[:, back] for x in (g, g3)],
+                    [x.cpu().numpy() for x in (sc, sc3)]))
+    a, b = out
+    for x, y in zip(a[0], b[0]):
+        assert np.all(np.isfinite(x)) and np.allclose(x, y, rtol=1e-13, atol=1e-13)
+    assert np.array_equal(a[1][0], b[1][0]) and np.array_equal(a[1][1], b[1][1])
+    for x, y in zip(a[2], b[2]):
+        assert np.allclose(x, y, rtol=1e-12, atol=1e-12 * np.abs(x).max())
+    for c in range(0, 128, 7):
+        ref = orc.logp(0, V[c, : n[c]])
+        assert abs(a[0][0][c] - ref) < (1e-9 if prec == "f64" else 8e-3), (c, a[0][0][c], ref)
+
+
 @pytest.mark.parametrize("prec", ["f32", "f64"])
 def test_bridge_by_vertices_and_by_lanes(rj, prec):
     """The bridge's waves share their chains' vertices or give each lane its
